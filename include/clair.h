@@ -367,7 +367,7 @@ int clair_ctx_stage_times(clair_ctx_t* ctx, const char** names, float* ms, int32
 
 /*
  * Tuning: kernel shape of the mixed path.  group = lanes that solve one row
- * of |N| <= 8 (1, 4 or 8) or the largest |N| the lane-group solver takes
+ * of |N| <= 8 (1, 4 or 8; 8 runs the four-lane solver too) or the largest |N| the lane-group solver takes
  * (16 or 32, one lane per block row); rows with larger blocks go to the
  * workgroup-per-row path.  wg_threads = threads per workgroup (64, 128 or
  * 256), chunk = fine points per workgroup in the symbolic pass (multiple of

@@ -536,7 +536,10 @@ int enqueue_numeric(clair_ctx* c, Batch& b, hipStream_t s, bool timing, const Co
   if (!known || known->nA > 0) {
     if (c->group == 1) {
       HIPCHK(launch_rows8(b.w, c->wg_threads, c->cus, s));
-    } else if (c->group == 4) {
+    } else if (c->group <= 8) {
+      // 4 and 8 both take the quad solver: eight lanes per row were slower on
+      // every batch (105 against 134 us on 16 matrices of 129^2 to 515^2,
+      // 667 against 990 us on 64 of 64^2 to 768^2)
       HIPCHK(launch_quad8(b.w, c->wg_threads, c->cus, s));
     } else {
       HIPCHK(launch_numeric(b.w, 0, c->group, c->group, c->wg_threads, c->cus, s));
@@ -1764,7 +1767,7 @@ int clair_autotune(clair_ctx_t* c, int32_t nmat, const clair_csr_t* A, const int
   }
   // candidates for the bin-A bound, from the histogram: 16 and 32 lanes per
   // row only when rows above 8 (16) points exist
-  std::vector<int> groups = {1, 4, 8};
+  std::vector<int> groups = {1, 4};  // 8 runs the same solver as 4
   if (above8) groups.push_back(16);
   if (above16) groups.push_back(32);
   hipEvent_t e0, e1;

@@ -76,6 +76,9 @@ __device__ __forceinline__ gptr<T> to_global(T* p) {
   return (gptr<T>)p;
 }
 
+// two consecutive int32 at any int32 address (a row's bounds in one load)
+typedef int i2u __attribute__((ext_vector_type(2), aligned(4)));
+
 struct GDesc {
   gptr<const int32_t> rp;
   gptr<const int32_t> ci;

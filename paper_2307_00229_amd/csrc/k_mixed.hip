@@ -19,15 +19,16 @@
 //   k_scan       one workgroup: chunk bases -> global row numbers, R offsets,
 //                n_c and nnz(R) per matrix, bin sizes, capacity check,
 //                R.row_ptr[n_c].
+//   k_quad8      (k_quad.hip) persistent over the rows, four lanes per row with
+//                |N| <= 8: see there.
 //   k_numeric    persistent over the rows in grid order (each XCD a contiguous
-//                slice), G lanes per row with |N| <= G (bin A, G = GA), or with
-//                GA < |N| <= 32 (bin B, G = 16 or 32): gather of the local
+//                slice), G lanes per row with |N| <= G (bin A, G = GA = 16 or
+//                32), or with GA < |N| <= 32 (bin B, G = 16 or 32): gather of the local
 //                block into LDS, FP32 inverse (Gauss-Jordan) and FP64
 //                iterative refinement of (A[N,N])^T z = -A[i,N]^T, R row
 //                write, projection sums.  Rows whose FP32 factorisation is not
 //                trusted are queued for k_rows_wg.
-//                k_quad8 (4 lanes per row) and k_rows8 (one thread per row)
-//                are the other bin-A solvers.
+//                k_rows8 (one thread per row) is the third bin-A solver.
 //   k_rows_wg    persistent, one workgroup per queued row: for 33..128 points
 //                an FP32 blocked LU with matrix-core trailing updates and FP64
 //                refinement; otherwise, or when that does not converge, FP64 LU
@@ -44,6 +45,7 @@
 
 #include "clair_device.h"
 #include "clair_launch.h"
+#include "mixed_device.h"
 
 namespace clair {
 
@@ -212,197 +214,6 @@ __device__ int block_bfs(int n, int i, int ell, gptr<const int32_t> __restrict__
   return s;
 }
 
-// chunk index of global row g: binary search in chunk_rbase[0..nch]
-__device__ __forceinline__ int row_chunk(const int32_t* rbase, int nch, int g) {
-  int lo = 0, hi = nch - 1;
-  while (lo < hi) {
-    int mid = (lo + hi + 1) >> 1;
-    if (rbase[mid] <= g) lo = mid; else hi = mid - 1;
-  }
-  return lo;
-}
-
-// chunk index of global row g (0 <= g < total rows): the chunk holding the
-// first row of g's block of kRowBlock rows, then a short forward walk
-constexpr int kRowBlockLog = 8;
-__device__ __forceinline__ int row_chunk_fast(const Work& w, int g) {
-  int c = w.row_block_chunk[g >> kRowBlockLog];
-  while (w.chunk_rbase[c + 1] <= g) ++c;
-  return c;
-}
-
-struct RowInfo {
-  int m;     // matrix
-  int i;     // fine index of the C-point
-  int r;     // matrix-local row of R
-  int off;   // first R entry of the row
-  int s;     // |N(i)|
-  int64_t fine0;
-};
-
-// row t of chunk c
-__device__ __forceinline__ RowInfo row_info(const Work& w, int c, int t) {
-  RowInfo ri;
-  ri.m = w.chunk_mat[c];
-  const GDesc d = gview(w.desc[ri.m]);
-  const int64_t base = d.fine0 + (int64_t)(c - d.chunk0) * w.chunk;
-  ri.i = w.clocal[base + t];
-  const int l0 = w.lnz[base + t];
-  const int l1 = (t + 1 < w.chunk_nc[c]) ? w.lnz[base + t + 1] : w.chunk_nnz[c];
-  ri.off = (int)(w.chunk_nzglob[c] - w.st[ri.m].nz_base) + l0;
-  ri.s = l1 - l0 - 1;
-  ri.r = w.chunk_rbase[c] + t - w.st[ri.m].row_base;
-  ri.fine0 = d.fine0;
-  return ri;
-}
-
-__device__ __forceinline__ bool matrix_live(const MatStatus& st) {
-  return st.status != ST_CAPACITY && st.status != ST_INVALID;
-}
-
-// F-entry (i, j) of R at position pos of its matrix: the value, and with a
-// constraint vector the entry joins the list of column j for the projection
-// (list entry link_base + pos, below the matrix's R capacity; one atomic
-// exchange on the list head; the projection orders each list itself, so the
-// exchange order does not matter)
-__device__ __forceinline__ void put_f_entry(const Work& w, const GDesc& d, int64_t fine0, int pos, int j, int i,
-                                            double z) {
-  d.Rci[pos] = j;
-  d.Rva[pos] = z;
-  if (d.B) {
-    const int64_t eg = d.link_base + pos;
-    const int prev = atomicExch(&w.chead[fine0 + j], (int32_t)eg);
-    w.clink[eg] = make_int2(prev, i);
-  }
-}
-
-// Per-lane cache of the chunk a run of consecutive rows lies in: reloaded only
-// when the row index crosses into another chunk, so a row costs one level of
-// (coalesced) per-row loads instead of the chunk -> matrix -> descriptor chain.
-struct ChunkCursor {
-  int c = -1;
-  int rb = 0, re = 0;   // global rows [rb, re) of chunk c
-  int m = 0;
-  int nc = 0;           // C-rows in the chunk
-  int tot = 0;          // nnz(R) of the chunk
-  int zoff = 0;         // R offset of the chunk inside its matrix
-  int rbase_m = 0;      // first global row of the matrix
-  int64_t fbase = 0;    // fine offset of the chunk's first point (batch-wide)
-  int64_t fine0 = 0;    // fine offset of the matrix (batch-wide)
-  bool live = false;
-  GDesc md;             // the matrix's pointers and geometry
-
-  __device__ __forceinline__ void seek(const Work& w, int g) {
-    if (c >= 0 && g >= rb && g < re) return;
-    c = row_chunk_fast(w, g);
-    rb = w.chunk_rbase[c];
-    re = w.chunk_rbase[c + 1];
-    m = w.chunk_mat[c];
-    md = gview(w.desc[m]);
-    const MatStatus& st = w.st[m];
-    nc = w.chunk_nc[c];
-    tot = w.chunk_nnz[c];
-    zoff = (int)(w.chunk_nzglob[c] - st.nz_base);
-    rbase_m = st.row_base;
-    fine0 = md.fine0;
-    fbase = md.fine0 + (int64_t)(c - md.chunk0) * w.chunk;
-    live = matrix_live(st);
-  }
-  // row g (inside the chunk): fine index, R offset and |N|
-  __device__ __forceinline__ void row(const Work& w, int g, int* t, int* i, int* off, int* sz) const {
-    const int tt = g - rb;
-    *t = tt;
-    *i = w.clocal[fbase + tt];
-    const int l0 = w.lnz[fbase + tt];
-    const int l1 = (tt + 1 < nc) ? w.lnz[fbase + tt + 1] : tot;
-    *off = zoff + l0;
-    *sz = l1 - l0 - 1;
-  }
-};
-
-
-// Logical workgroup index: the hardware deals workgroups to the 8 XCDs
-// round-robin (block b runs on XCD b % 8).  Give each XCD a contiguous range
-// of logical indices, so the rows one XCD works on are neighbours in the grid
-// and share its L2.
-__device__ __forceinline__ int xcd_logical_block(int nb) {
-  const int b = blockIdx.x;
-  const int x = b % 8, q = nb / 8, r = nb % 8;
-  return x * q + min(x, r) + b / 8;
-}
-__device__ __forceinline__ int xcd_logical_block() { return xcd_logical_block(gridDim.x); }
-// The same ranges, each walked from its end: the first workgroups of an XCD
-// take the last blocks of its range.
-__device__ __forceinline__ int xcd_logical_block_reversed() {
-  const int nb = gridDim.x;
-  const int b = blockIdx.x;
-  const int x = b % 8, q = nb / 8, r = nb % 8;
-  return x * q + min(x, r) + (q + (x < r ? 1 : 0)) - 1 - b / 8;
-}
-
-// Rows of the persistent numeric kernels: XCD x (= blockIdx.x % 8, the
-// hardware deals workgroups round-robin) owns a contiguous eighth of all
-// rows, and its workgroups take blocks of nb rows from it in turn.  The rows
-// in flight on one XCD at any time are then neighbours, whose blocks share A
-// rows in that XCD's L2 (with a contiguous range per workgroup they would be
-// as many separate streams through A as there are workgroups).
-struct RowBlocks {
-  int xb, xe, k, nx, nb;
-  __device__ __forceinline__ RowBlocks(int total, int nb_) {
-    const int x = blockIdx.x % 8;
-    const int per = (total + 7) / 8;
-    xb = min(total, x * per);
-    xe = min(total, xb + per);
-    nx = (int)gridDim.x / 8 + ((int)(gridDim.x % 8) > x ? 1 : 0);
-    k = blockIdx.x / 8;
-    nb = nb_;
-  }
-  // the j-th block of this workgroup: rows [*b, *e); false past the end
-  __device__ __forceinline__ bool block(int j, int* b, int* e) const {
-    const int64_t s0 = xb + ((int64_t)k + (int64_t)j * nx) * nb;
-    if (s0 >= xe) return false;
-    *b = (int)s0;
-    *e = min(xe, (int)s0 + nb);
-    return true;
-  }
-};
-
-// Most refinement steps of the rows a thread (lane 0 of a group) finished,
-// per matrix: gathered in registers and sent with one global atomic when the
-// thread moves on to another matrix or ends (one atomic per row would meet
-// at a handful of addresses in a batch of many matrices).
-struct RefineMax {
-  int m = -1, v = 0;
-  __device__ __forceinline__ void flush(const Work& w) {
-    if (m >= 0 && v > __hip_atomic_load(&w.st[m].refine_max, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT))
-      atomicMax(&w.st[m].refine_max, v);
-  }
-  __device__ __forceinline__ void add(const Work& w, int mm, int it) {
-    if (mm != m) {
-      flush(w);
-      m = mm;
-      v = 0;
-    }
-    v = max(v, it);
-  }
-};
-
-__device__ __forceinline__ int lane_id() { return threadIdx.x & 63; }
-
-// wave-aggregated queue append: every lane with `want` gets a distinct slot
-// (or -1 once the queue is full); one atomic per wave
-__device__ __forceinline__ int wave_append(bool want, int32_t* counter, int cap) {
-  const uint64_t mask = __ballot(want);
-  if (!mask) return -1;
-  const int leader = __ffsll((unsigned long long)mask) - 1;
-  int base = 0;
-  if (lane_id() == leader) base = atomicAdd(counter, __popcll(mask));
-  base = __shfl(base, leader, 64);
-  const int rank = __popcll(mask & ((1ull << lane_id()) - 1ull));
-  const int slot = base + rank;
-  return (want && slot < cap) ? slot : -1;
-}
-
 // ---------------------------------------------------------------------------
 // validation: CSR sorted, in range; cf is not checked (any nonzero is C)
 // ---------------------------------------------------------------------------
@@ -432,12 +243,6 @@ __global__ void k_validate(Work w) {
 // ---------------------------------------------------------------------------
 // symbolic pass
 // ---------------------------------------------------------------------------
-
-// rows the small solvers take: |N| <= 8 for the thread-per-row solver
-// (GA == 1), |N| <= GA for the lane-group solver
-__device__ __forceinline__ int small_limit(int GA) { return GA <= 4 ? 8 : GA; }
-// stride of a row's slot in slotA
-__device__ __forceinline__ int slot_stride(int GA) { return GA <= 4 ? 8 : GA; }
 
 // The compact adjacency of the matrices whose descriptor carries one: the
 // workgroup of logical block b takes 256 * kAdjPP points of chunk
@@ -1046,75 +851,6 @@ struct NumGroupBuf {
   int nb[G];  // sorted N(i), INT32_MAX beyond |N|
 };
 
-// Communication inside a group of G lanes (G = 8, 16 or 32; groups are
-// aligned runs of G lanes of a wavefront).
-//
-// gbi: lane k of the group to all its lanes.  ds_swizzle in bit mode keeps
-// the lane bits above the group (and-mask 32 - G) and sets the rest to k; the
-// pattern is an immediate, so k must fold to a constant (unrolled loops).
-template <int G>
-__device__ __forceinline__ int gbi(int v, int k) {
-  static_assert(G == 2 || G == 4 || G == 8 || G == 16 || G == 32, "group size");
-#define CLAIR_SWZ(K) \
-  case K: return __builtin_amdgcn_ds_swizzle(v, (32 - G) | ((K) << 5));
-  switch (k) {
-    CLAIR_SWZ(0) CLAIR_SWZ(1) CLAIR_SWZ(2) CLAIR_SWZ(3) CLAIR_SWZ(4) CLAIR_SWZ(5) CLAIR_SWZ(6) CLAIR_SWZ(7)
-    CLAIR_SWZ(8) CLAIR_SWZ(9) CLAIR_SWZ(10) CLAIR_SWZ(11) CLAIR_SWZ(12) CLAIR_SWZ(13) CLAIR_SWZ(14) CLAIR_SWZ(15)
-    CLAIR_SWZ(16) CLAIR_SWZ(17) CLAIR_SWZ(18) CLAIR_SWZ(19) CLAIR_SWZ(20) CLAIR_SWZ(21) CLAIR_SWZ(22) CLAIR_SWZ(23)
-    CLAIR_SWZ(24) CLAIR_SWZ(25) CLAIR_SWZ(26) CLAIR_SWZ(27) CLAIR_SWZ(28) CLAIR_SWZ(29) CLAIR_SWZ(30)
-    default: return __builtin_amdgcn_ds_swizzle(v, (32 - G) | (31 << 5));
-  }
-#undef CLAIR_SWZ
-}
-template <int G>
-__device__ __forceinline__ float gbf(float v, int k) { return __int_as_float(gbi<G>(__float_as_int(v), k)); }
-
-// gpart: the value of a partner lane for a butterfly-like reduction.  Steps 1
-// and 2 pair lanes inside a quad (DPP quad_perm [1,0,3,2] and [2,3,0,1]), step
-// 4 mirrors the halves of 8 lanes (DPP row_half_mirror), step 8 mirrors the
-// halves of 16 (DPP row_mirror), step 16 swaps the halves of 32 (ds_swizzle
-// xor 16).  After the steps up to G/2 every lane holds the group's reduction.
-template <int STEP>
-__device__ __forceinline__ int gpart(int v) {
-  if constexpr (STEP == 1) return __builtin_amdgcn_update_dpp(v, v, 0xB1, 0xF, 0xF, false);
-  else if constexpr (STEP == 2) return __builtin_amdgcn_update_dpp(v, v, 0x4E, 0xF, 0xF, false);
-  else if constexpr (STEP == 4) return __builtin_amdgcn_update_dpp(v, v, 0x141, 0xF, 0xF, false);
-  else if constexpr (STEP == 8) return __builtin_amdgcn_update_dpp(v, v, 0x140, 0xF, 0xF, false);
-  else return __builtin_amdgcn_ds_swizzle(v, 0x1f | (0x10 << 10));
-}
-template <int STEP>
-__device__ __forceinline__ double gpartd(double v) {
-  return __hiloint2double(gpart<STEP>(__double2hiint(v)), gpart<STEP>(__double2loint(v)));
-}
-
-template <int G>
-__device__ __forceinline__ float group_maxf(float v) {
-  v = fmaxf(v, __int_as_float(gpart<1>(__float_as_int(v))));
-  if constexpr (G >= 4) v = fmaxf(v, __int_as_float(gpart<2>(__float_as_int(v))));
-  if constexpr (G >= 8) v = fmaxf(v, __int_as_float(gpart<4>(__float_as_int(v))));
-  if constexpr (G >= 16) v = fmaxf(v, __int_as_float(gpart<8>(__float_as_int(v))));
-  if constexpr (G >= 32) v = fmaxf(v, __int_as_float(gpart<16>(__float_as_int(v))));
-  return v;
-}
-template <int G>
-__device__ __forceinline__ double group_maxd(double v) {
-  v = fmax(v, gpartd<1>(v));
-  if constexpr (G >= 4) v = fmax(v, gpartd<2>(v));
-  if constexpr (G >= 8) v = fmax(v, gpartd<4>(v));
-  if constexpr (G >= 16) v = fmax(v, gpartd<8>(v));
-  if constexpr (G >= 32) v = fmax(v, gpartd<16>(v));
-  return v;
-}
-template <int G>
-__device__ __forceinline__ int group_ori(int v) {
-  v |= gpart<1>(v);
-  if constexpr (G >= 4) v |= gpart<2>(v);
-  if constexpr (G >= 8) v |= gpart<4>(v);
-  if constexpr (G >= 16) v |= gpart<8>(v);
-  if constexpr (G >= 32) v |= gpart<16>(v);
-  return v;
-}
-
 // y_lane = sum_p Kinv[lane][p] v_p: the group's right-hand side goes through
 // LDS once (v_p from lane p), then every lane reads all of it (broadcast
 // reads, no dependence between the steps).  kf holds this lane's row of the
@@ -1129,19 +865,6 @@ __device__ __forceinline__ float inv_apply(const float (&kf)[SM], float* ybuf, b
   wave_sync();  // the buffer is reused by the next call
   return y;
 }
-
-// Position of key in the G sorted entries nb[0..G) (padded with INT32_MAX),
-// or -1: a branch-free lower bound of fixed depth log2(G).  Several searches
-// in a row have no loop between them, so their LDS reads overlap.
-template <int G>
-__device__ __forceinline__ int find_pos(const int* nb, int key) {
-  int pos = 0;
-#pragma unroll
-  for (int step = G / 2; step >= 1; step >>= 1) pos += (nb[pos + step - 1] < key) ? step : 0;
-  return (pos < G && nb[pos] == key) ? pos : -1;
-}
-
-constexpr int kRefineMax = 5;
 
 // G lanes per row, blocks of up to SM <= G points.  which = 0: bin A
 // (|N| <= G = GA); which = 1: bin B (GA < |N| <= 32), rows with |N| > SM are
@@ -1729,387 +1452,6 @@ __global__ __launch_bounds__(NT) void k_lanes(Work w, int which) {
   }
   }
   if (lane == 0) rmx.flush(w);
-}
-
-// ---------------------------------------------------------------------------
-// numeric pass, four lanes (a quad) per row with |N| <= 8.  Lane l of the quad
-// owns rows 2l and 2l+1 of K = (A[N,N])^T.  The block is transposed once
-// through LDS after the gather; the LU, both triangular solves and the FP64
-// residual then broadcast within the quad with DPP quad permutations
-// (register moves, no LDS round trip).  A row of at most four points takes
-// the 4 x 4 corner only, one block row per lane.  The kernel runs at three
-// wavefronts per SIMD: at four the compiler spills the two paths' registers.
-// ---------------------------------------------------------------------------
-// lane src of the quad, to all four (src is a constant once the calling loops
-// are unrolled, so the switch folds to one DPP move)
-__device__ __forceinline__ int qbi(int v, int src) {
-  switch (src) {
-    case 0: return __builtin_amdgcn_mov_dpp(v, 0x00, 0xF, 0xF, false);
-    case 1: return __builtin_amdgcn_mov_dpp(v, 0x55, 0xF, 0xF, false);
-    case 2: return __builtin_amdgcn_mov_dpp(v, 0xAA, 0xF, 0xF, false);
-    default: return __builtin_amdgcn_mov_dpp(v, 0xFF, 0xF, 0xF, false);
-  }
-}
-__device__ __forceinline__ float qb(float v, int src) { return __int_as_float(qbi(__float_as_int(v), src)); }
-__device__ __forceinline__ double qbd(double v, int src) {
-  return __hiloint2double(qbi(__double2hiint(v), src), qbi(__double2loint(v), src));
-}
-// quad reductions: partners lane^1 and lane^2 (quad_perm [1,0,3,2] and [2,3,0,1])
-__device__ __forceinline__ float qmaxf(float v) {
-  v = fmaxf(v, __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(v), 0xB1, 0xF, 0xF, false)));
-  v = fmaxf(v, __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(v), 0x4E, 0xF, 0xF, false)));
-  return v;
-}
-__device__ __forceinline__ double qxd(double v, int ctrl_is_b1) {
-  const int lo = ctrl_is_b1 ? __builtin_amdgcn_mov_dpp(__double2loint(v), 0xB1, 0xF, 0xF, false)
-                            : __builtin_amdgcn_mov_dpp(__double2loint(v), 0x4E, 0xF, 0xF, false);
-  const int hi = ctrl_is_b1 ? __builtin_amdgcn_mov_dpp(__double2hiint(v), 0xB1, 0xF, 0xF, false)
-                            : __builtin_amdgcn_mov_dpp(__double2hiint(v), 0x4E, 0xF, 0xF, false);
-  return __hiloint2double(hi, lo);
-}
-__device__ __forceinline__ double qmaxd(double v) {
-  v = fmax(v, qxd(v, 1));
-  v = fmax(v, qxd(v, 0));
-  return v;
-}
-__device__ __forceinline__ int qori(int v) {
-  v |= __builtin_amdgcn_mov_dpp(v, 0xB1, 0xF, 0xF, false);
-  v |= __builtin_amdgcn_mov_dpp(v, 0x4E, 0xF, 0xF, false);
-  return v;
-}
-
-constexpr int kQG = 5;  // entries per gather round of k_quad8
-
-struct QuadBuf {
-  double K[8 * 8];  // gathered block, row q of K at stride 8
-  double f[8];
-  int nb[8];
-};
-
-// value of register slot S (0/1) of lane SRC = row 2*SRC+S, broadcast in the quad
-#define QB_ROW(arr0, arr1, k, p) ((k) & 1 ? qb(arr1[p], (k) / 2) : qb(arr0[p], (k) / 2))
-
-template <int NT>
-__global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(3))) void k_quad8(Work w) {
-  constexpr int NQ = NT / 4;
-  __shared__ QuadBuf qbuf[NQ];
-  const int tid = threadIdx.x;
-  const int qd = tid >> 2;
-  const int ql = tid & 3;
-  QuadBuf& B = qbuf[qd];
-  if (w.cnt->nA == 0) return;
-  const int total = w.cnt->total_rows;
-  const RowBlocks rbk(total, 4 * NQ);
-  int r0, r1;
-  if (!rbk.block(0, &r0, &r1)) return;
-  RefineMax rmx;
-  const int q0 = 2 * ql, q1 = 2 * ql + 1;  // this lane's rows of K
-  ChunkCursor cc;
-
-  for (int jb = 0; rbk.block(jb, &r0, &r1); ++jb) {
-  for (int g = r0 + qd; g < r1; g += NQ) {  // quad-uniform
-    cc.seek(w, g);
-    int t, i, off, s;
-    cc.row(w, g, &t, &i, &off, &s);
-    if (s > 8 || !cc.live) continue;
-    const int c = cc.c;
-    MatStatus* st = &w.st[cc.m];
-    const GDesc& d = cc.md;
-    RowInfo ri;
-    ri.m = cc.m;
-    ri.i = i;
-    ri.r = g - cc.rbase_m;
-    ri.off = off;
-    ri.s = s;
-    ri.fine0 = cc.fine0;
-    const int64_t fbase = cc.fbase;
-    const int2 nn = *reinterpret_cast<const int2*>(w.slotA + (fbase + t) * 8 + q0);
-    const int n0 = q0 < s ? nn.x : 0x7fffffff;
-    const int n1 = q1 < s ? nn.y : 0x7fffffff;
-    if (ql == 0) d.Rrp[ri.r] = ri.off;
-    B.nb[q0] = n0;
-    B.nb[q1] = n1;
-#pragma unroll
-    for (int u = 0; u < 16; ++u) {  // zero the block, identity on the padding
-      const int idx = ql * 16 + u;
-      const int rq = idx / 8, cp = idx % 8;
-      B.K[idx] = (rq == cp && rq >= s) ? 1.0 : 0.0;
-    }
-    B.f[q0] = 0.0;
-    B.f[q1] = 0.0;
-    wave_sync();
-    // gather: lane l walks rows N_{2l}, N_{2l+1} of A (columns 2l, 2l+1 of
-    // K) side by side, kQG entries of each at a time (a five-point row in
-    // one round)
-    {
-      int a0 = 0, a1 = 0, b0 = 0, b1 = 0;
-      if (q0 < s) { a0 = d.rp[n0]; a1 = d.rp[n0 + 1]; }
-      if (q1 < s) { b0 = d.rp[n1]; b1 = d.rp[n1 + 1]; }
-      // row i's bounds and its first eight entries (two per lane) go out with
-      // the block rows' loads
-      const int i0 = d.rp[i], i1 = d.rp[i + 1];
-      int kf[2];
-      double vf[2];
-#pragma unroll
-      for (int h = 0; h < 2; ++h) {
-        const int e = i0 + ql + 4 * h;
-        kf[h] = -1;
-        vf[h] = 0.0;
-        if (e < i1) { kf[h] = d.ci[e]; vf[h] = d.va[e]; }
-      }
-      for (int o = 0; a0 + o < a1 || b0 + o < b1; o += kQG) {
-        int ka[kQG], kb[kQG];
-        double va_[kQG], vb_[kQG];
-#pragma unroll
-        for (int j = 0; j < kQG; ++j) {
-          ka[j] = -1;
-          kb[j] = -1;
-          va_[j] = 0.0;
-          vb_[j] = 0.0;
-          if (a0 + o + j < a1) { ka[j] = d.ci[a0 + o + j]; va_[j] = d.va[a0 + o + j]; }
-          if (b0 + o + j < b1) { kb[j] = d.ci[b0 + o + j]; vb_[j] = d.va[b0 + o + j]; }
-        }
-#pragma unroll
-        for (int j = 0; j < kQG; ++j) {
-          const int qa = find_pos<8>(B.nb, ka[j]);
-          const int qb_ = find_pos<8>(B.nb, kb[j]);
-          if (qa >= 0) B.K[qa * 8 + q0] = va_[j];
-          if (qb_ >= 0) B.K[qb_ * 8 + q1] = vb_[j];
-        }
-      }
-#pragma unroll
-      for (int h = 0; h < 2; ++h) {
-        const int qq = find_pos<8>(B.nb, kf[h]);
-        if (qq >= 0) B.f[qq] = -vf[h];
-      }
-      for (int e = i0 + ql + 8; e < i1; e += 4) {  // rows of more than eight entries
-        const int qq = find_pos<8>(B.nb, d.ci[e]);
-        if (qq >= 0) B.f[qq] = -d.va[e];
-      }
-    }
-    wave_sync();
-    if (s <= 4) {
-      // Blocks of at most four points (every row at distance 1 on a
-      // five-point graph): lane l owns row l of the 4 x 4 corner of K (the
-      // padding rows are identity there as in the full block), so the LU, the
-      // substitutions and the residual take four steps instead of eight.
-      const int q = ql;
-      double kq[4];
-      float amax = 0.f;
-      double rs = 0.0;
-#pragma unroll
-      for (int p = 0; p < 4; ++p) {
-        kq[p] = B.K[q * 8 + p];
-        amax = fmaxf(amax, (float)fabs(kq[p]));
-        rs += fabs(kq[p]);
-      }
-      const double fq = B.f[q];
-      const int nq = B.nb[q];  // INT32_MAX on padding rows
-      amax = qmaxf(amax);
-      const double knorm = qmaxd(rs);
-      const double fnorm = qmaxd(fabs(fq));
-      int ex = 0;
-      frexpf(amax, &ex);
-      const double scale = ldexp(1.0, -ex);
-      float a[4];
-#pragma unroll
-      for (int p = 0; p < 4; ++p) a[p] = (float)(kq[p] * scale);
-      int bad = !(amax > 0.f) || !(amax < 3.0e38f);
-      float ui = 1.f;
-#pragma unroll
-      for (int k = 0; k < 4; ++k) {
-        float pr[4];
-#pragma unroll
-        for (int p = k; p < 4; ++p) pr[p] = qb(a[p], k);
-        bad |= !(fabsf(pr[k]) >= 0x1p-24f);
-        const float pinv = __builtin_amdgcn_rcpf(pr[k]);
-        if (q == k) ui = pinv;
-        if (q > k) {
-          const float l = a[k] * pinv;
-          a[k] = l;
-#pragma unroll
-          for (int p = k + 1; p < 4; ++p) a[p] = fmaf(-l, pr[p], a[p]);
-        }
-      }
-      bad = qori(bad);
-      double z = 0.0;
-      int it = 0;
-      bool conv = false;
-      if (!bad) {
-        // K y = rhs for this lane's entry of y
-        auto solve4 = [&](float y) {
-#pragma unroll
-          for (int k = 0; k < 4; ++k) {  // forward, unit lower
-            const float yk = qb(y, k);
-            if (q > k) y = fmaf(-a[k], yk, y);
-          }
-#pragma unroll
-          for (int k = 3; k >= 0; --k) {  // backward, upper
-            if (q == k) y *= ui;
-            const float zk = qb(y, k);
-            if (q < k) y = fmaf(-a[k], zk, y);
-          }
-          return y;
-        };
-        z = solve4((float)(fq * scale));
-        for (it = 1; it <= kRefineMax; ++it) {
-          double r = fq;
-#pragma unroll
-          for (int p = 0; p < 4; ++p) r = fma(-kq[p], qbd(z, p), r);
-          const double rn = qmaxd(fabs(r));
-          const double zn = qmaxd(fabs(z));
-          if (rn <= 0x1p-47 * (knorm * zn + fnorm)) { conv = true; break; }
-          z += (double)solve4((float)(r * scale));
-        }
-        conv = conv && (z == z);
-        conv = qori(conv ? 0 : 1) == 0;
-      }
-      if (!conv) {
-        if (ql == 0) {
-          const int qc = atomicAdd(&w.cnt->nC, 1);
-          if (qc < w.capC) w.binC[qc] = c * w.chunk + t;
-          else flag_row(st, ST_UNSUPPORTED, i);
-        }
-        continue;
-      }
-      if (ql == 0) rmx.add(w, ri.m, it);
-      const int below = nq < i ? 1 : 0;
-      const int b2 = below + __builtin_amdgcn_mov_dpp(below, 0xB1, 0xF, 0xF, false);
-      const int dpos4 = b2 + __builtin_amdgcn_mov_dpp(b2, 0x4E, 0xF, 0xF, false);
-      if (q < s) put_f_entry(w, d, ri.fine0, ri.off + q + (q >= dpos4 ? 1 : 0), nq, i, z);
-      if (ql == 0) {
-        d.Rci[ri.off + dpos4] = i;
-        d.Rva[ri.off + dpos4] = 1.0;
-      }
-      continue;
-    }
-    // rows q0, q1 of K (FP64), scaled FP32 copies
-    double k0[8], k1[8];
-    float amax = 0.f;
-    double rs0 = 0.0, rs1 = 0.0;
-#pragma unroll
-    for (int p = 0; p < 8; ++p) {
-      k0[p] = B.K[q0 * 8 + p];
-      k1[p] = B.K[q1 * 8 + p];
-      amax = fmaxf(amax, fmaxf((float)fabs(k0[p]), (float)fabs(k1[p])));
-      rs0 += fabs(k0[p]);
-      rs1 += fabs(k1[p]);
-    }
-    const double f0 = B.f[q0], f1 = B.f[q1];
-    amax = qmaxf(amax);
-    const double knorm = qmaxd(fmax(rs0, rs1));
-    const double fnorm = qmaxd(fmax(fabs(f0), fabs(f1)));
-    int ex = 0;
-    frexpf(amax, &ex);
-    const double scale = ldexp(1.0, -ex);
-    float a0[8], a1[8];
-#pragma unroll
-    for (int p = 0; p < 8; ++p) {
-      a0[p] = (float)(k0[p] * scale);
-      a1[p] = (float)(k1[p] * scale);
-    }
-    // LU without pivoting: lane-local rows, pivot rows broadcast in the quad
-    int bad = !(amax > 0.f) || !(amax < 3.0e38f);
-    float ui0 = 1.f, ui1 = 1.f;
-#pragma unroll
-    for (int k = 0; k < 8; ++k) {
-      float pr[8];
-#pragma unroll
-      for (int p = k; p < 8; ++p) pr[p] = QB_ROW(a0, a1, k, p);
-      const float piv = pr[k];
-      bad |= !(fabsf(piv) >= 0x1p-24f);
-      const float pinv = __builtin_amdgcn_rcpf(piv);
-      if (q0 == k) ui0 = pinv;
-      if (q1 == k) ui1 = pinv;
-      if (q0 > k) {
-        const float l = a0[k] * pinv;
-        a0[k] = l;
-#pragma unroll
-        for (int p = k + 1; p < 8; ++p) a0[p] = fmaf(-l, pr[p], a0[p]);
-      }
-      if (q1 > k) {
-        const float l = a1[k] * pinv;
-        a1[k] = l;
-#pragma unroll
-        for (int p = k + 1; p < 8; ++p) a1[p] = fmaf(-l, pr[p], a1[p]);
-      }
-    }
-    bad = qori(bad);
-
-    double z0 = 0.0, z1 = 0.0;
-    int it = 0;
-    bool conv = false;
-    if (!bad) {
-      // solve K y = rhs for this lane's two entries y0, y1
-      auto solve = [&](float y0, float y1, float* o0, float* o1) {
-#pragma unroll
-        for (int k = 0; k < 8; ++k) {  // forward, unit lower
-          const float yk = (k & 1) ? qb(y1, k / 2) : qb(y0, k / 2);
-          if (q0 > k) y0 = fmaf(-a0[k], yk, y0);
-          if (q1 > k) y1 = fmaf(-a1[k], yk, y1);
-        }
-#pragma unroll
-        for (int k = 7; k >= 0; --k) {  // backward, upper
-          if (q0 == k) y0 *= ui0;
-          if (q1 == k) y1 *= ui1;
-          const float zk = (k & 1) ? qb(y1, k / 2) : qb(y0, k / 2);
-          if (q0 < k) y0 = fmaf(-a0[k], zk, y0);
-          if (q1 < k) y1 = fmaf(-a1[k], zk, y1);
-        }
-        *o0 = y0;
-        *o1 = y1;
-      };
-      float y0, y1;
-      solve((float)(f0 * scale), (float)(f1 * scale), &y0, &y1);
-      z0 = y0;
-      z1 = y1;
-      for (it = 1; it <= kRefineMax; ++it) {
-        // r = f - K z in FP64: all of z broadcast in the quad
-        // (the FP64 rows are read from LDS again rather than kept live)
-        double r0 = f0, r1 = f1;
-#pragma unroll
-        for (int p = 0; p < 8; ++p) {
-          const double zp = (p & 1) ? qbd(z1, p / 2) : qbd(z0, p / 2);
-          r0 = fma(-B.K[q0 * 8 + p], zp, r0);
-          r1 = fma(-B.K[q1 * 8 + p], zp, r1);
-        }
-        const double rn = qmaxd(fmax(fabs(r0), fabs(r1)));
-        const double zn = qmaxd(fmax(fabs(z0), fabs(z1)));
-        if (rn <= 0x1p-47 * (knorm * zn + fnorm)) { conv = true; break; }
-        float d0, d1;
-        solve((float)(r0 * scale), (float)(r1 * scale), &d0, &d1);
-        z0 += (double)d0;
-        z1 += (double)d1;
-      }
-      conv = conv && (z0 == z0) && (z1 == z1);
-      conv = qori(conv ? 0 : 1) == 0;
-    }
-    if (!conv) {
-      // FP32 factorisation not trusted: the workgroup solver redoes the row in FP64
-      if (ql == 0) {
-        const int qc = atomicAdd(&w.cnt->nC, 1);
-        if (qc < w.capC) w.binC[qc] = c * w.chunk + t;
-        else flag_row(st, ST_UNSUPPORTED, i);
-      }
-      continue;
-    }
-    if (ql == 0) rmx.add(w, ri.m, it);
-    // R row
-    const int dpos_l = (n0 < i ? 1 : 0) + (n1 < i ? 1 : 0);
-    const int dpos = dpos_l + __builtin_amdgcn_mov_dpp(dpos_l, 0xB1, 0xF, 0xF, false);
-    const int dposq = dpos + __builtin_amdgcn_mov_dpp(dpos, 0x4E, 0xF, 0xF, false);
-#pragma unroll
-    for (int h = 0; h < 2; ++h) {
-      const int p = q0 + h;
-      if (p < s) put_f_entry(w, d, ri.fine0, ri.off + p + (p >= dposq ? 1 : 0), h ? n1 : n0, i, h ? z1 : z0);
-    }
-    if (ql == 0) {
-      d.Rci[ri.off + dposq] = i;
-      d.Rva[ri.off + dposq] = 1.0;
-    }
-  }
-  }
-  if (ql == 0) rmx.flush(w);
 }
 
 // ---------------------------------------------------------------------------
@@ -3286,9 +2628,6 @@ hipError_t launch_numeric(const Work& w, int which, int group, int sm, int wg_th
     hipLaunchKernelGGL((k_numeric<GG, NTT, SMM>), dim3(blocks), dim3(NTT), 0, s, w, which);             \
     return hipGetLastError();                                                                           \
   }
-  CLAIR_NUM(8, 256, 8)
-  CLAIR_NUM(8, 128, 8)
-  CLAIR_NUM(8, 64, 8)
   CLAIR_NUM(16, 256, 16)
   CLAIR_NUM(16, 128, 16)
   CLAIR_NUM(16, 64, 16)
@@ -3347,23 +2686,6 @@ hipError_t launch_rows8(const Work& w, int wg_threads, int cus, hipStream_t s) {
   CLAIR_R8(128)
   CLAIR_R8(64)
 #undef CLAIR_R8
-  return hipErrorInvalidValue;
-}
-
-hipError_t launch_quad8(const Work& w, int wg_threads, int cus, hipStream_t s) {
-#define CLAIR_Q8(NTT)                                                                       \
-  if (wg_threads == NTT) {                                                                  \
-    int per = 0;                                                                            \
-    hipError_t e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per, k_quad8<NTT>, NTT, 0); \
-    if (e != hipSuccess) return e;                                                          \
-    const int blocks = (std::max(1, per) * cus + 7) / 8 * 8;                               \
-    hipLaunchKernelGGL((k_quad8<NTT>), dim3(blocks), dim3(NTT), 0, s, w);                   \
-    return hipGetLastError();                                                               \
-  }
-  CLAIR_Q8(256)
-  CLAIR_Q8(128)
-  CLAIR_Q8(64)
-#undef CLAIR_Q8
   return hipErrorInvalidValue;
 }
 

@@ -1,0 +1,296 @@
+// mixed_device.h -- device code shared by the kernels of the mixed form
+// (k_mixed.hip, k_quad.hip): row bookkeeping, work distribution, lane-group
+// communication.
+#pragma once
+
+#include <hip/hip_runtime.h>
+#include <stdint.h>
+
+#include "clair_device.h"
+
+namespace clair {
+
+namespace {
+
+// chunk index of global row g: binary search in chunk_rbase[0..nch]
+__device__ __forceinline__ int row_chunk(const int32_t* rbase, int nch, int g) {
+  int lo = 0, hi = nch - 1;
+  while (lo < hi) {
+    int mid = (lo + hi + 1) >> 1;
+    if (rbase[mid] <= g) lo = mid; else hi = mid - 1;
+  }
+  return lo;
+}
+
+// chunk index of global row g (0 <= g < total rows): the chunk holding the
+// first row of g's block of kRowBlock rows, then a short forward walk
+constexpr int kRowBlockLog = 8;
+__device__ __forceinline__ int row_chunk_fast(const Work& w, int g) {
+  int c = w.row_block_chunk[g >> kRowBlockLog];
+  while (w.chunk_rbase[c + 1] <= g) ++c;
+  return c;
+}
+
+struct RowInfo {
+  int m;     // matrix
+  int i;     // fine index of the C-point
+  int r;     // matrix-local row of R
+  int off;   // first R entry of the row
+  int s;     // |N(i)|
+  int64_t fine0;
+};
+
+// row t of chunk c
+__device__ __forceinline__ RowInfo row_info(const Work& w, int c, int t) {
+  RowInfo ri;
+  ri.m = w.chunk_mat[c];
+  const GDesc d = gview(w.desc[ri.m]);
+  const int64_t base = d.fine0 + (int64_t)(c - d.chunk0) * w.chunk;
+  ri.i = w.clocal[base + t];
+  const int l0 = w.lnz[base + t];
+  const int l1 = (t + 1 < w.chunk_nc[c]) ? w.lnz[base + t + 1] : w.chunk_nnz[c];
+  ri.off = (int)(w.chunk_nzglob[c] - w.st[ri.m].nz_base) + l0;
+  ri.s = l1 - l0 - 1;
+  ri.r = w.chunk_rbase[c] + t - w.st[ri.m].row_base;
+  ri.fine0 = d.fine0;
+  return ri;
+}
+
+__device__ __forceinline__ bool matrix_live(const MatStatus& st) {
+  return st.status != ST_CAPACITY && st.status != ST_INVALID;
+}
+
+// F-entry (i, j) of R at position pos of its matrix: the value, and with a
+// constraint vector the entry joins the list of column j for the projection
+// (list entry link_base + pos, below the matrix's R capacity; one atomic
+// exchange on the list head; the projection orders each list itself, so the
+// exchange order does not matter)
+__device__ __forceinline__ void put_f_entry(const Work& w, const GDesc& d, int64_t fine0, int pos, int j, int i,
+                                            double z) {
+  d.Rci[pos] = j;
+  d.Rva[pos] = z;
+  if (d.B) {
+    const int64_t eg = d.link_base + pos;
+    const int prev = atomicExch(&w.chead[fine0 + j], (int32_t)eg);
+    w.clink[eg] = make_int2(prev, i);
+  }
+}
+
+// Per-lane cache of the chunk a run of consecutive rows lies in: reloaded only
+// when the row index crosses into another chunk, so a row costs one level of
+// (coalesced) per-row loads instead of the chunk -> matrix -> descriptor chain.
+struct ChunkCursor {
+  int c = -1;
+  int rb = 0, re = 0;   // global rows [rb, re) of chunk c
+  int m = 0;
+  int nc = 0;           // C-rows in the chunk
+  int tot = 0;          // nnz(R) of the chunk
+  int zoff = 0;         // R offset of the chunk inside its matrix
+  int rbase_m = 0;      // first global row of the matrix
+  int64_t fbase = 0;    // fine offset of the chunk's first point (batch-wide)
+  int64_t fine0 = 0;    // fine offset of the matrix (batch-wide)
+  bool live = false;
+  GDesc md;             // the matrix's pointers and geometry
+
+  __device__ __forceinline__ void seek(const Work& w, int g) {
+    if (c >= 0 && g >= rb && g < re) return;
+    c = row_chunk_fast(w, g);
+    rb = w.chunk_rbase[c];
+    re = w.chunk_rbase[c + 1];
+    m = w.chunk_mat[c];
+    md = gview(w.desc[m]);
+    const MatStatus& st = w.st[m];
+    nc = w.chunk_nc[c];
+    tot = w.chunk_nnz[c];
+    zoff = (int)(w.chunk_nzglob[c] - st.nz_base);
+    rbase_m = st.row_base;
+    fine0 = md.fine0;
+    fbase = md.fine0 + (int64_t)(c - md.chunk0) * w.chunk;
+    live = matrix_live(st);
+  }
+  // row g (inside the chunk): fine index, R offset and |N|
+  __device__ __forceinline__ void row(const Work& w, int g, int* t, int* i, int* off, int* sz) const {
+    const int tt = g - rb;
+    *t = tt;
+    *i = w.clocal[fbase + tt];
+    const int l0 = w.lnz[fbase + tt];
+    const int l1 = (tt + 1 < nc) ? w.lnz[fbase + tt + 1] : tot;
+    *off = zoff + l0;
+    *sz = l1 - l0 - 1;
+  }
+};
+
+
+// Logical workgroup index: the hardware deals workgroups to the 8 XCDs
+// round-robin (block b runs on XCD b % 8).  Give each XCD a contiguous range
+// of logical indices, so the rows one XCD works on are neighbours in the grid
+// and share its L2.
+__device__ __forceinline__ int xcd_logical_block(int nb) {
+  const int b = blockIdx.x;
+  const int x = b % 8, q = nb / 8, r = nb % 8;
+  return x * q + min(x, r) + b / 8;
+}
+__device__ __forceinline__ int xcd_logical_block() { return xcd_logical_block(gridDim.x); }
+// The same ranges, each walked from its end: the first workgroups of an XCD
+// take the last blocks of its range.
+__device__ __forceinline__ int xcd_logical_block_reversed() {
+  const int nb = gridDim.x;
+  const int b = blockIdx.x;
+  const int x = b % 8, q = nb / 8, r = nb % 8;
+  return x * q + min(x, r) + (q + (x < r ? 1 : 0)) - 1 - b / 8;
+}
+
+// Rows of the persistent numeric kernels: XCD x (= blockIdx.x % 8, the
+// hardware deals workgroups round-robin) owns a contiguous eighth of all
+// rows, and its workgroups take blocks of nb rows from it in turn.  The rows
+// in flight on one XCD at any time are then neighbours, whose blocks share A
+// rows in that XCD's L2 (with a contiguous range per workgroup they would be
+// as many separate streams through A as there are workgroups).
+struct RowBlocks {
+  int xb, xe, k, nx, nb;
+  __device__ __forceinline__ RowBlocks(int total, int nb_) {
+    const int x = blockIdx.x % 8;
+    const int per = (total + 7) / 8;
+    xb = min(total, x * per);
+    xe = min(total, xb + per);
+    nx = (int)gridDim.x / 8 + ((int)(gridDim.x % 8) > x ? 1 : 0);
+    k = blockIdx.x / 8;
+    nb = nb_;
+  }
+  // the j-th block of this workgroup: rows [*b, *e); false past the end
+  __device__ __forceinline__ bool block(int j, int* b, int* e) const {
+    const int64_t s0 = xb + ((int64_t)k + (int64_t)j * nx) * nb;
+    if (s0 >= xe) return false;
+    *b = (int)s0;
+    *e = min(xe, (int)s0 + nb);
+    return true;
+  }
+};
+
+// Most refinement steps of the rows a thread (lane 0 of a group) finished,
+// per matrix: gathered in registers and sent with one global atomic when the
+// thread moves on to another matrix or ends (one atomic per row would meet
+// at a handful of addresses in a batch of many matrices).
+struct RefineMax {
+  int m = -1, v = 0;
+  __device__ __forceinline__ void flush(const Work& w) {
+    if (m >= 0 && v > __hip_atomic_load(&w.st[m].refine_max, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT))
+      atomicMax(&w.st[m].refine_max, v);
+  }
+  __device__ __forceinline__ void add(const Work& w, int mm, int it) {
+    if (mm != m) {
+      flush(w);
+      m = mm;
+      v = 0;
+    }
+    v = max(v, it);
+  }
+};
+
+__device__ __forceinline__ int lane_id() { return threadIdx.x & 63; }
+
+// wave-aggregated queue append: every lane with `want` gets a distinct slot
+// (or -1 once the queue is full); one atomic per wave
+__device__ __forceinline__ int wave_append(bool want, int32_t* counter, int cap) {
+  const uint64_t mask = __ballot(want);
+  if (!mask) return -1;
+  const int leader = __ffsll((unsigned long long)mask) - 1;
+  int base = 0;
+  if (lane_id() == leader) base = atomicAdd(counter, __popcll(mask));
+  base = __shfl(base, leader, 64);
+  const int rank = __popcll(mask & ((1ull << lane_id()) - 1ull));
+  const int slot = base + rank;
+  return (want && slot < cap) ? slot : -1;
+}
+
+// rows the small solvers take: |N| <= 8 for the thread-per-row solver
+// (GA == 1), |N| <= GA for the lane-group solver
+__device__ __forceinline__ int small_limit(int GA) { return GA <= 4 ? 8 : GA; }
+// stride of a row's slot in slotA
+__device__ __forceinline__ int slot_stride(int GA) { return GA <= 4 ? 8 : GA; }
+
+// Communication inside a group of G lanes (G = 8, 16 or 32; groups are
+// aligned runs of G lanes of a wavefront).
+//
+// gbi: lane k of the group to all its lanes.  ds_swizzle in bit mode keeps
+// the lane bits above the group (and-mask 32 - G) and sets the rest to k; the
+// pattern is an immediate, so k must fold to a constant (unrolled loops).
+template <int G>
+__device__ __forceinline__ int gbi(int v, int k) {
+  static_assert(G == 2 || G == 4 || G == 8 || G == 16 || G == 32, "group size");
+#define CLAIR_SWZ(K) \
+  case K: return __builtin_amdgcn_ds_swizzle(v, (32 - G) | ((K) << 5));
+  switch (k) {
+    CLAIR_SWZ(0) CLAIR_SWZ(1) CLAIR_SWZ(2) CLAIR_SWZ(3) CLAIR_SWZ(4) CLAIR_SWZ(5) CLAIR_SWZ(6) CLAIR_SWZ(7)
+    CLAIR_SWZ(8) CLAIR_SWZ(9) CLAIR_SWZ(10) CLAIR_SWZ(11) CLAIR_SWZ(12) CLAIR_SWZ(13) CLAIR_SWZ(14) CLAIR_SWZ(15)
+    CLAIR_SWZ(16) CLAIR_SWZ(17) CLAIR_SWZ(18) CLAIR_SWZ(19) CLAIR_SWZ(20) CLAIR_SWZ(21) CLAIR_SWZ(22) CLAIR_SWZ(23)
+    CLAIR_SWZ(24) CLAIR_SWZ(25) CLAIR_SWZ(26) CLAIR_SWZ(27) CLAIR_SWZ(28) CLAIR_SWZ(29) CLAIR_SWZ(30)
+    default: return __builtin_amdgcn_ds_swizzle(v, (32 - G) | (31 << 5));
+  }
+#undef CLAIR_SWZ
+}
+template <int G>
+__device__ __forceinline__ float gbf(float v, int k) { return __int_as_float(gbi<G>(__float_as_int(v), k)); }
+
+// gpart: the value of a partner lane for a butterfly-like reduction.  Steps 1
+// and 2 pair lanes inside a quad (DPP quad_perm [1,0,3,2] and [2,3,0,1]), step
+// 4 mirrors the halves of 8 lanes (DPP row_half_mirror), step 8 mirrors the
+// halves of 16 (DPP row_mirror), step 16 swaps the halves of 32 (ds_swizzle
+// xor 16).  After the steps up to G/2 every lane holds the group's reduction.
+template <int STEP>
+__device__ __forceinline__ int gpart(int v) {
+  if constexpr (STEP == 1) return __builtin_amdgcn_update_dpp(v, v, 0xB1, 0xF, 0xF, false);
+  else if constexpr (STEP == 2) return __builtin_amdgcn_update_dpp(v, v, 0x4E, 0xF, 0xF, false);
+  else if constexpr (STEP == 4) return __builtin_amdgcn_update_dpp(v, v, 0x141, 0xF, 0xF, false);
+  else if constexpr (STEP == 8) return __builtin_amdgcn_update_dpp(v, v, 0x140, 0xF, 0xF, false);
+  else return __builtin_amdgcn_ds_swizzle(v, 0x1f | (0x10 << 10));
+}
+template <int STEP>
+__device__ __forceinline__ double gpartd(double v) {
+  return __hiloint2double(gpart<STEP>(__double2hiint(v)), gpart<STEP>(__double2loint(v)));
+}
+
+template <int G>
+__device__ __forceinline__ float group_maxf(float v) {
+  v = fmaxf(v, __int_as_float(gpart<1>(__float_as_int(v))));
+  if constexpr (G >= 4) v = fmaxf(v, __int_as_float(gpart<2>(__float_as_int(v))));
+  if constexpr (G >= 8) v = fmaxf(v, __int_as_float(gpart<4>(__float_as_int(v))));
+  if constexpr (G >= 16) v = fmaxf(v, __int_as_float(gpart<8>(__float_as_int(v))));
+  if constexpr (G >= 32) v = fmaxf(v, __int_as_float(gpart<16>(__float_as_int(v))));
+  return v;
+}
+template <int G>
+__device__ __forceinline__ double group_maxd(double v) {
+  v = fmax(v, gpartd<1>(v));
+  if constexpr (G >= 4) v = fmax(v, gpartd<2>(v));
+  if constexpr (G >= 8) v = fmax(v, gpartd<4>(v));
+  if constexpr (G >= 16) v = fmax(v, gpartd<8>(v));
+  if constexpr (G >= 32) v = fmax(v, gpartd<16>(v));
+  return v;
+}
+template <int G>
+__device__ __forceinline__ int group_ori(int v) {
+  v |= gpart<1>(v);
+  if constexpr (G >= 4) v |= gpart<2>(v);
+  if constexpr (G >= 8) v |= gpart<4>(v);
+  if constexpr (G >= 16) v |= gpart<8>(v);
+  if constexpr (G >= 32) v |= gpart<16>(v);
+  return v;
+}
+
+// Position of key in the G sorted entries nb[0..G) (padded with INT32_MAX),
+// or -1: a branch-free lower bound of fixed depth log2(G).  Several searches
+// in a row have no loop between them, so their LDS reads overlap.
+template <int G>
+__device__ __forceinline__ int find_pos(const int* nb, int key) {
+  int pos = 0;
+#pragma unroll
+  for (int step = G / 2; step >= 1; step >>= 1) pos += (nb[pos + step - 1] < key) ? step : 0;
+  return (pos < G && nb[pos] == key) ? pos : -1;
+}
+
+constexpr int kRefineMax = 5;
+
+}  // namespace
+
+}  // namespace clair
