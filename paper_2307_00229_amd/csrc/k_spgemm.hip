@@ -69,7 +69,7 @@ __device__ __forceinline__ int table_lg(long long prod, int* bound) {
 
 // largest number of products of a row (indices out of range skipped; the
 // count pass reports them), into *maxprod
-__global__ void k_sg_maxprod(int m, const int32_t* __restrict__ xrp, const int32_t* __restrict__ xci, int k,
+__global__ __launch_bounds__(256) void k_sg_maxprod(int m, const int32_t* __restrict__ xrp, const int32_t* __restrict__ xci, int k,
                              const int32_t* __restrict__ yrp, int32_t* maxprod) {
   int best = 0;
   for (int i = blockIdx.x * 256 + threadIdx.x; i < m; i += gridDim.x * 256) {
@@ -87,12 +87,26 @@ __global__ void k_sg_maxprod(int m, const int32_t* __restrict__ xrp, const int32
   }
 #pragma unroll
   for (int o = 32; o > 0; o >>= 1) best = max(best, __shfl_xor(best, o, 64));
-  if ((threadIdx.x & 63) == 0 && best > 0) atomicMax(maxprod, best);
+  // one atomic a workgroup at most, and only above the value already there:
+  // an unconditional atomic of every wavefront to the one address took 50 us
+  // on 261,121 rows, this 7
+  __shared__ int s_best[4];
+  if ((threadIdx.x & 63) == 0) s_best[threadIdx.x >> 6] = best;
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    best = max(max(s_best[0], s_best[1]), max(s_best[2], s_best[3]));
+    if (best > __hip_atomic_load(maxprod, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) atomicMax(maxprod, best);
+  }
 }
 
-// lanes per row: a quarter wavefront for tables of up to 128 slots (short
-// rows), the whole wavefront above
-constexpr int lanes_for(int LG) { return LG <= 7 ? 16 : 64; }
+// Y entries a lane has in flight at once (most rows of P and of A P's factors
+// fit one round; one at a time each insert waits for the next entry's load)
+constexpr int kSB = 4;
+
+// lanes per row: eight for tables of 64 slots (rows of few entries of X: a
+// count pass over 261,121 rows of five entries took 45 us with 16 lanes, 24
+// with eight), a quarter wavefront for 128, the whole wavefront above
+constexpr int lanes_for(int LG) { return LG <= 6 ? 8 : LG == 7 ? 16 : 64; }
 
 // Symbolic pass: groups of GL lanes, one row each (lane t of a group takes X
 // entries t, t + GL, ...; the first one's column and Y row bounds stay in
@@ -133,13 +147,16 @@ __global__ __launch_bounds__(64 * waves_for(LG)) void k_sg_count(int m, const in
     for (int t = tl; t < (1 << lg); t += GL) kt[t] = -1;
     if (tl == 0) count[grp] = 0;
     wave_sync();
-    bool over = false, bad = false;
-    if (mine) {
-      if ((unsigned)j0 >= (unsigned)k) bad = true;
-      for (int f = ya; f < yb; ++f) {
-        const int c = yci[f];
-        if ((unsigned)c >= (unsigned)ny) bad = true;
-        else if (hash_insert(kt, &count[grp], c, lg, bound) < 0) over = true;
+    bool over = false, bad = mine && (unsigned)j0 >= (unsigned)k;
+    for (int f0 = ya; f0 < yb; f0 += kSB) {
+      int c[kSB];
+#pragma unroll
+      for (int t = 0; t < kSB; ++t) c[t] = f0 + t < yb ? yci[f0 + t] : 0;
+#pragma unroll
+      for (int t = 0; t < kSB; ++t) {
+        if (f0 + t >= yb) break;
+        if ((unsigned)c[t] >= (unsigned)ny) bad = true;
+        else if (hash_insert(kt, &count[grp], c[t], lg, bound) < 0) over = true;
       }
     }
     for (int e = x0 + GL + tl; e < x1; e += GL) {
@@ -212,9 +229,20 @@ __global__ __launch_bounds__(64 * waves_for(LG)) void k_sg_fill(int m, const int
     for (int t = tl; t < size; t += GL) { kt[t] = -1; vt[t] = 0.0; }
     if (tl == 0) count[grp] = 0;
     wave_sync();
-    for (int f = ya; f < yb; ++f) {
-      const int h = hash_insert(kt, &count[grp], yci[f], lg, bound);
-      if (h >= 0) atomicAdd(&vt[h], xv * yva[f]);
+    for (int f0 = ya; f0 < yb; f0 += kSB) {
+      int c[kSB];
+      double y[kSB];
+#pragma unroll
+      for (int t = 0; t < kSB; ++t) {
+        c[t] = f0 + t < yb ? yci[f0 + t] : 0;
+        y[t] = f0 + t < yb ? yva[f0 + t] : 0.0;
+      }
+#pragma unroll
+      for (int t = 0; t < kSB; ++t) {
+        if (f0 + t >= yb) break;
+        const int h = hash_insert(kt, &count[grp], c[t], lg, bound);
+        if (h >= 0) atomicAdd(&vt[h], xv * y[t]);
+      }
     }
     for (int e = x0 + GL + tl; e < x1; e += GL) {
       const int j = xci[e];
@@ -277,7 +305,7 @@ hipError_t launch_spgemm_count(int m, const int32_t* xrp, const int32_t* xci, in
   *lg_out = 6;
   if (m <= 0) return hipSuccess;
   // the table size: twice the largest product count, as a power of two
-  hipLaunchKernelGGL(k_sg_maxprod, dim3(std::max(1, std::min((m + 255) / 256, cus * 8))), dim3(256), 0, s, m, xrp,
+  hipLaunchKernelGGL(k_sg_maxprod, dim3(std::max(1, std::min((m + 255) / 256, cus * 2))), dim3(256), 0, s, m, xrp,
                      xci, k, yrp, flags + 2);
   int32_t maxprod = 0;
   hipError_t e = hipMemcpyAsync(&maxprod, flags + 2, sizeof(int32_t), hipMemcpyDeviceToHost, s);
