@@ -261,11 +261,13 @@ void timing_mark(clair_ctx* c, bool on, hipStream_t s, const char* name) {
 // ---------------------------------------------------------------------------
 struct Batch {
   int nmat;
+  int chunk = 0;  // fine points per workgroup of the chunk-wise passes
   int nchunks;
   int64_t n_total;
   int64_t cap_sum = 0;  // R capacities summed over the batch (bounds the R entries of an asynchronous call)
   bool any_B;
   bool any_agg = false;
+  bool any_near = false, any_far = false;  // matrices at distance 1 or 2, and beyond
   int adj_w = 0;  // slots per point of the search's compact adjacency (0: not built)
   Layout L;
   Work w;
@@ -290,6 +292,18 @@ int check_args(int32_t nmat, const clair_csr_t* A, const int8_t* const* cf, cons
   return CLAIR_OK;
 }
 
+// Fine points per workgroup: the tuning's, halved while the batch has fewer than
+// two workgroups a CU (not below 64).  The chunk-wise passes (symbolic search,
+// projection) then fill the chip on small inputs too; the results do not depend
+// on the chunk.  150^2 at distance 5: its two 22-workgroup passes took 254 us with 1024
+// points (search 124, projection 130) and the projection takes 39 with 64; from
+// about 524,000 points on the chunk is the tuning's own.
+int effective_chunk(const clair_ctx* c, int64_t n_total) {
+  int chunk = c->chunk;
+  while (chunk > 64 && n_total < (int64_t)chunk * 2 * c->cus) chunk /= 2;
+  return chunk;
+}
+
 int prepare(clair_ctx* c, int32_t nmat, const clair_csr_t* A, const int8_t* const* cf,
             const double* const* B, const int32_t* ell, const clair_csr_out_t* R, Batch* b,
             const int32_t* const* agg = nullptr) {
@@ -305,12 +319,14 @@ int prepare(clair_ctx* c, int32_t nmat, const clair_csr_t* A, const int8_t* cons
   b->any_agg = false;
   b->cap_sum = 0;
   for (int m = 0; m < nmat; ++m) {
-    b->nchunks += (A[m].n + c->chunk - 1) / c->chunk;
     b->n_total += A[m].n;
+    (ell[m] <= 2 ? b->any_near : b->any_far) = true;
     b->cap_sum += std::max<int64_t>(0, R[m].nnz_capacity);
     b->any_B |= (B && B[m]);
     b->any_agg |= (agg && agg[m]);
   }
+  b->chunk = effective_chunk(c, b->n_total);
+  for (int m = 0; m < nmat; ++m) b->nchunks += (A[m].n + b->chunk - 1) / b->chunk;
   // the compact adjacency serves the searches of distance 2 and more on
   // sparse graphs: width 4 when every such graph has at most five stored
   // entries per row on average, else 8 (points beyond it are searched from
@@ -383,13 +399,14 @@ int prepare(clair_ctx* c, int32_t nmat, const clair_csr_t* A, const int8_t* cons
   w.scratch_stride = c->scratch_stride;
   w.nmat = nmat;
   w.nchunks = b->nchunks;
-  w.chunk = c->chunk;
+  w.chunk = b->chunk;
   w.GA = c->group;
   w.capC = (int32_t)std::min<int64_t>(b->L.capC, INT32_MAX);
   w.adj_w = b->adj_w;
   w.fadj = reinterpret_cast<int32_t*>(base + b->L.fadj);
   w.bf16 = 0;
-  w.pad1 = 0;
+  w.gj = 0;
+  w.adj_live = 1;
   w.midq = reinterpret_cast<int32_t*>(base + b->L.midq);
 
   char* h = stage_base(c);
@@ -420,7 +437,7 @@ int prepare(clair_ctx* c, int32_t nmat, const clair_csr_t* A, const int8_t* cons
     d.ell = ell[m];
     d.chunk0 = chunk0;
     d.nnz = A[m].nnz;
-    d.nchunks = (A[m].n + c->chunk - 1) / c->chunk;
+    d.nchunks = (A[m].n + b->chunk - 1) / b->chunk;
     d.fine0 = fine0;
     d.cmax = w.cmax + fine0;
     d.theta = c->theta;
@@ -567,6 +584,15 @@ int enqueue_numeric(clair_ctx* c, Batch& b, hipStream_t s, bool timing, const Co
     if (capture_check(c->capturing, s, "k_numeric32", __LINE__)) return CLAIR_ERR_HIP;
     timing_mark(c, timing, s, "numeric32");
   }
+  b.w.gj = 0;
+  // rows of 33 to 128 points: not launched when the last sizes read back say
+  // there are none (k_rows_wg takes any row) nor for BF16 trailing updates,
+  // which are k_rows_wg's blocked LU
+  if (!b.w.bf16 && (known ? known->nC > 0 : c->last_maxb == 0 || c->last_maxb > 32)) {
+    b.w.gj = 1;
+    HIPCHK(launch_rows_gj(b.w, c->cus, s));
+    if (capture_check(c->capturing, s, "k_rows_gj", __LINE__)) return CLAIR_ERR_HIP;
+  }
   HIPCHK(launch_rows_wg(b.w, occupancy_blocks(c, 1), s));
   if (capture_check(c->capturing, s, "k_rows_wg", __LINE__)) return CLAIR_ERR_HIP;
   timing_mark(c, timing, s, "rows_wg");
@@ -605,8 +631,14 @@ int enqueue_symbolic(clair_ctx* c, Batch& b, hipStream_t s, bool validate, bool 
   HIPCHK(launch_count(b.w, s));
   if (capture_check(c->capturing, s, "k_count", __LINE__)) return CLAIR_ERR_HIP;
   timing_mark(c, timing, s, "count");
-  HIPCHK(launch_count_mid(b.w, occupancy_blocks(c, 4), s));
-  if (capture_check(c->capturing, s, "k_count_mid", __LINE__)) return CLAIR_ERR_HIP;
+  if (b.any_near) {
+    HIPCHK(launch_count_mid(b.w, occupancy_blocks(c, 8), s));
+    if (capture_check(c->capturing, s, "k_count_mid", __LINE__)) return CLAIR_ERR_HIP;
+  }
+  if (b.any_far) {
+    HIPCHK(launch_count_wide(b.w, occupancy_blocks(c, 4), s));
+    if (capture_check(c->capturing, s, "k_count_wide", __LINE__)) return CLAIR_ERR_HIP;
+  }
   timing_mark(c, timing, s, "count_mid");
   HIPCHK(launch_count_big(b.w, std::max(8, c->cus * 2), s));
   if (capture_check(c->capturing, s, "k_count_big", __LINE__)) return CLAIR_ERR_HIP;
@@ -2015,6 +2047,7 @@ int clair_plan_execute(clair_plan_t* pl, int32_t nmat, const clair_csr_t* A, con
   const bool async = o && o->async;
   const bool timing = o && o->timing;
   Batch b = pl->b;
+  b.w.adj_live = 0;  // the adjacency is the plan's values'; rows searched again read A
   // the previous upload must have left the staging buffer before it is rewritten
   if (c->upload_pending) {
     HIPCHK(hipEventSynchronize(c->upload_done));

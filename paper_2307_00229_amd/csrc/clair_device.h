@@ -195,9 +195,10 @@ struct Work {
                           // previous entry and the row's C-point
   int32_t* slotA;         // [n_total * GA]
   int32_t* slotB;         // [n_total * 32]
-  int32_t* binC;          // [capC] rows for the workgroup solver
+  int32_t* binC;          // [capC] rows for the workgroup solvers
   int32_t* chunk_unsized;  // [nchunks] rows of the chunk not yet sized (more than 32 points)
-  int32_t* bigq;           // [capC] those rows, c * chunk + t
+  int32_t* bigq;           // [capC] those rows, c * chunk + t; in the numeric phase (gj = 1): 1 for a row of binC that
+                           // k_rows_gj has solved, else 0
   int32_t* big_size;       // [n_total] their sizes, until the chunk's prefix is redone
   double* cmax;            // [n_total] column maxima for the strength test (theta > 0)
   int32_t* agg_cnt;        // [n_total] aggregate sizes, then fill cursors (aggregates given)
@@ -216,7 +217,9 @@ struct Work {
   int32_t adj_w;          // slots per point of the compact adjacency (0: none built)
   int32_t* fadj;          // [n_total * adj_w]
   int32_t bf16;           // 1: the workgroup solver's trailing updates take bfloat16 inputs
-  int32_t pad1;
+  int32_t gj;             // 1: k_rows_gj runs before k_rows_wg
+  int32_t pad2;
+  int32_t adj_live;       // 1: the compact adjacency was built from this call's values (0 in a plan's execute)
   int32_t* midq;          // [nchunks] chunks k_count left unfinished
 };
 
@@ -452,81 +455,6 @@ __device__ __forceinline__ int rega_bfs(RegSetA<SM>& S, int n, int i, int ell, g
   if (S.ovf) return -1;
   bitonic_sort<SM>(S.v);
   return S.s;
-}
-
-// The literal reading of Algorithm 1's pattern S^{ell-1} T, T = [S_fc, I]:
-// the first step reaches i's F-neighbours; the second step expands i itself
-// (T's identity part) and those points; from the second step on, C-points
-// may be interior vertices of a walk (they stay in the set until the last
-// step and are dropped at the end); i never enters.  The graph's rows only
-// (the compact adjacency lists F-points alone).  Returns |N(i)| with
-// S.v[0..s) ascending, or -1 when more than SM points (C-points included)
-// are met.
-template <int SM>
-__device__ __forceinline__ void rowa_expand_literal(RegSetA<SM>& S, int n, int u, int i, bool allow_c,
-                                                    gptr<const int32_t> __restrict__ rp,
-                                                    gptr<const int32_t> __restrict__ ci,
-                                                    gptr<const double> __restrict__ va,
-                                                    gptr<const int8_t> __restrict__ cf, double theta,
-                                                    gptr<const double> __restrict__ cmax) {
-  const int e1 = rp[u + 1];
-  for (int e = rp[u]; e < e1 && !S.ovf; e += 8) {
-    int k[8];
-    double x[8];
-#pragma unroll
-    for (int j = 0; j < 8; ++j) {
-      k[j] = u;
-      x[j] = 0.0;
-      if (e + j < e1) { k[j] = ci[e + j]; x[j] = va[e + j]; }
-    }
-    bool in[8];
-    int8_t c8[8];
-#pragma unroll
-    for (int j = 0; j < 8; ++j) {
-      in[j] = (unsigned)k[j] < (unsigned)n;
-      c8[j] = in[j] ? cf[k[j]] : (int8_t)0;
-    }
-#pragma unroll
-    for (int j = 0; j < 8; ++j)
-      if (in[j] && k[j] != u && k[j] != i && x[j] != 0.0 && (c8[j] == 0 || allow_c) &&
-          strong_edge(x[j], k[j], theta, cmax))
-        S.insert(k[j]);
-  }
-}
-
-template <int SM>
-__device__ __forceinline__ int rega_bfs_literal(RegSetA<SM>& S, int n, int i, int ell,
-                                                gptr<const int32_t> __restrict__ rp,
-                                                gptr<const int32_t> __restrict__ ci,
-                                                gptr<const double> __restrict__ va,
-                                                gptr<const int8_t> __restrict__ cf, double theta,
-                                                gptr<const double> __restrict__ cmax) {
-  S.clear();
-  rowa_expand_literal(S, n, i, i, false, rp, ci, va, cf, theta, cmax);
-  int lo = 0;
-  for (int L = 2; L <= ell && !S.ovf; ++L) {
-    const int hi = S.s;
-    const bool allow_c = L < ell;
-    if (L == 2) rowa_expand_literal(S, n, i, i, allow_c, rp, ci, va, cf, theta, cmax);
-    else if (lo == hi) break;
-    for (int p = lo; p < hi && !S.ovf; ++p)
-      rowa_expand_literal(S, n, S.get(p), i, allow_c, rp, ci, va, cf, theta, cmax);
-    lo = hi;
-  }
-  if (S.ovf) return -1;
-  // the C-points were interior vertices only
-  int8_t c8[SM];
-#pragma unroll
-  for (int j = 0; j < SM; ++j) c8[j] = (S.v[j] != 0x7fffffff) ? cf[S.v[j]] : (int8_t)0;
-  int f = 0;
-#pragma unroll
-  for (int j = 0; j < SM; ++j) {
-    if (c8[j] != 0) S.v[j] = 0x7fffffff;
-    f += S.v[j] != 0x7fffffff ? 1 : 0;
-  }
-  bitonic_sort<SM>(S.v);
-  S.s = f;
-  return f;
 }
 
 // matrix owning global chunk c (desc[].chunk0 ascending): the last matrix

@@ -21,6 +21,8 @@ hipError_t launch_colmax(const Work& w, int64_t n_total, int blocks, hipStream_t
 hipError_t launch_adj(const Work& w, hipStream_t s);
 hipError_t launch_count(const Work& w, hipStream_t s);
 hipError_t launch_count_mid(const Work& w, int blocks, hipStream_t s);
+// the chunks launch_count left unfinished: matrices at distance 1 and 2, and beyond
+hipError_t launch_count_wide(const Work& w, int blocks, hipStream_t s);
 hipError_t launch_count_big(const Work& w, int blocks, hipStream_t s);
 hipError_t launch_scan(const Work& w, hipStream_t s);
 // which = 0: bin A with group = GA; which = 1: bin B with group = 32
@@ -31,6 +33,8 @@ hipError_t launch_lanes(const Work& w, int which, int group, int rows_per_lane, 
 // one thread per row with |N| <= 8 (GA == 1); four lanes per row (GA == 4)
 hipError_t launch_quad8(const Work& w, int wg_threads, int cus, hipStream_t s);
 hipError_t launch_rows8(const Work& w, int wg_threads, int cus, hipStream_t s);
+// queued rows of 33 to 128 points: FP32 inverse in registers, FP64 refinement
+hipError_t launch_rows_gj(const Work& w, int cus, hipStream_t s);
 hipError_t launch_rows_wg(const Work& w, int blocks, hipStream_t s);
 // the constraint projection over the column lists (one workgroup per chunk)
 hipError_t launch_project(const Work& w, hipStream_t s);

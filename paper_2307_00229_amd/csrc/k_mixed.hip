@@ -9,10 +9,12 @@
 //                candidate list and written to their slot; a chunk with every
 //                row sized gets its chunk-local prefix of |N(i)|+1 here;
 //                clears the projection's column lists of the chunk.
-//   k_count_mid  the other rows of unfinished chunks: one thread per row, up
-//                to 32 points in registers (over the adjacency when built),
-//                then the chunk's prefix.  Rows of more than 32 points are
-//                queued, unsized.
+//   k_count_mid  the other rows of unfinished chunks at distance 1 and 2: one
+//                thread per row, up to 32 points in registers (over the
+//                adjacency when built), then the chunk's prefix.  Larger rows
+//                are queued, unsized.
+//   k_count_wide the same at distance 3 and more: sixteen lanes per row up to
+//                32 points, a wavefront up to 128, in LDS.
 //   k_count_big  one workgroup per queued row: a workgroup-wide search sizes
 //                it (queued for the workgroup solver); the last row of a chunk
 //                to be sized redoes the chunk's prefix.
@@ -46,6 +48,7 @@
 #include "clair_device.h"
 #include "clair_launch.h"
 #include "mixed_device.h"
+#include "search_device.h"
 
 namespace clair {
 
@@ -57,7 +60,7 @@ constexpr int kWN = kMaxBlock;
 constexpr int kWC = 4096;
 
 // Workgroup-wide neighbourhood search for rows of any size up to kWN points:
-// the same set as rega_bfs (F-points reachable from C-point i by at most ell
+// the same set as group_search (F-points reachable from C-point i by at most ell
 // edges with F-points inside the walk).  The entries of a level's frontier
 // rows are taken in windows of kWC: each window is sorted (bitonic, in LDS),
 // reduced to points that are new (first of their run, not yet in N, not yet
@@ -410,18 +413,18 @@ __device__ __forceinline__ int count_row_ell1(const Work& w, const GDesc& d, int
 __device__ __forceinline__ void finish_chunk(const Work& w, int c, int m, MatStatus* st, int64_t base, int nc,
                                              const int* s_rows, const int16_t* s_size, const int16_t* s_unres,
                                              int nunres, int* s_scan, int* s_flag, int* s_qbase) {
-  const int tid = threadIdx.x;
+  const int tid = threadIdx.x, nt = blockDim.x;
   const int lim = small_limit(w.GA);
   if (nunres) {
     if (tid == 0) *s_qbase = atomicAdd(&w.cnt->nbig, nunres);
     __syncthreads();
-    for (int k = tid; k < nunres; k += kNT) {
+    for (int k = tid; k < nunres; k += nt) {
       const int q = *s_qbase + k;
       if (q < w.capC) w.bigq[q] = c * w.chunk + s_unres[k];
       else flag_row(st, ST_UNSUPPORTED, -s_rows[s_unres[k]] - 1);
     }
   }
-  const int per2 = (nc + kNT - 1) / kNT;
+  const int per2 = (nc + nt - 1) / nt;
   const int t0 = tid * per2;
   int mysum = 0, mymax = 0, inA = 0, inB = 0;
   for (int t = t0; t < min(t0 + per2, nc); ++t) {
@@ -430,7 +433,7 @@ __device__ __forceinline__ void finish_chunk(const Work& w, int c, int m, MatSta
     mymax = max(mymax, sz);
     if (s_rows[t] >= 0) {
       inA += sz <= lim ? 1 : 0;
-      inB += sz > lim ? 1 : 0;
+      inB += sz > lim && sz <= 32 ? 1 : 0;  // larger rows are queued for the workgroup solvers
     }
   }
   int tot;
@@ -542,14 +545,21 @@ __global__ __launch_bounds__(kNT) void k_count(Work w) {
   }
 }
 
-// Symbolic pass, second part: the chunks k_count left unfinished (queued by
-// it; the workgroups take them in turn, so an empty queue costs one load per
-// workgroup).  One thread per row not
-// yet sized searches up to 32 points in registers (over the compact
-// adjacency when the matrix has one); larger rows are left unsized for
-// k_count_big.  Then the chunk's bookkeeping.
+// Symbolic pass, second part, distances 1 and 2: the chunks k_count left
+// unfinished (queued by it; the workgroups take them in turn, so an empty
+// queue costs one load per workgroup).  One thread per row not yet sized
+// searches up to 32 points in registers (over the compact adjacency when the
+// matrix has one); larger rows are left unsized for k_count_big.  Then the
+// chunk's bookkeeping.
+//
+// Bound: latency at two wavefronts per SIMD (the register set).  A chunk of
+// 1024 points has 114 to 256 rows, so workgroups of 128 threads keep their
+// wavefronts busy (with 256, half of each workgroup's waited):
+// 2048^2 nine-point rows 251 -> 230 us, 128^3 seven-point 81 -> 70 us.  (A set
+// in LDS shared by sixteen lanes per row, as in k_count_wide, took 222 and 93.)
+constexpr int kMT = 128;
 template <int W>
-__global__ __launch_bounds__(kNT) void k_count_mid(Work w) {
+__global__ __launch_bounds__(kMT) void k_count_mid(Work w) {
   __shared__ int s_rows[kMaxChunk];
   __shared__ int16_t s_size[kMaxChunk];
   __shared__ int s_scan[kNT];
@@ -565,12 +575,13 @@ __global__ __launch_bounds__(kNT) void k_count_mid(Work w) {
   __syncthreads();  // the previous chunk's LDS is free
   const int m = w.chunk_mat[c];
   const GDesc d = gview(w.desc[m]);
+  if (d.ell > 2) continue;  // k_count_wide's
   MatStatus* st = &w.st[m];
   const int64_t base = d.fine0 + (int64_t)(c - d.chunk0) * w.chunk;
   const int nc = w.chunk_nc[c];
   if (tid == 0) { s_flag[0] = 0; s_flag[1] = 0; s_flag[2] = 0; s_flag[3] = 0; s_nlist = 0; }
   __syncthreads();
-  for (int t = tid; t < nc; t += kNT) {
+  for (int t = tid; t < nc; t += kMT) {
     s_rows[t] = w.clocal[base + t];
     const int sz = w.lnz[base + t];
     s_size[t] = (int16_t)sz;
@@ -580,14 +591,12 @@ __global__ __launch_bounds__(kNT) void k_count_mid(Work w) {
   const int SA = slot_stride(w.GA);
   const int lim = small_limit(w.GA);
   const int nl = s_nlist;
-  for (int k = tid; k < nl; k += kNT) {
+  for (int k = tid; k < nl; k += kMT) {
     const int t = s_list[k];
     const int i = s_rows[t];
     RegSetA<32> S;
     int sz;
-    if (d.literal && d.ell >= 3) {
-      sz = rega_bfs_literal<32>(S, d.n, i, d.ell, d.grp, d.gci, d.gva, d.cf, d.theta, d.cmax);
-    } else if constexpr (W > 0) {
+    if constexpr (W > 0) {
       if (d.fadj)
         sz = rega_bfs<32, W>(S, d.n, i, d.ell, d.fadj, d.grp, d.gci, d.gva, d.cf, d.theta, d.cmax, nullptr, nullptr);
       else
@@ -619,7 +628,123 @@ __global__ __launch_bounds__(kNT) void k_count_mid(Work w) {
   }
 }
 
-// Rows with more than 32 points, one workgroup per row (grid-stride over the
+// The same at distance 3 and more, where rows of more than 32 points are
+// common: sixteen lanes per row search up to 32 points (group_search, over the
+// compact adjacency when the matrix has one); the rows that hold more are
+// searched again by a wavefront each, up to kMidMax points, and queued for the
+// workgroup solvers; larger rows are left unsized for k_count_big.  Then the
+// chunk's bookkeeping.  Bound: the latency of a level's trips to memory.
+// 150^2 nine-point rows at distance 5 (up to 108 points): one thread per row,
+// then a workgroup per row of more than 32 points, took 445 us, this 70.
+constexpr int kMidMax = 128;
+
+template <int W>
+__global__ __launch_bounds__(kNT) void k_count_wide(Work w) {
+  constexpr int G = 16, NG = kNT / G, NW = kNT / 64;
+  constexpr int LW = W == 4 ? 2 : W == 8 ? 3 : 0;
+  typedef SearchBuf<32, 64> SmallBuf;
+  typedef SearchBuf<kMidMax, 4 * kMidMax> WaveBuf;
+  __shared__ int s_rows[kMaxChunk];
+  __shared__ int16_t s_size[kMaxChunk];
+  __shared__ int s_scan[kNT];
+  __shared__ int s_flag[4];  // max |N|, rows left unsized, rows in bin A, rows in bin B
+  __shared__ int16_t s_list[kMaxChunk];   // rows to size here, then rows of more than 32 points
+  __shared__ int16_t s_unres[kMaxChunk];  // rows of more than kMidMax points
+  __shared__ int s_nlist, s_nwide, s_qbase;
+  __shared__ union {
+    SmallBuf small[NG];
+    WaveBuf wide[NW];
+  } s_buf;
+
+  const int tid = threadIdx.x;
+  const int nq = w.cnt->nmid;
+  for (int qi = blockIdx.x; qi < nq; qi += gridDim.x) {
+  const int c = w.midq[qi];
+  __syncthreads();  // the previous chunk's LDS is free
+  const int m = w.chunk_mat[c];
+  const GDesc d = gview(w.desc[m]);
+  if (d.ell <= 2) continue;  // k_count_mid's
+  MatStatus* st = &w.st[m];
+  const int64_t base = d.fine0 + (int64_t)(c - d.chunk0) * w.chunk;
+  const int nc = w.chunk_nc[c];
+  if (tid == 0) { s_flag[0] = 0; s_flag[1] = 0; s_flag[2] = 0; s_flag[3] = 0; s_nlist = 0; s_nwide = 0; }
+  __syncthreads();
+  for (int t = tid; t < nc; t += kNT) {
+    s_rows[t] = w.clocal[base + t];
+    const int sz = w.lnz[base + t];
+    s_size[t] = (int16_t)sz;
+    if (sz < 0) s_list[atomicAdd(&s_nlist, 1)] = (int16_t)t;
+  }
+  __syncthreads();
+  const int SA = slot_stride(w.GA);
+  const int lim = small_limit(w.GA);
+  const bool literal = d.literal != 0 && d.ell >= 3;
+  const int nl = s_nlist;
+  // the points of a row of at most 32 to its slot, each at its rank
+  auto put_slot = [&](auto& b, int t, int n, int sz, int lane, int lanes) {
+    gptr<int32_t> dst = sz <= lim ? to_global(w.slotA) + (base + t) * SA : to_global(w.slotB) + (base + t) * 32;
+    for (int q = lane; q < n; q += lanes) {
+      const int v = b.list[q];
+      if (v != INT32_MAX) dst[search_rank(b, n, v)] = v;
+    }
+  };
+  {
+    const int lane = tid % G;
+    SmallBuf& b = s_buf.small[tid / G];
+    for (int k = tid / G; k < nl; k += NG) {
+      const int t = s_list[k];
+      const int n = group_search<G>(b, d, s_rows[t], LW, lane);
+      if (n < 0) {
+        if (lane == 0) s_size[t] = -2;  // more than 32 points were met
+      } else {
+        const int sz = literal ? drop_c_points<G>(b, d, n, lane) : n;
+        put_slot(b, t, n, sz, lane, G);
+        if (lane == 0) s_size[t] = (int16_t)sz;
+      }
+      group_sync<G>();  // the buffer is free
+    }
+  }
+  __syncthreads();
+  for (int t = tid; t < nc; t += kNT)
+    if (s_size[t] == -2) s_list[atomicAdd(&s_nwide, 1)] = (int16_t)t;
+  __syncthreads();
+  {
+    const int lane = tid & 63;
+    WaveBuf& b = s_buf.wide[tid >> 6];
+    const int nw = s_nwide;
+    for (int k = tid >> 6; k < nw; k += NW) {
+      const int t = s_list[k];
+      const int i = s_rows[t];
+      const int n = group_search<64>(b, d, i, LW, lane);
+      if (n < 0) {
+        if (lane == 0) {
+          s_size[t] = 0;
+          s_rows[t] = -(i + 1);
+          w.clocal[base + t] = -(i + 1);
+          s_unres[atomicAdd(&s_flag[1], 1)] = (int16_t)t;
+        }
+      } else {
+        const int sz = literal ? drop_c_points<64>(b, d, n, lane) : n;
+        if (sz <= 32) put_slot(b, t, n, sz, lane, 64);
+        if (lane == 0) {
+          s_size[t] = (int16_t)sz;
+          if (sz > 32) {
+            const int q = atomicAdd(&w.cnt->nC, 1);
+            if (q < w.capC) w.binC[q] = c * w.chunk + t;
+            else flag_row(st, ST_UNSUPPORTED, i);
+          }
+        }
+      }
+      group_sync<64>();
+    }
+  }
+  __syncthreads();
+  finish_chunk(w, c, m, st, base, nc, s_rows, s_size, s_unres, s_flag[1], s_scan, s_flag, &s_qbase);
+  }
+}
+
+// Rows the searches above left unsized (more than 32 points at distance 2, more
+// than kMidMax beyond), one workgroup per row (grid-stride over the
 // queue): the workgroup search sizes the row, which is queued for the
 // workgroup solver.  The workgroup that sizes the last such row of a chunk
 // then redoes the chunk's prefix.
@@ -2079,6 +2204,7 @@ __global__ __launch_bounds__(kWT) void k_rows_wg(Work w) {
         // no scratch: report oversized rows instead of solving them
         for (int qi = blockIdx.x; qi < qlen; qi += gridDim.x) {
           const int e = w.binC[qi];
+          if (w.gj && w.bigq[qi]) continue;  // solved by k_rows_gj
           const int c = e / w.chunk;
           const RowInfo ri = row_info(w, c, e - c * w.chunk);
           if (ri.s > kLdsBlockMax && tid == 0) flag_row(&w.st[ri.m], ST_UNSUPPORTED, ri.i);
@@ -2089,6 +2215,7 @@ __global__ __launch_bounds__(kWT) void k_rows_wg(Work w) {
     const int stride = (pass == 0) ? gridDim.x : (int)min<int64_t>(gridDim.x, w.scratch_slots);
     for (int qi = blockIdx.x; qi < qlen; qi += stride) {
       const int e = w.binC[qi];
+      if (w.gj && w.bigq[qi]) continue;  // solved by k_rows_gj
       const int c = e / w.chunk;
       const RowInfo ri = row_info(w, c, e - c * w.chunk);
       const bool big = ri.s > kLdsBlockMax;
@@ -2596,10 +2723,20 @@ hipError_t launch_count(const Work& w, hipStream_t s) {
 
 hipError_t launch_count_mid(const Work& w, int blocks, hipStream_t s) {
   if (w.nchunks == 0) return hipSuccess;
-  const dim3 grid(std::min(w.nchunks, std::max(1, blocks))), block(kNT);
+  const dim3 grid(std::min(w.nchunks, std::max(1, blocks))), block(kMT);
   if (w.adj_w == 0) hipLaunchKernelGGL(k_count_mid<0>, grid, block, 0, s, w);
   else if (w.adj_w == 4) hipLaunchKernelGGL(k_count_mid<4>, grid, block, 0, s, w);
   else if (w.adj_w == 8) hipLaunchKernelGGL(k_count_mid<8>, grid, block, 0, s, w);
+  else return hipErrorInvalidValue;
+  return hipGetLastError();
+}
+
+hipError_t launch_count_wide(const Work& w, int blocks, hipStream_t s) {
+  if (w.nchunks == 0) return hipSuccess;
+  const dim3 grid(std::min(w.nchunks, std::max(1, blocks))), block(kNT);
+  if (w.adj_w == 0) hipLaunchKernelGGL(k_count_wide<0>, grid, block, 0, s, w);
+  else if (w.adj_w == 4) hipLaunchKernelGGL(k_count_wide<4>, grid, block, 0, s, w);
+  else if (w.adj_w == 8) hipLaunchKernelGGL(k_count_wide<8>, grid, block, 0, s, w);
   else return hipErrorInvalidValue;
   return hipGetLastError();
 }

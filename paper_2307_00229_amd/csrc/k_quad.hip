@@ -141,6 +141,10 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(3))) void k_
       t = nx_t; i = nx_i; off = nx_off; s = nx_s; nn = nx_nn;
     } else {
       cc.seek(w, g);
+      if (cc.bins.x == 0) {  // no row of this chunk is ours: on to the next one
+        g += (cc.re - g + NQ - 1) / NQ * NQ - NQ;
+        continue;
+      }
       cc.row(w, g, &t, &i, &off, &s);
       nn = *reinterpret_cast<const int2*>(w.slotA + (cc.fbase + t) * 8 + 2 * ql);
     }

@@ -85,6 +85,7 @@ struct ChunkCursor {
   int m = 0;
   int nc = 0;           // C-rows in the chunk
   int tot = 0;          // nnz(R) of the chunk
+  int2 bins = {0, 0};   // rows of the chunk in bin A and bin B
   int zoff = 0;         // R offset of the chunk inside its matrix
   int rbase_m = 0;      // first global row of the matrix
   int64_t fbase = 0;    // fine offset of the chunk's first point (batch-wide)
@@ -102,6 +103,7 @@ struct ChunkCursor {
     const MatStatus& st = w.st[m];
     nc = w.chunk_nc[c];
     tot = w.chunk_nnz[c];
+    bins = w.chunk_bins[c];
     zoff = (int)(w.chunk_nzglob[c] - st.nz_base);
     rbase_m = st.row_base;
     fine0 = md.fine0;
