@@ -559,28 +559,15 @@ int enqueue_numeric(clair_ctx* c, Batch& b, hipStream_t s, bool timing, const Co
       // 667 against 990 us on 64 of 64^2 to 768^2)
       HIPCHK(launch_quad8(b.w, c->wg_threads, c->cus, s));
     } else {
-      HIPCHK(launch_numeric(b.w, 0, c->group, c->group, c->wg_threads, c->cus, s));
+      HIPCHK(launch_tile(b.w, 0, std::min(c->group, c->binB_max), c->cus, s));
     }
     if (capture_check(c->capturing, s, "k_numeric", __LINE__)) return CLAIR_ERR_HIP;
   }
   timing_mark(c, timing, s, "numeric");
   if (c->group < 32 && (!known || known->nB > 0)) {
-    // bin B: the smallest block bound that holds the largest block seen (rows
-    // beyond it go to the workgroup solver, so any bound is correct)
-    // block bound 16, 18, 20, 24 or 32 (the smallest that holds the largest
-    // block read back).  binB_lanes = 32: one lane per block row (16 lanes at
-    // the bound 16); 8 or 16: ceil(bound / lanes) block rows per lane (8
-    // lanes at 32 points would need more LDS than a workgroup has: 16 then)
-    const int bsm = c->binB_max <= 16 ? 16 : c->binB_max <= 20 ? 20 : c->binB_max <= 24 ? 24 : 32;
-    if (c->binB_lanes == 32) {
-      // (17 and 18 points, the 128^3 seven-point rows, have a bound of their own)
-      const int b32 = (c->binB_max > 16 && c->binB_max <= 18) ? 18 : bsm;
-      HIPCHK(launch_numeric(b.w, 1, b32 == 16 ? 16 : 32, b32, 128, c->cus, s));
-    } else {
-      const int bg = (bsm == 32 && c->binB_lanes == 8) ? 16 : c->binB_lanes;
-      const int br = (bsm + bg - 1) / bg;
-      HIPCHK(launch_lanes(b.w, 1, bg, br, bsm, 64, c->cus, s));
-    }
+    // bin B, for the largest block the last synchronous call read back (a
+    // larger row goes to the workgroup solvers, so any bound is correct)
+    HIPCHK(launch_tile(b.w, 1, c->binB_max, c->cus, s));
     if (capture_check(c->capturing, s, "k_numeric32", __LINE__)) return CLAIR_ERR_HIP;
     timing_mark(c, timing, s, "numeric32");
   }
@@ -1790,10 +1777,8 @@ int clair_autotune(clair_ctx_t* c, int32_t nmat, const clair_csr_t* A, const int
       return clair_build_R_batched(c, nmat, A, cf, B, ell, R, &o, nullptr);
     }
   }
-  int maxs = 0;
-  int64_t above8 = 0, above16 = 0, binB_rows = 0;
+  int64_t above8 = 0, above16 = 0;
   for (int k = 0; k < 34; ++k) {
-    if (hist[k]) maxs = k;
     if (k > 8) above8 += hist[k];
     if (k > 16) above16 += hist[k];
   }
@@ -1839,23 +1824,8 @@ int clair_autotune(clair_ctx_t* c, int32_t nmat, const clair_csr_t* A, const int
     float ms = 0.f;
     if (!time_one(&ms) && ms < best_ms) { best_ms = ms; best.chunk = ch; }
   }
-  // stage 3: the bin-B layout, when rows fall between the bin-A bound and 32
-  const int abound = best.group <= 8 ? 8 : best.group;
-  for (int k = abound + 1; k <= 32; ++k) binB_rows += hist[k];
-  if (binB_rows) {
-    for (int lanes : {8, 16, 32}) {
-      if (lanes == best.binB_lanes) continue;
-      c->group = best.group;
-      c->wg_threads = best.wg_threads;
-      c->chunk = best.chunk;
-      c->binB_lanes = lanes;
-      float ms = 0.f;
-      if (!time_one(&ms) && ms < best_ms) { best_ms = ms; best.binB_lanes = lanes; }
-    }
-  }
   (void)hipEventDestroy(e0);
   (void)hipEventDestroy(e1);
-  (void)maxs;
   c->group = best.group;
   c->wg_threads = best.wg_threads;
   c->chunk = best.chunk;

@@ -25,11 +25,9 @@ hipError_t launch_count_mid(const Work& w, int blocks, hipStream_t s);
 hipError_t launch_count_wide(const Work& w, int blocks, hipStream_t s);
 hipError_t launch_count_big(const Work& w, int blocks, hipStream_t s);
 hipError_t launch_scan(const Work& w, hipStream_t s);
-// which = 0: bin A with group = GA; which = 1: bin B with group = 32
-hipError_t launch_numeric(const Work& w, int which, int group, int sm, int wg_threads, int cus, hipStream_t s);
-// group lanes per row with rows_per_lane block rows each (bins A and B)
-hipError_t launch_lanes(const Work& w, int which, int group, int rows_per_lane, int sm, int wg_threads, int cus,
-                        hipStream_t s);
+// sixteen lanes per row, blocks of up to sm <= 32 points (which = 0: bin A of
+// bound 16 or 32; which = 1: bin B)
+hipError_t launch_tile(const Work& w, int which, int sm, int cus, hipStream_t s);
 // one thread per row with |N| <= 8 (GA == 1); four lanes per row (GA == 4)
 hipError_t launch_quad8(const Work& w, int wg_threads, int cus, hipStream_t s);
 hipError_t launch_rows8(const Work& w, int wg_threads, int cus, hipStream_t s);

@@ -23,14 +23,13 @@
 //                R.row_ptr[n_c].
 //   k_quad8      (k_quad.hip) persistent over the rows, four lanes per row with
 //                |N| <= 8: see there.
-//   k_numeric    persistent over the rows in grid order (each XCD a contiguous
-//                slice), G lanes per row with |N| <= G (bin A, G = GA = 16 or
-//                32), or with GA < |N| <= 32 (bin B, G = 16 or 32): gather of the local
-//                block into LDS, FP32 inverse (Gauss-Jordan) and FP64
-//                iterative refinement of (A[N,N])^T z = -A[i,N]^T, R row
-//                write, projection sums.  Rows whose FP32 factorisation is not
-//                trusted are queued for k_rows_wg.
-//                k_rows8 (one thread per row) is the third bin-A solver.
+//   k_tile       (k_tile.hip) sixteen lanes per row with up to 32 points: FP32
+//                inverse (Gauss-Jordan) and FP64 iterative refinement of
+//                (A[N,N])^T z = -A[i,N]^T, R row write, column lists of the
+//                projection.  Rows whose FP32 factorisation is not trusted are
+//                queued for k_rows_wg.
+//   k_rows8      the one-thread-per-row bin-A solver (group 1).
+//   k_rows_gj    (k_block.hip) a workgroup per queued row of 33 to 128 points.
 //   k_rows_wg    persistent, one workgroup per queued row: for 33..128 points
 //                an FP32 blocked LU with matrix-core trailing updates and FP64
 //                refinement; otherwise, or when that does not converge, FP64 LU
@@ -953,630 +952,6 @@ __global__ __launch_bounds__(1024) void k_scan(Work w) {
     w.cnt->nA = na;
     w.cnt->nB = nb;
   }
-}
-
-// ---------------------------------------------------------------------------
-// numeric pass: G lanes per queued row
-// ---------------------------------------------------------------------------
-// LDS of one lane group: blocks of up to SM points (SM <= G)
-template <int G, int SM>
-struct NumGroupBuf {
-  double K[SM * (SM + 1)];  // FP64 block, row q = row q of (A[N,N])^T, stride SM+1
-  // -A[i,N] (written by the gather, read once after the factorisation), the
-  // refinement broadcast z and a correction's FP32 right-hand side y are
-  // never live together, so they share one buffer: every store to it comes
-  // after the group's last load of the previous contents in program order,
-  // and a wavefront's LDS instructions execute in order.  (At 24 points
-  // this holds a group to 5,120 bytes, eight workgroups of four per CU.)
-  union {
-    double f[SM];
-    double z[SM];
-    float y[SM];
-  };
-  int nb[G];  // sorted N(i), INT32_MAX beyond |N|
-};
-
-// y_lane = sum_p Kinv[lane][p] v_p: the group's right-hand side goes through
-// LDS once (v_p from lane p), then every lane reads all of it (broadcast
-// reads, no dependence between the steps).  kf holds this lane's row of the
-// FP32 inverse; lanes at or beyond SM hold no row.
-template <int SM>
-__device__ __forceinline__ float inv_apply(const float (&kf)[SM], float* ybuf, bool rowl, int lane, float v) {
-  if (rowl) ybuf[lane] = v;
-  wave_sync();
-  float y = 0.f;
-#pragma unroll
-  for (int p = 0; p < SM; ++p) y = fmaf(kf[p], ybuf[p], y);
-  wave_sync();  // the buffer is reused by the next call
-  return y;
-}
-
-// G lanes per row, blocks of up to SM <= G points.  which = 0: bin A
-// (|N| <= G = GA); which = 1: bin B (GA < |N| <= 32), rows with |N| > SM are
-// handed to the workgroup solver.
-// (at SM = 20 the registers fit four wavefronts per SIMD without spilling;
-// the other shapes are held to fewer by their LDS or would spill)
-template <int G, int NT, int SM>
-__global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu((SM == 18 || SM == 20 || SM == 24) ? 4 : 1))) void k_numeric(Work w, int which) {
-  static_assert(SM <= G, "block bound");
-  constexpr int NG = NT / G;
-  constexpr int LD = SM + 1;
-  __shared__ NumGroupBuf<G, SM> sb[NG];
-
-  const int tid = threadIdx.x;
-  const int grp = tid / G;
-  const int lane = tid % G;
-  const bool rowl = lane < SM;  // this lane can hold a row of the block
-  NumGroupBuf<G, SM>& gb = sb[grp];
-
-  // rows of this solver
-  if ((which ? w.cnt->nB : w.cnt->nA) == 0) return;
-  const int smin = which ? small_limit(w.GA) + 1 : 0;
-  const int32_t* slots = which ? w.slotB : w.slotA;
-  const int sstride = which ? 32 : w.GA;
-  const int total = w.cnt->total_rows;
-  const RowBlocks rbk(total, 4 * NG);
-  int r0, r1;
-  if (!rbk.block(0, &r0, &r1)) return;
-  RefineMax rmx;
-  ChunkCursor cc;
-  // The group works one row ahead: while row g is solved, the chunk-local
-  // data, the slot entry and the A-row bounds of row g + NG (same chunk) are
-  // already on their way, so a row starts with only its A entries to load.
-  int nx_t = 0, nx_i = 0, nx_off = 0, nx_s = -1, nx_N = 0, nx_e0 = 0, nx_e1 = 0, nx_f0 = 0, nx_f1 = 0;
-  bool ahead = false;
-
-  for (int jb = 0; rbk.block(jb, &r0, &r1); ++jb) {
-  ahead = false;
-  for (int gbase = r0; gbase < r1; gbase += NG) {
-    const int g = gbase + grp;
-    if (g >= r1) break;  // group-uniform
-    int t, i, off, s, myN0, ae0, ae1, fe0, fe1;
-    if (ahead) {
-      t = nx_t; i = nx_i; off = nx_off; s = nx_s; myN0 = nx_N;
-      ae0 = nx_e0; ae1 = nx_e1; fe0 = nx_f0; fe1 = nx_f1;
-    } else {
-      cc.seek(w, g);
-      cc.row(w, g, &t, &i, &off, &s);
-      myN0 = slots[(cc.fbase + t) * sstride + min(lane, sstride - 1)];
-      ae0 = 0; ae1 = 0; fe0 = 0; fe1 = 0;
-      if (s >= smin && s <= SM && cc.live) {
-        if (lane < s) { ae0 = cc.md.rp[myN0]; ae1 = cc.md.rp[myN0 + 1]; }
-        fe0 = cc.md.rp[i];
-        fe1 = cc.md.rp[i + 1];
-      }
-    }
-    // the next row of this group, if it lies in the same chunk: its
-    // chunk-local data and slot entry now, its A-row bounds after the gather
-    const int gn = g + NG;
-    ahead = gn < r1 && gn < cc.re;
-    if (ahead) {
-      cc.row(w, gn, &nx_t, &nx_i, &nx_off, &nx_s);
-      nx_N = slots[(cc.fbase + nx_t) * sstride + min(lane, sstride - 1)];
-    }
-    const bool mine = s >= smin && s <= SM && cc.live;  // group-uniform
-    const bool nx_mine = ahead && nx_s >= smin && nx_s <= SM && cc.live;
-    if (!mine) {
-      if (which && s > SM && s <= 32 && cc.live && lane == 0) {
-        // a bin-B row larger than this kernel's blocks: the workgroup solver
-        const int qc = atomicAdd(&w.cnt->nC, 1);
-        if (qc < w.capC) w.binC[qc] = cc.c * w.chunk + t;
-        else flag_row(&w.st[cc.m], ST_UNSUPPORTED, i);
-      }
-      if (nx_mine) {
-        nx_e0 = 0; nx_e1 = 0;
-        if (lane < nx_s) { nx_e0 = cc.md.rp[nx_N]; nx_e1 = cc.md.rp[nx_N + 1]; }
-        nx_f0 = cc.md.rp[nx_i];
-        nx_f1 = cc.md.rp[nx_i + 1];
-      }
-      continue;  // another solver's row
-    }
-    const int c = cc.c;
-    const int entry = c * w.chunk + t;
-    const GDesc& d = cc.md;
-    MatStatus* st = &w.st[cc.m];
-    RowInfo ri;
-    ri.m = cc.m;
-    ri.i = i;
-    ri.r = g - cc.rbase_m;
-    ri.off = off;
-    ri.s = s;
-    ri.fine0 = cc.fine0;
-    if (lane == 0) d.Rrp[ri.r] = ri.off;
-    const int myN = (lane < s) ? myN0 : 0x7fffffff;
-    gb.nb[lane] = myN;
-    const uint64_t below = __ballot(lane < s && myN < i);
-    const int dpos = __popcll((below >> ((threadIdx.x & 63) - lane)) & ((G >= 64) ? ~0ull : ((1ull << G) - 1)));
-
-    // ---- gather: K = (A[N,N])^T (padded with identity), f = -A[i,N] ----
-    if (rowl) {
-#pragma unroll
-      for (int tt = 0; tt < SM; ++tt) gb.K[tt * LD + lane] = (tt == lane && tt >= s) ? 1.0 : 0.0;
-      gb.f[lane] = 0.0;
-    }
-    wave_sync();
-    for (int e = ae0; e < ae1; e += 4) {
-      int k[4];
-      double v[4];
-#pragma unroll
-      for (int j = 0; j < 4; ++j) {
-        k[j] = -1;
-        v[j] = 0.0;
-        if (e + j < ae1) { k[j] = d.ci[e + j]; v[j] = d.va[e + j]; }
-      }
-#pragma unroll
-      for (int j = 0; j < 4; ++j) {
-        const int qq = find_pos<G>(gb.nb, k[j]);
-        if (qq >= 0) gb.K[qq * LD + lane] = v[j];
-      }
-    }
-    for (int e = fe0 + lane; e < fe1; e += G) {
-      const int qq = find_pos<G>(gb.nb, d.ci[e]);
-      if (qq >= 0) gb.f[qq] = -d.va[e];
-    }
-    wave_sync();
-    if (nx_mine) {
-      nx_e0 = 0; nx_e1 = 0;
-      if (lane < nx_s) { nx_e0 = d.rp[nx_N]; nx_e1 = d.rp[nx_N + 1]; }
-      nx_f0 = d.rp[nx_i];
-      nx_f1 = d.rp[nx_i + 1];
-    }
-
-    // ---- FP32 inverse of the row-scaled block ----
-    float amax = 0.f;
-    double knorm = 0.0;
-#pragma unroll
-    for (int p = 0; p < SM; ++p) {
-      const double v = rowl ? gb.K[lane * LD + p] : 0.0;
-      amax = fmaxf(amax, (float)fabs(v));
-      knorm += fabs(v);
-    }
-    amax = group_maxf<G>(amax);
-    knorm = group_maxd<G>(knorm);
-    int ex = 0;
-    frexpf(amax, &ex);
-    const double scale = ldexp(1.0, -ex);
-    float kf[SM];
-#pragma unroll
-    for (int p = 0; p < SM; ++p) kf[p] = rowl ? (float)(gb.K[lane * LD + p] * scale) : 0.f;
-    int bad = !(amax > 0.f) || !(amax < 3.0e38f);
-    // Gauss-Jordan in place, no pivoting: step k scales pivot row k and
-    // clears column k in every other row; column k then holds the inverse's
-    // column k.  The pivots are those of the LU factorisation, so the same
-    // tiny-pivot test applies.  Each lane holds one row; the pivot row reaches
-    // the group by ds_swizzle.  One update serves every lane: the pivot lane
-    // subtracts (1 - 1/pivot) times its own row, which scales it by 1/pivot.
-#pragma unroll
-    for (int k = 0; k < SM; ++k) {
-      float u[SM];
-#pragma unroll
-      for (int p = 0; p < SM; ++p) u[p] = gbf<G>(kf[p], k);
-      // FP32 factors only precondition the FP64 refinement: the hardware
-      // reciprocal (1 ulp) is accurate enough
-      const float pinv = __builtin_amdgcn_rcpf(u[k]);
-      bad |= !(fabsf(u[k]) >= 0x1p-24f);
-      const bool pl = lane == k;
-      const float lk = kf[k] * pinv;
-      const float l = pl ? 1.f - pinv : lk;
-#pragma unroll
-      for (int p = 0; p < SM; ++p)
-        if (p != k) kf[p] = fmaf(-l, u[p], kf[p]);
-      kf[k] = pl ? pinv : -lk;
-    }
-    bad = group_ori<G>(bad);
-
-    // ---- solve and refine in FP64 ----
-    const double fq = rowl ? gb.f[lane] : 0.0;
-    const double fnorm = group_maxd<G>(fabs(fq));
-    double z = 0.0;
-    int it = 0;
-    bool conv = false;
-    if (!bad) {
-      z = (double)inv_apply<SM>(kf, gb.y, rowl, lane, (float)(fq * scale));
-      for (it = 1; it <= kRefineMax; ++it) {
-        if (rowl) gb.z[lane] = z;
-        wave_sync();
-        double r = fq;
-        if (rowl) {
-#pragma unroll
-          for (int p = 0; p < SM; ++p) r = fma(-gb.K[lane * LD + p], gb.z[p], r);
-        }
-        // the FP32 solution itself is never accurate to FP64 rounding: the
-        // first correction is applied unchecked
-        if (it > 1) {
-          const double rn = group_maxd<G>(fabs(r));
-          const double zn = group_maxd<G>(fabs(z));
-          if (rn <= 0x1p-47 * (knorm * zn + fnorm)) { conv = true; break; }
-        }
-        const float dz = inv_apply<SM>(kf, gb.y, rowl, lane, (float)(r * scale));
-        z += (double)dz;
-        wave_sync();
-      }
-      if (!(z == z)) conv = false;
-      conv = group_ori<G>(conv ? 0 : 1) == 0;
-    }
-    if (!conv) {
-      // FP32 factorisation not trusted: the workgroup solver redoes the row in FP64
-      if (lane == 0) {
-        const int qc = atomicAdd(&w.cnt->nC, 1);
-        if (qc < w.capC) w.binC[qc] = entry;
-        else flag_row(st, ST_UNSUPPORTED, i);
-      }
-      continue;
-    }
-    if (lane == 0) rmx.add(w, ri.m, it);
-
-    // ---- R row: F-entries of N(i) around the injected C-point ----
-    if (lane < s) put_f_entry(w, d, ri.fine0, ri.off + lane + (lane >= dpos ? 1 : 0), myN, i, z);
-    if (lane == 0) {
-      d.Rci[ri.off + dpos] = i;
-      d.Rva[ri.off + dpos] = 1.0;
-    }
-  }
-  }
-  if (lane == 0) rmx.flush(w);
-}
-
-// ---------------------------------------------------------------------------
-// numeric pass, G lanes per row with R block rows per lane: block row q lives
-// in lane q % G, register slot q / G.  Every lane works on R rows of the
-// block, so a wavefront solves 64 / G rows at a time with no lane idle when
-// G R = |N|, and each Gauss-Jordan step broadcasts the pivot row once for
-// the R rows of a lane (the lane-per-row kernel above broadcasts it once per
-// block row and leaves G - |N| lanes idle).
-// ---------------------------------------------------------------------------
-constexpr int pow2_at_least(int x) { return x <= 1 ? 1 : 2 * pow2_at_least((x + 1) / 2); }
-
-// LDS of one row of k_lanes: blocks of up to SM points
-// (f, zb and nb hold a slot for every lane row, dummies included, so that
-// no store or load on them depends on the lane)
-template <int SM, int RS>
-struct LaneRowsBuf {
-  double K[SM * SM];                 // FP64 block, row q = row q of (A[N,N])^T
-  double f[RS];                      // -A[i,N], 0 beyond |N|
-  double zb[RS];                     // broadcast buffer: z (FP64), or a correction's right-hand side (FP32)
-  int nb[pow2_at_least(SM)];         // sorted N(i), INT32_MAX beyond |N|
-};
-
-// y_q = sum_p Kinv[q][p] v_p for the R rows q of a lane (v = scale * x in
-// FP32): v goes through LDS once, then every lane reads all of it
-template <int G, int R, int SM>
-__device__ __forceinline__ void lanes_apply_inv(const float (&kf)[R][SM], float* yb, int lane, const double (&x)[R],
-                                                double scale, float (&y)[R]) {
-#pragma unroll
-  for (int r = 0; r < R; ++r) yb[lane + G * r] = (float)(x[r] * scale);  // dummy rows write past SM, unread
-  wave_sync();
-  float vs[SM];
-#pragma unroll
-  for (int p = 0; p < SM; ++p) vs[p] = yb[p];
-  wave_sync();  // the buffer is reused next
-#pragma unroll
-  for (int r = 0; r < R; ++r) {
-    float acc = 0.f;
-#pragma unroll
-    for (int p = 0; p < SM; ++p) acc = fmaf(kf[r][p], vs[p], acc);
-    y[r] = acc;
-  }
-}
-
-// One Gauss-Jordan step of k_lanes, K a compile-time constant (the swizzle
-// pattern is an immediate; a loop over K is not always unrolled in full).
-template <int G, int R, int SM, int K>
-__device__ __forceinline__ void lanes_gj_step(float (&kf)[R][SM], int lane, int& bad) {
-  constexpr int src = K % G, slot = K / G;
-  float u[SM];
-#pragma unroll
-  for (int p = 0; p < SM; ++p)
-    u[p] = __int_as_float(__builtin_amdgcn_ds_swizzle(__float_as_int(kf[slot][p]), (32 - G) | (src << 5)));
-  // FP32 factors only precondition the FP64 refinement: the hardware
-  // reciprocal (1 ulp) is accurate enough
-  const float pinv = __builtin_amdgcn_rcpf(u[K]);
-  bad |= !(fabsf(u[K]) >= 0x1p-24f);
-#pragma unroll
-  for (int r = 0; r < R; ++r) {
-    const bool pl = (r == slot) && (lane == src);
-    const float lk = kf[r][K] * pinv;
-    const float l = pl ? 1.f - pinv : lk;
-#pragma unroll
-    for (int p = 0; p < SM; ++p)
-      if (p != K) kf[r][p] = fmaf(-l, u[p], kf[r][p]);
-    kf[r][K] = pl ? pinv : -lk;
-  }
-  // keep the scheduler from interleaving steps (that multiplies live rows)
-  __builtin_amdgcn_sched_barrier(0);
-}
-
-template <int G, int R, int SM, int... Ks>
-__device__ __forceinline__ void lanes_gj(float (&kf)[R][SM], int lane, int& bad, std::integer_sequence<int, Ks...>) {
-  (lanes_gj_step<G, R, SM, Ks>(kf, lane, bad), ...);
-}
-
-template <int G, int R, int SM, int NT>
-__global__ __launch_bounds__(NT) void k_lanes(Work w, int which) {
-  static_assert(SM <= G * R && SM > G * (R - 1), "block bound");
-  static_assert(NT % 64 == 0 && 64 % G == 0, "shape");
-  constexpr int NG = NT / G;
-  constexpr int NBP = pow2_at_least(SM);
-  __shared__ LaneRowsBuf<SM, G * R> sb[NG];
-
-  const int tid = threadIdx.x;
-  const int grp = tid / G;
-  const int lane = tid % G;
-  LaneRowsBuf<SM, G * R>& gb = sb[grp];
-  const uint64_t gmask = (G >= 64) ? ~0ull : (((1ull << G) - 1ull) << ((threadIdx.x & 63) - lane));
-  // block rows of this lane: q_r = lane + G r; rows at or beyond SM are dummies
-  bool rowl[R];
-#pragma unroll
-  for (int r = 0; r < R; ++r) rowl[r] = lane + G * r < SM;
-
-  if ((which ? w.cnt->nB : w.cnt->nA) == 0) return;
-  const int smin = which ? small_limit(w.GA) + 1 : 0;
-  const int32_t* slots = which ? w.slotB : w.slotA;
-  const int sstride = which ? 32 : slot_stride(w.GA);
-  const int total = w.cnt->total_rows;
-  const RowBlocks rbk(total, 4 * NG);
-  int r0, r1;
-  if (!rbk.block(0, &r0, &r1)) return;
-  RefineMax rmx;
-  ChunkCursor cc;
-  // one row ahead, as in k_numeric: chunk data, slot entries and A-row bounds
-  // of row g + NG are loaded while row g is solved
-  int nx_t = 0, nx_i = 0, nx_off = 0, nx_s = -1, nx_f0 = 0, nx_f1 = 0;
-  int nx_N[R], nx_e0[R], nx_e1[R];
-  bool ahead = false;
-
-  for (int jb = 0; rbk.block(jb, &r0, &r1); ++jb) {
-  ahead = false;
-  for (int gbase = r0; gbase < r1; gbase += NG) {
-    const int g = gbase + grp;
-    if (g >= r1) break;  // group-uniform
-    int t, i, off, s, fe0, fe1;
-    int myN0[R], ae0[R], ae1[R];
-    if (ahead) {
-      t = nx_t; i = nx_i; off = nx_off; s = nx_s; fe0 = nx_f0; fe1 = nx_f1;
-#pragma unroll
-      for (int r = 0; r < R; ++r) { myN0[r] = nx_N[r]; ae0[r] = nx_e0[r]; ae1[r] = nx_e1[r]; }
-    } else {
-      cc.seek(w, g);
-      cc.row(w, g, &t, &i, &off, &s);
-      fe0 = 0; fe1 = 0;
-      const bool ok = s >= smin && s <= SM && cc.live;
-#pragma unroll
-      for (int r = 0; r < R; ++r) {
-        const int q = lane + G * r;
-        myN0[r] = slots[(cc.fbase + t) * sstride + min(q, sstride - 1)];
-        ae0[r] = 0; ae1[r] = 0;
-        if (ok && q < s) { ae0[r] = cc.md.rp[myN0[r]]; ae1[r] = cc.md.rp[myN0[r] + 1]; }
-      }
-      if (ok) { fe0 = cc.md.rp[i]; fe1 = cc.md.rp[i + 1]; }
-    }
-    const int gn = g + NG;
-    ahead = gn < r1 && gn < cc.re;
-    if (ahead) {
-      cc.row(w, gn, &nx_t, &nx_i, &nx_off, &nx_s);
-#pragma unroll
-      for (int r = 0; r < R; ++r) nx_N[r] = slots[(cc.fbase + nx_t) * sstride + min(lane + G * r, sstride - 1)];
-    }
-    const bool mine = s >= smin && s <= SM && cc.live;  // group-uniform
-    const bool nx_mine = ahead && nx_s >= smin && nx_s <= SM && cc.live;
-    if (!mine) {
-      if (which && s > SM && s <= 32 && cc.live && lane == 0) {
-        const int qc = atomicAdd(&w.cnt->nC, 1);
-        if (qc < w.capC) w.binC[qc] = cc.c * w.chunk + t;
-        else flag_row(&w.st[cc.m], ST_UNSUPPORTED, i);
-      }
-      if (nx_mine) {
-#pragma unroll
-        for (int r = 0; r < R; ++r) {
-          nx_e0[r] = 0; nx_e1[r] = 0;
-          if (lane + G * r < nx_s) { nx_e0[r] = cc.md.rp[nx_N[r]]; nx_e1[r] = cc.md.rp[nx_N[r] + 1]; }
-        }
-        nx_f0 = cc.md.rp[nx_i];
-        nx_f1 = cc.md.rp[nx_i + 1];
-      }
-      continue;
-    }
-    const int entry = cc.c * w.chunk + t;
-    const GDesc& d = cc.md;
-    MatStatus* st = &w.st[cc.m];
-    const int rr = g - cc.rbase_m;
-    if (lane == 0) d.Rrp[rr] = off;
-    int myN[R];
-    int below = 0;
-#pragma unroll
-    for (int r = 0; r < R; ++r) {
-      const int q = lane + G * r;
-      myN[r] = (q < s) ? myN0[r] : 0x7fffffff;
-      gb.nb[q] = myN[r];
-      gb.f[q] = 0.0;
-      below += __popcll(__ballot(q < s && myN[r] < i) & gmask);
-    }
-    if constexpr (G * R < NBP) {
-      for (int q = G * R + lane; q < NBP; q += G) gb.nb[q] = 0x7fffffff;
-    }
-    const int dpos = below;
-
-    // ---- gather: K = (A[N,N])^T (identity on the padding), f = -A[i,N] ----
-#pragma unroll
-    for (int r = 0; r < R; ++r) {
-      const int q = lane + G * r;
-      if (q < SM) {
-#pragma unroll
-        for (int p = 0; p < SM; ++p) gb.K[q * SM + p] = (p == q && q >= s) ? 1.0 : 0.0;
-      }
-    }
-    wave_sync();
-    {
-      int len = 0;
-#pragma unroll
-      for (int r = 0; r < R; ++r) len = max(len, ae1[r] - ae0[r]);
-      for (int o = 0; o < len; o += 4) {
-        int k[R][4];
-        double v[R][4];
-#pragma unroll
-        for (int r = 0; r < R; ++r) {
-#pragma unroll
-          for (int j = 0; j < 4; ++j) {
-            k[r][j] = -1;
-            v[r][j] = 0.0;
-            if (ae0[r] + o + j < ae1[r]) { k[r][j] = d.ci[ae0[r] + o + j]; v[r][j] = d.va[ae0[r] + o + j]; }
-          }
-        }
-#pragma unroll
-        for (int r = 0; r < R; ++r) {
-#pragma unroll
-          for (int j = 0; j < 4; ++j) {
-            const int qq = find_pos<NBP>(gb.nb, k[r][j]);
-            if (qq >= 0) gb.K[qq * SM + lane + G * r] = v[r][j];
-          }
-        }
-      }
-    }
-    for (int e = fe0 + lane; e < fe1; e += G) {
-      const int qq = find_pos<NBP>(gb.nb, d.ci[e]);
-      if (qq >= 0) gb.f[qq] = -d.va[e];
-    }
-    wave_sync();
-    if (nx_mine) {
-#pragma unroll
-      for (int r = 0; r < R; ++r) {
-        nx_e0[r] = 0; nx_e1[r] = 0;
-        if (lane + G * r < nx_s) { nx_e0[r] = d.rp[nx_N[r]]; nx_e1[r] = d.rp[nx_N[r] + 1]; }
-      }
-      nx_f0 = d.rp[nx_i];
-      nx_f1 = d.rp[nx_i + 1];
-    }
-
-    // ---- FP32 inverse of the scaled block ----
-    // (loops over columns that index no register array stay rolled, so the
-    // compiler does not hoist every LDS load of the block at once)
-    float amax = 0.f;
-    double knorm = 0.0;
-#pragma unroll
-    for (int r = 0; r < R; ++r) {
-      // a dummy row (beyond SM) reads the last row and is ignored
-      const double* kr = gb.K + min(lane + G * r, SM - 1) * SM;
-      double rs = 0.0;
-#pragma unroll 4
-      for (int p = 0; p < SM; ++p) {
-        const double v = (lane + G * r < s) ? fabs(kr[p]) : 0.0;  // the identity padding does not count
-        amax = fmaxf(amax, (float)v);
-        rs += v;
-      }
-      knorm = fmax(knorm, rs);
-    }
-    amax = group_maxf<G>(amax);
-    knorm = group_maxd<G>(knorm);
-    int ex = 0;
-    frexpf(amax, &ex);
-    const double scale = ldexp(1.0, -ex);
-    float kf[R][SM];
-#pragma unroll
-    for (int r = 0; r < R; ++r) {
-#pragma unroll
-      for (int p = 0; p < SM; ++p) {
-        const float x = (float)(gb.K[min(lane + G * r, SM - 1) * SM + p] * scale);
-        // padding rows keep a unit pivot whatever the scale (they are
-        // decoupled from the block, and their z stays 0)
-        kf[r][p] = !rowl[r] ? 0.f : (lane + G * r >= s) ? (p == lane + G * r ? 1.f : 0.f) : x;
-        if ((p & 7) == 7) __builtin_amdgcn_sched_barrier(0);
-      }
-    }
-    int bad = !(amax > 0.f) || !(amax < 3.0e38f);
-    // Gauss-Jordan in place without pivoting (as in k_numeric): step k
-    // broadcasts pivot row k from lane k % G, slot k / G, once for all R rows
-    // of every lane
-    lanes_gj<G, R, SM>(kf, lane, bad, std::make_integer_sequence<int, SM>{});
-    bad = group_ori<G>(bad);
-
-    // ---- solve and refine in FP64 ----
-    double fq[R], z[R];
-    double fmaxv = 0.0;
-#pragma unroll
-    for (int r = 0; r < R; ++r) {
-      fq[r] = gb.f[lane + G * r];  // 0 on padding and dummy rows
-      fmaxv = fmax(fmaxv, fabs(fq[r]));
-      z[r] = 0.0;
-    }
-    const double fnorm = group_maxd<G>(fmaxv);
-    int it = 0;
-    bool conv = false;
-    // Every group runs the solve, also one whose factorisation is not
-    // trusted (its result is then discarded): a branch on `bad` here lets the
-    // compiler sink the last elimination steps into it, which keeps the
-    // broadcasts of many steps alive at once and spills.
-    {
-      {
-        float y[R];
-        lanes_apply_inv<G, R, SM>(kf, reinterpret_cast<float*>(gb.zb), lane, fq, scale, y);
-#pragma unroll
-        for (int r = 0; r < R; ++r) z[r] = (double)y[r];
-      }
-      for (it = 1; it <= kRefineMax; ++it) {
-#pragma unroll
-        for (int r = 0; r < R; ++r) gb.zb[lane + G * r] = z[r];  // dummy rows write past SM, unread
-        wave_sync();
-        double res[R];
-        double rmax = 0.0, zmax = 0.0;
-#pragma unroll
-        for (int r = 0; r < R; ++r) res[r] = fq[r];
-        // (a dummy row, beyond SM, reads the last row and is ignored: no
-        // branch on the lane inside the loop)
-#pragma unroll 2
-        for (int p = 0; p < SM; ++p) {
-          const double zp = gb.zb[p];
-#pragma unroll
-          for (int r = 0; r < R; ++r) res[r] = fma(-gb.K[min(lane + G * r, SM - 1) * SM + p], zp, res[r]);
-        }
-        wave_sync();
-#pragma unroll
-        for (int r = 0; r < R; ++r) {
-          rmax = fmax(rmax, rowl[r] ? fabs(res[r]) : 0.0);
-          zmax = fmax(zmax, rowl[r] ? fabs(z[r]) : 0.0);
-        }
-        // the FP32 solution is never accurate to FP64 rounding: the first
-        // correction is applied unchecked
-        if (bad) break;  // group-uniform: the FP64 solver takes the row
-        if (it > 1) {
-          const double rn = group_maxd<G>(rmax);
-          const double zn = group_maxd<G>(zmax);
-          if (rn <= 0x1p-47 * (knorm * zn + fnorm)) { conv = true; break; }
-        }
-        float y[R];
-        lanes_apply_inv<G, R, SM>(kf, reinterpret_cast<float*>(gb.zb), lane, res, scale, y);
-#pragma unroll
-        for (int r = 0; r < R; ++r) z[r] += (double)y[r];
-      }
-      bool nan = false;
-#pragma unroll
-      for (int r = 0; r < R; ++r) nan |= !(z[r] == z[r]);
-      if (nan || bad) conv = false;
-      conv = group_ori<G>(conv ? 0 : 1) == 0;
-    }
-    if (!conv) {
-      // FP32 factorisation not trusted: the workgroup solver redoes the row in FP64
-      if (lane == 0) {
-        const int qc = atomicAdd(&w.cnt->nC, 1);
-        if (qc < w.capC) w.binC[qc] = entry;
-        else flag_row(st, ST_UNSUPPORTED, i);
-      }
-      continue;
-    }
-    if (lane == 0) rmx.add(w, cc.m, it);
-
-    // ---- R row: F-entries of N(i) around the injected C-point ----
-#pragma unroll
-    for (int r = 0; r < R; ++r) {
-      const int q = lane + G * r;
-      if (q < s) put_f_entry(w, d, cc.fine0, off + q + (q >= dpos ? 1 : 0), myN[r], i, z[r]);
-    }
-    if (lane == 0) {
-      d.Rci[off + dpos] = i;
-      d.Rva[off + dpos] = 1.0;
-    }
-  }
-  }
-  if (lane == 0) rmx.flush(w);
 }
 
 // ---------------------------------------------------------------------------
@@ -2750,63 +2125,6 @@ hipError_t launch_count_big(const Work& w, int blocks, hipStream_t s) {
 hipError_t launch_scan(const Work& w, hipStream_t s) {
   hipLaunchKernelGGL(k_scan, dim3(1), dim3(1024), 0, s, w);
   return hipGetLastError();
-}
-
-// persistent grid: as many workgroups as fit on the device at once.
-// which = 0: bin A with `group` lanes per row; which = 1: bin B with blocks of
-// up to sm points (16: 16 lanes per row; 18, 20, 24 or 32: 32 lanes per row).
-hipError_t launch_numeric(const Work& w, int which, int group, int sm, int wg_threads, int cus, hipStream_t s) {
-#define CLAIR_NUM(GG, NTT, SMM)                                                                         \
-  if (group == GG && wg_threads == NTT && sm == SMM) {                                                  \
-    int per = 0;                                                                                        \
-    hipError_t e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per, k_numeric<GG, NTT, SMM>, NTT, 0); \
-    if (e != hipSuccess) return e;                                                                      \
-    const int blocks = (std::max(1, per) * cus + 7) / 8 * 8;                                           \
-    hipLaunchKernelGGL((k_numeric<GG, NTT, SMM>), dim3(blocks), dim3(NTT), 0, s, w, which);             \
-    return hipGetLastError();                                                                           \
-  }
-  CLAIR_NUM(16, 256, 16)
-  CLAIR_NUM(16, 128, 16)
-  CLAIR_NUM(16, 64, 16)
-  CLAIR_NUM(32, 256, 32)
-  CLAIR_NUM(32, 128, 32)
-  CLAIR_NUM(32, 64, 32)
-  CLAIR_NUM(32, 128, 18)
-  CLAIR_NUM(32, 128, 20)
-  CLAIR_NUM(32, 128, 24)
-#undef CLAIR_NUM
-  return hipErrorInvalidValue;
-}
-
-// G lanes per row, R block rows per lane, blocks of up to SM points, one
-// wavefront per workgroup; persistent grid as for k_numeric
-hipError_t launch_lanes(const Work& w, int which, int group, int rows_per_lane, int sm, int wg_threads, int cus,
-                        hipStream_t s) {
-#define CLAIR_LR(GG, RR, SMM, NTT)                                                                          \
-  if (group == GG && rows_per_lane == RR && sm == SMM && wg_threads == NTT) {                               \
-    int per = 0;                                                                                            \
-    hipError_t e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per, k_lanes<GG, RR, SMM, NTT>, NTT, 0);   \
-    if (e != hipSuccess) return e;                                                                          \
-    const int blocks = (std::max(1, per) * cus + 7) / 8 * 8;                                               \
-    hipLaunchKernelGGL((k_lanes<GG, RR, SMM, NTT>), dim3(blocks), dim3(NTT), 0, s, w, which);               \
-    return hipGetLastError();                                                                               \
-  }
-  CLAIR_LR(8, 2, 16, 64)
-  CLAIR_LR(8, 3, 20, 64)
-  CLAIR_LR(8, 3, 24, 64)
-  CLAIR_LR(16, 1, 16, 64)
-  CLAIR_LR(16, 2, 20, 64)
-  CLAIR_LR(16, 2, 24, 64)
-  CLAIR_LR(16, 2, 32, 64)
-  CLAIR_LR(32, 1, 20, 64)
-  CLAIR_LR(32, 1, 24, 64)
-  CLAIR_LR(32, 1, 32, 64)
-  CLAIR_LR(4, 2, 8, 64)
-  CLAIR_LR(4, 2, 8, 128)
-  CLAIR_LR(2, 4, 8, 64)
-  CLAIR_LR(2, 4, 8, 128)
-#undef CLAIR_LR
-  return hipErrorInvalidValue;
 }
 
 hipError_t launch_rows8(const Work& w, int wg_threads, int cus, hipStream_t s) {

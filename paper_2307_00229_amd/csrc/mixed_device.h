@@ -79,6 +79,57 @@ __device__ __forceinline__ void put_f_entry(const Work& w, const GDesc& d, int64
 // Per-lane cache of the chunk a run of consecutive rows lies in: reloaded only
 // when the row index crosses into another chunk, so a row costs one level of
 // (coalesced) per-row loads instead of the chunk -> matrix -> descriptor chain.
+// The matrix's pointers are not part of it: held per lane through a solve they
+// cost up to 40 VGPRs, so the solvers read the few they need from the
+// descriptor (row_desc) before the gather and again before the row's stores.
+struct RowCursor {
+  int c = -1;
+  int rb = 0, re = 0;   // global rows [rb, re) of chunk c
+  int m = 0;
+  int nc = 0;           // C-rows in the chunk
+  int tot = 0;          // nnz(R) of the chunk
+  int2 bins = {0, 0};   // rows of the chunk in bin A and bin B
+  int zoff = 0;         // R offset of the chunk inside its matrix
+  int rbase_m = 0;      // first global row of the matrix
+  int64_t fbase = 0;    // fine offset of the chunk's first point (batch-wide)
+  bool live = false;
+
+  __device__ __forceinline__ void seek(const Work& w, int g) {
+    if (c >= 0 && g >= rb && g < re) return;
+    c = row_chunk_fast(w, g);
+    rb = w.chunk_rbase[c];
+    re = w.chunk_rbase[c + 1];
+    m = w.chunk_mat[c];
+    const MatStatus& st = w.st[m];
+    nc = w.chunk_nc[c];
+    tot = w.chunk_nnz[c];
+    bins = w.chunk_bins[c];
+    zoff = (int)(w.chunk_nzglob[c] - st.nz_base);
+    rbase_m = st.row_base;
+    fbase = w.desc[m].fine0 + (int64_t)(c - w.desc[m].chunk0) * w.chunk;
+    live = matrix_live(st);
+  }
+  // row g (inside the chunk): fine index, R offset and |N|
+  __device__ __forceinline__ void row(const Work& w, int g, int* t, int* i, int* off, int* sz) const {
+    const int tt = g - rb;
+    *t = tt;
+    *i = w.clocal[fbase + tt];
+    const int l0 = w.lnz[fbase + tt];
+    const int l1 = (tt + 1 < nc) ? w.lnz[fbase + tt + 1] : tot;
+    *off = zoff + l0;
+    *sz = l1 - l0 - 1;
+  }
+};
+
+// matrix m's descriptor, read here and not kept from an earlier read
+__device__ __forceinline__ GDesc row_desc(const Work& w, int m) {
+  asm volatile("" ::: "memory");
+  return gview(w.desc[m]);
+}
+
+// Per-lane cache of the chunk a run of consecutive rows lies in: reloaded only
+// when the row index crosses into another chunk, so a row costs one level of
+// (coalesced) per-row loads instead of the chunk -> matrix -> descriptor chain.
 struct ChunkCursor {
   int c = -1;
   int rb = 0, re = 0;   // global rows [rb, re) of chunk c
@@ -214,26 +265,6 @@ __device__ __forceinline__ int slot_stride(int GA) { return GA <= 4 ? 8 : GA; }
 // Communication inside a group of G lanes (G = 8, 16 or 32; groups are
 // aligned runs of G lanes of a wavefront).
 //
-// gbi: lane k of the group to all its lanes.  ds_swizzle in bit mode keeps
-// the lane bits above the group (and-mask 32 - G) and sets the rest to k; the
-// pattern is an immediate, so k must fold to a constant (unrolled loops).
-template <int G>
-__device__ __forceinline__ int gbi(int v, int k) {
-  static_assert(G == 2 || G == 4 || G == 8 || G == 16 || G == 32, "group size");
-#define CLAIR_SWZ(K) \
-  case K: return __builtin_amdgcn_ds_swizzle(v, (32 - G) | ((K) << 5));
-  switch (k) {
-    CLAIR_SWZ(0) CLAIR_SWZ(1) CLAIR_SWZ(2) CLAIR_SWZ(3) CLAIR_SWZ(4) CLAIR_SWZ(5) CLAIR_SWZ(6) CLAIR_SWZ(7)
-    CLAIR_SWZ(8) CLAIR_SWZ(9) CLAIR_SWZ(10) CLAIR_SWZ(11) CLAIR_SWZ(12) CLAIR_SWZ(13) CLAIR_SWZ(14) CLAIR_SWZ(15)
-    CLAIR_SWZ(16) CLAIR_SWZ(17) CLAIR_SWZ(18) CLAIR_SWZ(19) CLAIR_SWZ(20) CLAIR_SWZ(21) CLAIR_SWZ(22) CLAIR_SWZ(23)
-    CLAIR_SWZ(24) CLAIR_SWZ(25) CLAIR_SWZ(26) CLAIR_SWZ(27) CLAIR_SWZ(28) CLAIR_SWZ(29) CLAIR_SWZ(30)
-    default: return __builtin_amdgcn_ds_swizzle(v, (32 - G) | (31 << 5));
-  }
-#undef CLAIR_SWZ
-}
-template <int G>
-__device__ __forceinline__ float gbf(float v, int k) { return __int_as_float(gbi<G>(__float_as_int(v), k)); }
-
 // gpart: the value of a partner lane for a butterfly-like reduction.  Steps 1
 // and 2 pair lanes inside a quad (DPP quad_perm [1,0,3,2] and [2,3,0,1]), step
 // 4 mirrors the halves of 8 lanes (DPP row_half_mirror), step 8 mirrors the
@@ -252,24 +283,6 @@ __device__ __forceinline__ double gpartd(double v) {
   return __hiloint2double(gpart<STEP>(__double2hiint(v)), gpart<STEP>(__double2loint(v)));
 }
 
-template <int G>
-__device__ __forceinline__ float group_maxf(float v) {
-  v = fmaxf(v, __int_as_float(gpart<1>(__float_as_int(v))));
-  if constexpr (G >= 4) v = fmaxf(v, __int_as_float(gpart<2>(__float_as_int(v))));
-  if constexpr (G >= 8) v = fmaxf(v, __int_as_float(gpart<4>(__float_as_int(v))));
-  if constexpr (G >= 16) v = fmaxf(v, __int_as_float(gpart<8>(__float_as_int(v))));
-  if constexpr (G >= 32) v = fmaxf(v, __int_as_float(gpart<16>(__float_as_int(v))));
-  return v;
-}
-template <int G>
-__device__ __forceinline__ double group_maxd(double v) {
-  v = fmax(v, gpartd<1>(v));
-  if constexpr (G >= 4) v = fmax(v, gpartd<2>(v));
-  if constexpr (G >= 8) v = fmax(v, gpartd<4>(v));
-  if constexpr (G >= 16) v = fmax(v, gpartd<8>(v));
-  if constexpr (G >= 32) v = fmax(v, gpartd<16>(v));
-  return v;
-}
 template <int G>
 __device__ __forceinline__ int group_ori(int v) {
   v |= gpart<1>(v);
