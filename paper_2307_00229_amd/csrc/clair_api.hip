@@ -77,7 +77,7 @@ struct Layout {
   int64_t capC;
 };
 
-Layout make_layout(int nmat, int nchunks, int64_t n_total, int GA, bool any_agg, int adj_w) {
+Layout make_layout(int nmat, int nchunks, int64_t n_total, int GA, bool any_agg, int adj_w, int rb_log) {
   Layout L{};
   size_t o = 0;
   auto take = [&](size_t bytes) {
@@ -99,7 +99,7 @@ Layout make_layout(int nmat, int nchunks, int64_t n_total, int GA, bool any_agg,
   L.chunk_nzbase = take(sizeof(int64_t) * (nchunks + 1));
   L.chunk_mat = take(sizeof(int32_t) * (nchunks + 1));
   L.chunk_bins = take(sizeof(int2) * (nchunks + 1));
-  L.row_block_chunk = take(sizeof(int32_t) * (n_total / 256 + 2));
+  L.row_block_chunk = take(sizeof(int32_t) * ((n_total >> rb_log) + 2));
   L.clocal = take(sizeof(int32_t) * (n_total + 1));
   L.lnz = take(sizeof(int32_t) * (n_total + 1));
   L.chead = take(sizeof(int32_t) * (n_total + 1));
@@ -348,7 +348,12 @@ int prepare(clair_ctx* c, int32_t nmat, const clair_csr_t* A, const int8_t* cons
     }
     b->adj_w = c->adj_mode > 0 ? (w_need ? c->adj_mode : 0) : w_need;
   }
-  b->L = make_layout(nmat, b->nchunks, b->n_total, c->group, b->any_agg, b->adj_w);
+  // an entry per 256 rows where a chunk holds about as many (k_scan writes them,
+  // one workgroup: an entry per 64 rows cost it 23 us more on 13,400 chunks),
+  // per 64 rows for smaller chunks, whose rows are found by bisection between
+  // two entries
+  const int rb_log = b->chunk >= 512 ? 8 : 6;
+  b->L = make_layout(nmat, b->nchunks, b->n_total, c->group, b->any_agg, b->adj_w, rb_log);
   if (c->fixed) {
     if (b->L.total > c->fixed_dev_bytes || b->L.head_bytes > c->fixed_host_bytes / 2) {
       snprintf(g_last_error, sizeof(g_last_error),
@@ -406,6 +411,7 @@ int prepare(clair_ctx* c, int32_t nmat, const clair_csr_t* A, const int8_t* cons
   w.fadj = reinterpret_cast<int32_t*>(base + b->L.fadj);
   w.bf16 = 0;
   w.gj = 0;
+  w.rb_log = rb_log;
   w.adj_live = 1;
   w.midq = reinterpret_cast<int32_t*>(base + b->L.midq);
 

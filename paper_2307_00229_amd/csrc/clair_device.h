@@ -187,7 +187,7 @@ struct Work {
   int64_t* chunk_nzglob;  // [nchunks] first R entry of each chunk, batch-wide
   int32_t* chunk_mat;     // [nchunks]
   int2* chunk_bins;       // [nchunks] rows of the chunk in bin A (x) and bin B (y)
-  int32_t* row_block_chunk;  // [n_total / 256 + 2] chunk holding global row 256 b
+  int32_t* row_block_chunk;  // [(n_total >> rb_log) + 2] chunk holding global row b << rb_log
   int32_t* clocal;        // [n_total] chunk-local C-points (negative while unsized)
   int32_t* lnz;           // [n_total] chunk-local prefix of |N(i)|+1
   int32_t* chead;         // [n_total] projection lists: the last R entry (batch-wide number) of each F-column, -1 = none
@@ -218,7 +218,7 @@ struct Work {
   int32_t* fadj;          // [n_total * adj_w]
   int32_t bf16;           // 1: the workgroup solver's trailing updates take bfloat16 inputs
   int32_t gj;             // 1: k_rows_gj runs before k_rows_wg
-  int32_t pad2;
+  int32_t rb_log;         // rows per entry of row_block_chunk, as a power of two
   int32_t adj_live;       // 1: the compact adjacency was built from this call's values (0 in a plan's execute)
   int32_t* midq;          // [nchunks] chunks k_count left unfinished
 };

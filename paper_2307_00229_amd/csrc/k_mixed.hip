@@ -909,7 +909,7 @@ __global__ __launch_bounds__(1024) void k_scan(Work w) {
         w.chunk_rbase[c] = (int32_t)rr;
         w.chunk_nzglob[c] = zz;
         // row blocks whose first row lies in this chunk
-        for (long long b = (rr + (1 << kRowBlockLog) - 1) >> kRowBlockLog; (b << kRowBlockLog) < rr + ncs[k]; ++b)
+        for (long long b = (rr + (1 << w.rb_log) - 1) >> w.rb_log; (b << w.rb_log) < rr + ncs[k]; ++b)
           w.row_block_chunk[b] = c;
       }
       rr += ncs[k];
@@ -1036,7 +1036,7 @@ __global__ __launch_bounds__(NT) void k_rows8(Work w) {
   const int tid = threadIdx.x;
   const int lane = tid & 63;
   const int total = w.cnt->total_rows;
-  const RowBlocks rbk(total, 4 * NT);
+  const RowBlocks rbk(total, (total >= 4 * NT * (int)gridDim.x ? 4 : 1) * NT);
   int r0, r1;
   if (!rbk.block(0, &r0, &r1)) return;
   RefineMax rmx;

@@ -122,7 +122,9 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(3))) void k_
   QuadBuf& B = qbuf[qd];
   if (w.cnt->nA == 0) return;
   const int total = w.cnt->total_rows;
-  const RowBlocks rbk(total, 4 * NQ);
+  // runs of four rows a quad where there are plenty (the row ahead is loaded
+  // within a run), of one on small batches, so that more workgroups have some
+  const RowBlocks rbk(total, (total >= 4 * NQ * (int)gridDim.x ? 4 : 1) * NQ);
   int r0, r1;
   if (!rbk.block(0, &r0, &r1)) return;
   RefineMax rmx;

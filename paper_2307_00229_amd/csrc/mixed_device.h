@@ -12,23 +12,18 @@ namespace clair {
 
 namespace {
 
-// chunk index of global row g: binary search in chunk_rbase[0..nch]
-__device__ __forceinline__ int row_chunk(const int32_t* rbase, int nch, int g) {
-  int lo = 0, hi = nch - 1;
+// chunk index of global row g (0 <= g < total rows): between the chunks that
+// hold the first rows of g's block of rows and of the next one, by bisection
+// (one chunk where chunks are large; a few small ones otherwise)
+__device__ __forceinline__ int row_chunk_fast(const Work& w, int g) {
+  const int b = g >> w.rb_log;
+  int lo = w.row_block_chunk[b];
+  int hi = (int64_t)(b + 1) << w.rb_log < w.cnt->total_rows ? w.row_block_chunk[b + 1] : w.nchunks - 1;
   while (lo < hi) {
-    int mid = (lo + hi + 1) >> 1;
-    if (rbase[mid] <= g) lo = mid; else hi = mid - 1;
+    const int mid = (lo + hi + 1) >> 1;
+    if (w.chunk_rbase[mid] <= g) lo = mid; else hi = mid - 1;
   }
   return lo;
-}
-
-// chunk index of global row g (0 <= g < total rows): the chunk holding the
-// first row of g's block of kRowBlock rows, then a short forward walk
-constexpr int kRowBlockLog = 8;
-__device__ __forceinline__ int row_chunk_fast(const Work& w, int g) {
-  int c = w.row_block_chunk[g >> kRowBlockLog];
-  while (w.chunk_rbase[c + 1] <= g) ++c;
-  return c;
 }
 
 struct RowInfo {
