@@ -182,7 +182,6 @@ struct clair_ctx {
   size_t timing_used = 0;
   // plain-form scratch
   DevBuf plain_ws;
-  DevBuf plain_k;
   // transpose and P-side buffers: A^T, the restriction built on it, scratch
   DevBuf t_rp, t_ci, t_va, q_rp, q_ci, q_va, t_scratch;
   // sparse products: row pointers of a product, the intermediate A P
@@ -821,9 +820,6 @@ int run_plain_one(clair_ctx* c, const clair_csr_t& A, const int8_t* cf, const do
     return CLAIR_OK;
   }
   const int smax = std::max(1, hflags[2]);
-  const size_t kb = (size_t)n_c * ((size_t)smax * smax + smax) * sizeof(double);
-  if (c->plain_k.ensure(std::max<size_t>(kb, 64)) != hipSuccess) return CLAIR_ERR_NOMEM;
-  p.kbuf = static_cast<double*>(c->plain_k.p);
   HIPCHK(plain_solve(p, n_c, smax, s));
   if (B) {
     HIPCHK(hipMemsetAsync(p.dsum, 0, sizeof(double) * (n + 1), s));
@@ -914,7 +910,6 @@ void clair_ctx_destroy(clair_ctx_t* c) {
   c->scratch.release();
   c->links.release();
   c->plain_ws.release();
-  c->plain_k.release();
   c->stage.release();
   c->readback.release();
   if (c->upload_done) (void)hipEventDestroy(c->upload_done);

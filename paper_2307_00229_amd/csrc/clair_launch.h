@@ -94,8 +94,9 @@ hipError_t launch_project_k(int n, int n_rows, const int32_t* rp, const int32_t*
 // C-point of row q; work arrays: diag, d, sj (n), cnt (n, zeroed), u and erow
 // (nnz), *bad_row (INT32_MAX beforehand), *uncovered (zeroed).  ilu: ILU(0)
 // of every block instead of its diagonal; gmres: `krylov` GMRES steps on
-// every local system; fac holds the blocks (factors for ILU(0)), smax^2 * n_c
-// doubles (smax >= the largest block, <= 64), interleaved over rows; gw the
+// every local system; fac holds the factors for ILU(0), row by row, or the
+// blocks, interleaved over rows: smax^2 * n_c doubles (smax >= the largest
+// block, <= 64); gw the
 // GMRES work, ((krylov + 1) (smax + krylov + 3)) * n_c doubles.
 struct DiagWork {
   int ilu, gmres, krylov;
@@ -166,7 +167,6 @@ struct PlainWork {
   int32_t* clist;     // [n]   C-points in ascending order
   int32_t* sizes;     // [n+1] |N(i)| then exclusive scan of |N(i)|+1
   int32_t* scan_tmp;  // [n/256 + 2]
-  double* kbuf;       // [n_c * (smax * smax + smax)]
   double* dsum;       // [n]
   double* rsum;       // [n]
   int32_t* flags;     // [8]: status, first_bad, max_block, ...

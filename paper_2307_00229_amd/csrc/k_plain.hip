@@ -1,9 +1,9 @@
 // k_plain.hip -- the plain FP64 per-row form of the restriction setup.
 //
 // The straightforward GPU formulation, kept as the baseline the mixed,
-// batched path is measured against: one matrix at a time, one thread per
-// C-row, one kernel per stage, FP64 everywhere, local blocks in global
-// scratch, Gaussian elimination with partial pivoting.  Stages:
+// batched path is measured against: one matrix at a time, sixteen lanes per
+// C-row, one kernel per stage, FP64 everywhere, local blocks in LDS, Gaussian
+// elimination with partial pivoting.  Stages:
 //   C-point count per block -> scan -> C list -> |N(i)| per row -> scan ->
 //   column indices -> gather + solve -> projection sums -> projection.
 #include <hip/hip_runtime.h>
@@ -11,13 +11,15 @@
 
 #include "clair_device.h"
 #include "clair_launch.h"
+#include "lds_block.h"
+#include "search_device.h"
 
 namespace clair {
 
 namespace {
 
 constexpr int kPT = 256;
-constexpr int kPlainCap = 64;  // neighbourhood capacity of one thread
+constexpr int kPlainCap = 64;  // neighbourhood capacity of a row
 
 enum { PF_STATUS = 0, PF_FIRST_BAD = 1, PF_MAX_BLOCK = 2, PF_UNCOVERED = 3 };
 
@@ -26,52 +28,35 @@ __device__ void pflag(int32_t* flags, int code, int row) {
   atomicMin(&flags[PF_FIRST_BAD], row);
 }
 
-// breadth-first search into a private array; returns |N(i)| (sorted) or -1.
-// With p.literal the pattern of S^{ell-1} T is taken literally: from the
-// second step on C-points may be interior vertices (those reached before the
-// last step wait in the array with the F-points, counting against its
-// capacity, and are dropped at the end), and the second step also expands i
-// itself (T's identity part).
-__device__ int plain_bfs(const PlainWork& p, int i, int* N) {
-  int s = 0, lo = 0, hi = 0;
-  for (int depth = 1; depth <= p.ell; ++depth) {
-    const int start = s;
-    const bool lit = p.literal && depth >= 2;
-    const int ulo = (depth == 1) ? 0 : (lit && depth == 2 ? lo - 1 : lo);
-    const int uhi = (depth == 1) ? 1 : hi;
-    for (int t = ulo; t < uhi; ++t) {
-      const int u = (depth == 1 || t < lo) ? i : N[t];
-      for (int e = p.grp[u]; e < p.grp[u + 1]; ++e) {  // the search graph: A or a strength matrix
-        const int k = p.gci[e];
-        if (k == u || k == i || (unsigned)k >= (unsigned)p.n || p.gva[e] == 0.0) continue;
-        if (p.cf[k] != 0 && !(lit && depth < p.ell)) continue;  // a C-point is kept only to be expanded
-        if (p.theta != 0.0 && !(fabs(p.gva[e]) >= p.theta * p.cmax[k])) continue;  // strength of A^T
-        bool seen = false;
-        for (int q = 0; q < s && !seen; ++q) seen = (N[q] == k);
-        if (seen) continue;
-        if (s == kPlainCap) return -1;
-        N[s++] = k;
-      }
-    }
-    lo = start;
-    hi = s;
-    // literal: the second step also expands i itself (T's identity part), so
-    // an empty first level does not end the search
-    if (lo == hi && !(p.literal && depth == 1)) break;
-  }
-  if (p.literal) {  // C-points were interior vertices only
-    int m = 0;
-    for (int a = 0; a < s; ++a)
-      if (p.cf[N[a]] == 0) N[m++] = N[a];
-    s = m;
-  }
-  for (int a = 1; a < s; ++a) {  // insertion sort
-    const int v = N[a];
-    int b = a - 1;
-    while (b >= 0 && N[b] > v) { N[b + 1] = N[b]; --b; }
-    N[b + 1] = v;
-  }
-  return s;
+// The search of a row by sixteen lanes (group_search), up to kPlainCap points
+// (C-points walked through in the literal reading included).  A thread per row
+// with its points in a private array took 28 us a pass on 16,641 rows, this
+// 12 (sizes) and 8 (fill).
+constexpr int kPG = 16;
+typedef SearchBuf<kPlainCap, 2 * kPlainCap> PlainBuf;
+
+__device__ __forceinline__ GDesc plain_desc(const PlainWork& p) {
+  GDesc d{};
+  d.n = p.n;
+  d.ell = p.ell;
+  d.theta = p.theta;
+  d.literal = p.literal;
+  d.cf = to_global(p.cf);
+  d.cmax = to_global((const double*)p.cmax);
+  d.grp = to_global(p.grp);
+  d.gci = to_global(p.gci);
+  d.gva = to_global(p.gva);
+  d.agg_rp = nullptr;
+  d.fadj = nullptr;
+  return d;
+}
+
+// points listed (gaps, INT32_MAX, where C-points were dropped) into *n; returns
+// |N(i)| or -1
+__device__ __forceinline__ int plain_search(const GDesc& d, int i, PlainBuf& b, int lane, int* n) {
+  *n = group_search<kPG>(b, d, i, 0, lane);
+  if (*n < 0) return -1;
+  return d.literal != 0 && d.ell >= 3 ? drop_c_points<kPG>(b, d, *n, lane) : *n;
 }
 
 // cmax[v] = max over w != v of |a_wv| (bit patterns of non-negative doubles
@@ -144,26 +129,32 @@ __global__ void k_p_clist(PlainWork p) {
   if (isc) p.clist[p.blk_cnt[blockIdx.x] + sh[threadIdx.x] - 1] = j;
 }
 
-__global__ void k_p_sizes(PlainWork p, int n_c) {
-  const int r = blockIdx.x * blockDim.x + threadIdx.x;
-  int s = 0;
-  if (r < n_c) {
-    int N[kPlainCap];
-    const int i = p.clist[r];
-    s = plain_bfs(p, i, N);
-    if (s < 0) {
-      pflag(p.flags, ST_UNSUPPORTED, i);
-      s = 0;
-    }
-    p.sizes[r] = s + 1;
-  }
-  // largest block: reduced over the workgroup, one atomic per workgroup
+__global__ __launch_bounds__(kPT) void k_p_sizes(PlainWork p, int n_c) {
+  __shared__ PlainBuf sb[kPT / kPG];
   __shared__ int smax;
+  const int lane = threadIdx.x % kPG, grp = threadIdx.x / kPG;
   if (threadIdx.x == 0) smax = 0;
   __syncthreads();
-  atomicMax(&smax, s);
+  const int r = blockIdx.x * (kPT / kPG) + grp;
+  if (r < n_c) {
+    const GDesc d = plain_desc(p);
+    const int i = p.clist[r];
+    int n;
+    int s = plain_search(d, i, sb[grp], lane, &n);
+    if (lane == 0) {
+      if (s < 0) {
+        pflag(p.flags, ST_UNSUPPORTED, i);
+        s = 0;
+      }
+      p.sizes[r] = s + 1;
+      atomicMax(&smax, s);
+    }
+  }
+  // largest block: one atomic per workgroup, when it grows
   __syncthreads();
-  if (threadIdx.x == 0) atomicMax(&p.flags[PF_MAX_BLOCK], smax);
+  if (threadIdx.x == 0 &&
+      smax > __hip_atomic_load(&p.flags[PF_MAX_BLOCK], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT))
+    atomicMax(&p.flags[PF_MAX_BLOCK], smax);
 }
 
 // three-phase scan of sizes[0..n) into R.row_ptr
@@ -195,100 +186,110 @@ __global__ void k_p_apply(const int32_t* a, int n, const int32_t* sums, int nblk
   if (blockIdx.x == 0 && threadIdx.x == 0) out[n] = sums[nblk];
 }
 
-__global__ void k_p_fill(PlainWork p, int n_c) {
-  const int r = blockIdx.x * blockDim.x + threadIdx.x;
+__global__ __launch_bounds__(kPT) void k_p_fill(PlainWork p, int n_c) {
+  __shared__ PlainBuf sb[kPT / kPG];
+  const int lane = threadIdx.x % kPG, grp = threadIdx.x / kPG;
+  const int r = blockIdx.x * (kPT / kPG) + grp;
   if (r >= n_c) return;
-  int N[kPlainCap];
+  const GDesc d = plain_desc(p);
   const int i = p.clist[r];
-  const int s = plain_bfs(p, i, N);
-  if (s < 0 || s + 1 != p.Rrp[r + 1] - p.Rrp[r]) return;
-  int pos = p.Rrp[r];
-  bool ins = false;
-  for (int q = 0; q < s; ++q) {
-    if (!ins && i < N[q]) { p.Rci[pos++] = i; ins = true; }
-    p.Rci[pos++] = N[q];
+  int n;
+  const int s = plain_search(d, i, sb[grp], lane, &n);
+  const int pos = p.Rrp[r];
+  if (s < 0 || s + 1 != p.Rrp[r + 1] - pos) return;
+  for (int q = lane; q < n; q += kPG) {
+    const int v = sb[grp].list[q];
+    if (v != INT32_MAX) p.Rci[pos + search_rank(sb[grp], n, v) + (v > i ? 1 : 0)] = v;
   }
-  if (!ins) p.Rci[pos] = i;
+  if (lane == 0) p.Rci[pos + search_rank(sb[grp], n, i)] = i;
 }
 
-// thread per row: FP64 block in global scratch, GEPP, solve
+// sixteen lanes per row: FP64 block in LDS, elimination with partial pivoting
+// (the largest magnitude, the first of equal ones), each lane taking the rows
+// below the pivot in turn
 __global__ void k_p_solve(PlainWork p, int n_c, int smax) {
-  const int r = blockIdx.x * blockDim.x + threadIdx.x;
+  extern __shared__ double s_base[];
+  const int lane = threadIdx.x % kLB, grp = threadIdx.x / kLB;
+  const int r = blockIdx.x * (blockDim.x / kLB) + grp;
   if (r >= n_c) return;
   const int i = p.clist[r];
-  const int e0 = p.Rrp[r], e1 = p.Rrp[r + 1];
-  const int s = e1 - e0 - 1;
-  double* K = p.kbuf + (int64_t)r * ((int64_t)smax * smax + smax);  // s x s, row stride s
-  double* f = K + (int64_t)s * s;                                     // s entries
+  const int e0 = p.Rrp[r], s = p.Rrp[r + 1] - e0 - 1;
   if (s <= 0) {
-    for (int e = e0; e < e1; ++e) p.Rva[e] = 1.0;
+    if (s == 0 && lane == 0) p.Rva[e0] = 1.0;
     return;
   }
-  const int* Rc = p.Rci + e0;
-  // position of fine column k in the row's F-list (the row holds i as well)
-  auto fpos = [&](int k) -> int {
-    int lo = 0, hi = s + 1;
-    while (lo < hi) {
-      const int mid = (lo + hi) >> 1;
-      if (Rc[mid] < k) lo = mid + 1; else hi = mid;
-    }
-    if (lo > s || Rc[lo] != k || k == i) return -1;
-    return (k > i) ? lo - 1 : lo;
-  };
-  for (int t = 0; t < s * s; ++t) K[t] = 0.0;
-  for (int q = 0; q < s; ++q) f[q] = 0.0;
-  int p_ = 0;
-  for (int e = 0; e <= s; ++e) {
-    const int u = Rc[e];
-    if (u == i) continue;
-    for (int a = p.rp[u]; a < p.rp[u + 1]; ++a) {
-      const int q = fpos(p.ci[a]);
-      if (q >= 0) K[q * s + p_] = p.va[a];
-    }
-    ++p_;
-  }
-  for (int a = p.rp[i]; a < p.rp[i + 1]; ++a) {
-    const int q = fpos(p.ci[a]);
-    if (q >= 0) f[q] = -p.va[a];
+  const LdsBlock b = lds_block(s_base, grp, smax);
+  double* K = b.K;
+  double* f = b.f;
+  const int ld = b.ld;
+  for (int t = lane; t < s; t += kLB) f[t] = 0.0;
+  lds_gather(b, s, i, p.Rci, e0, p.rp, p.ci, p.va, lane);
+  for (int e = p.rp[i] + lane; e < p.rp[i + 1]; e += kLB) {
+    const int q = find_sorted(b.nb, s, p.ci[e]);
+    if (q >= 0) f[q] = -p.va[e];
   }
   double amax = 0.0;
-  for (int t = 0; t < s * s; ++t) amax = fmax(amax, fabs(K[t]));
+  for (int t = lane; t < s * ld; t += kLB)
+    if (t % ld < s) amax = fmax(amax, fabs(K[t]));
+  amax = fmax(amax, gpartd<1>(amax));
+  amax = fmax(amax, gpartd<2>(amax));
+  amax = fmax(amax, gpartd<4>(amax));
+  amax = fmax(amax, gpartd<8>(amax));
   const double tiny = 1e-14 * amax;
+  wave_sync();
   bool sing = false;
-  for (int k = 0; k < s && !sing; ++k) {
+  for (int k = 0; k < s; ++k) {
+    const double dk = fabs(K[k * ld + k]);
+    double best = -1.0;
     int piv = k;
-    double best = fabs(K[k * s + k]);
-    for (int q = k + 1; q < s; ++q) {
-      const double v = fabs(K[q * s + k]);
+    for (int q = k + lane; q < s; q += kLB) {
+      const double v = fabs(K[q * ld + k]);
       if (v > best) { best = v; piv = q; }
     }
-    if (!(best > tiny)) { sing = true; break; }
+#define CLAIR_PIV(STEP)                                                        \
+  {                                                                            \
+    const double ob = gpartd<STEP>(best);                                      \
+    const int op = gpart<STEP>(piv);                                           \
+    if (ob > best || (ob == best && op < piv)) { best = ob; piv = op; }        \
+  }
+    CLAIR_PIV(1) CLAIR_PIV(2) CLAIR_PIV(4) CLAIR_PIV(8)
+#undef CLAIR_PIV
+    // (a NaN on the diagonal is no pivot and hides the others, as when the
+    // column is searched from the diagonal down)
+    if (!(dk == dk) || !(best > tiny)) { sing = true; break; }
     if (piv != k) {
-      for (int c = 0; c < s; ++c) { const double t = K[k * s + c]; K[k * s + c] = K[piv * s + c]; K[piv * s + c] = t; }
-      const double t = f[k]; f[k] = f[piv]; f[piv] = t;
+      for (int c = lane; c < s; c += kLB) {
+        const double t = K[k * ld + c];
+        K[k * ld + c] = K[piv * ld + c];
+        K[piv * ld + c] = t;
+      }
+      if (lane == 0) { const double t = f[k]; f[k] = f[piv]; f[piv] = t; }
+      wave_sync();
     }
-    const double pv = K[k * s + k];
-    for (int q = k + 1; q < s; ++q) {
-      const double l = K[q * s + k] / pv;
-      for (int c = k + 1; c < s; ++c) K[q * s + c] -= l * K[k * s + c];
-      f[q] -= l * f[k];
+    const double pv = K[k * ld + k];
+    const double fk = f[k];
+    for (int q = k + 1 + lane; q < s; q += kLB) {
+      const double l = K[q * ld + k] / pv;
+      for (int c = k + 1; c < s; ++c) K[q * ld + c] -= l * K[k * ld + c];
+      f[q] -= l * fk;
     }
+    wave_sync();
   }
   if (sing) {
-    pflag(p.flags, ST_SINGULAR, i);
-    for (int q = 0; q < s; ++q) f[q] = 0.0;
+    if (lane == 0) pflag(p.flags, ST_SINGULAR, i);
+    for (int q = lane; q < s; q += kLB) f[q] = 0.0;
   } else {
     for (int k = s - 1; k >= 0; --k) {
-      double acc = f[k];
-      for (int c = k + 1; c < s; ++c) acc -= K[k * s + c] * f[c];
-      f[k] = acc / K[k * s + k];
+      const double x = f[k] / K[k * ld + k];
+      wave_sync();
+      if (lane == 0) f[k] = x;
+      for (int q = lane; q < k; q += kLB) f[q] -= K[q * ld + k] * x;
+      wave_sync();
     }
   }
-  int q = 0;
-  for (int e = 0; e <= s; ++e) {
-    if (Rc[e] == i) p.Rva[e0 + e] = 1.0;
-    else p.Rva[e0 + e] = f[q++];
-  }
+  wave_sync();
+  for (int q = lane; q < s; q += kLB) p.Rva[e0 + q + (b.nb[q] > i ? 1 : 0)] = f[q];
+  if (lane == 0) p.Rva[e0 + lower_bound_i32(b.nb, s, i)] = 1.0;
 }
 
 __global__ void k_p_colsum(PlainWork p, int n_c) {
@@ -350,7 +351,7 @@ hipError_t plain_clist(const PlainWork& p, hipStream_t s) {
   return hipGetLastError();
 }
 hipError_t plain_sizes(const PlainWork& p, int n_c, hipStream_t s) {
-  if (n_c > 0) hipLaunchKernelGGL(k_p_sizes, dim3(nblk(n_c)), dim3(kPT), 0, s, p, n_c);
+  if (n_c > 0) hipLaunchKernelGGL(k_p_sizes, dim3((n_c + kPT / kPG - 1) / (kPT / kPG)), dim3(kPT), 0, s, p, n_c);
   return hipGetLastError();
 }
 hipError_t plain_scan(const PlainWork& p, int n_c, hipStream_t s) {
@@ -361,11 +362,15 @@ hipError_t plain_scan(const PlainWork& p, int n_c, hipStream_t s) {
   return hipGetLastError();
 }
 hipError_t plain_fill(const PlainWork& p, int n_c, hipStream_t s) {
-  if (n_c > 0) hipLaunchKernelGGL(k_p_fill, dim3(nblk(n_c)), dim3(kPT), 0, s, p, n_c);
+  if (n_c > 0) hipLaunchKernelGGL(k_p_fill, dim3((n_c + kPT / kPG - 1) / (kPT / kPG)), dim3(kPT), 0, s, p, n_c);
   return hipGetLastError();
 }
 hipError_t plain_solve(const PlainWork& p, int n_c, int smax, hipStream_t s) {
-  if (n_c > 0) hipLaunchKernelGGL(k_p_solve, dim3(nblk(n_c)), dim3(kPT), 0, s, p, n_c, smax);
+  if (n_c > 0) {
+    const int R = lds_rows(smax);
+    hipLaunchKernelGGL(k_p_solve, dim3((n_c + R - 1) / R), dim3(kLB * R), sizeof(double) * R * lds_row_doubles(smax), s,
+                       p, n_c, smax);
+  }
   return hipGetLastError();
 }
 hipError_t plain_colsum(const PlainWork& p, int n_c, hipStream_t s) {
