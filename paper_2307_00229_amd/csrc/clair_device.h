@@ -219,6 +219,8 @@ struct Work {
   int32_t bf16;           // 1: the workgroup solver's trailing updates take bfloat16 inputs
   int32_t gj;             // 1: k_rows_gj runs before k_rows_wg
   int32_t rb_log;         // rows per entry of row_block_chunk, as a power of two
+  int32_t skip;           // 1: k_count_mid / _wide not launched, 2: k_count_big not launched (k_scan stops the call
+                          // when one of them was needed)
   int32_t adj_live;       // 1: the compact adjacency was built from this call's values (0 in a plan's execute)
   int32_t* midq;          // [nchunks] chunks k_count left unfinished
 };

@@ -37,11 +37,31 @@ hipError_t launch_rows_wg(const Work& w, int blocks, hipStream_t s);
 // the constraint projection over the column lists (one workgroup per chunk)
 hipError_t launch_project(const Work& w, hipStream_t s);
 
+// up to kCollectMax runs of 0..64 int32 each, one after another, to dst (pinned
+// host memory)
+constexpr int kCollectMax = 4;
+struct CollectArgs {
+  const int32_t* src[kCollectMax];
+  int n[kCollectMax];
+  int32_t* dst;
+};
+hipError_t launch_collect(const CollectArgs& a, hipStream_t s);
+hipError_t launch_copy_words(const int32_t* src, int32_t* dst, int n, hipStream_t s);
+struct SetArgs {
+  int32_t v[8];
+  int n;
+};
+hipError_t launch_set_ints(int32_t* dst, const SetArgs& a, hipStream_t s);
+// dst = src, unless *flag is set (flag may be null)
+hipError_t launch_copy_unless(const int32_t* flag, const double* src, double* dst, int n, hipStream_t s);
+
 // CSR transpose of an m x ncol matrix: trp[ncol+1], tci/tva[nnz]; scratch of
-// transpose_scratch_ints(ncol) ints (column cursors, a flag set to 1 for an
-// index outside [0, ncol), block totals)
+// transpose_scratch_ints(ncol) ints (column counts, a flag set to 1 for an
+// index outside [0, ncol) or row pointers that do not run from 0 to nnz, block
+// totals).  With the flag set the result is still a CSR array that can be
+// walked (skipped entries are left out; none at all for bad row pointers).
 size_t transpose_scratch_ints(int ncol);
-hipError_t launch_transpose(int m, int ncol, const int32_t* rp, const int32_t* ci, const double* va, int32_t* trp,
+hipError_t launch_transpose(int m, int ncol, int64_t nnz, const int32_t* rp, const int32_t* ci, const double* va, int32_t* trp,
                             int32_t* tci, double* tva, int32_t* scratch, int cus, hipStream_t s);
 
 // out[0..n) = exclusive prefix of cnt, out[n] = total; sums: scan_scratch_ints(n)
@@ -52,13 +72,13 @@ hipError_t launch_exclusive_scan(const int32_t* cnt, int n, int32_t* out, int32_
 // Symbolic: cnt[i] = distinct columns of row i; flags (4 ints, zeroed by the
 // caller): [0] = 1 for a row above kSpgemmMaxRow columns, [1] = 1 for an index
 // out of range, [2] the largest product count of a row.  It synchronises the
-// stream once (to size the hash tables) and returns the table size in
+// stream once (to size the hash tables; pinned: a word of pinned host memory) and returns the table size in
 // *lg_out, which the numeric pass takes.  Numeric: sorted rows at crp[i]
 // (crp from the scan of cnt).
 constexpr int kSpgemmMaxRow = 1536;
 hipError_t launch_spgemm_count(int m, const int32_t* xrp, const int32_t* xci, int k, const int32_t* yrp,
-                               const int32_t* yci, int ny, int32_t* cnt, int32_t* flags, int* lg_out, int cus,
-                               hipStream_t s);
+                               const int32_t* yci, int ny, int32_t* cnt, int32_t* flags, int* lg_out, int32_t* pinned,
+                               int cus, hipStream_t s);
 hipError_t launch_spgemm_fill(int m, const int32_t* xrp, const int32_t* xci, const double* xva, const int32_t* yrp,
                               const int32_t* yci, const double* yva, const int32_t* crp, int32_t* cci, double* cva,
                               int lg, int cus, hipStream_t s);
@@ -85,7 +105,7 @@ struct ProjectScratch {
   int32_t *flag, *pos, *scan_sums, *rowc;
   double* lam;
 };
-hipError_t launch_project_k(int n, int n_rows, const int32_t* rp, const int32_t* ci, double* va, const int8_t* cf,
+hipError_t launch_project_k(int n, int n_rows, int64_t nnz, const int32_t* rp, const int32_t* ci, double* va, const int8_t* cf,
                             const double* B, int k, double rcond, const ProjectScratch& w,
                             unsigned long long* uncovered, int cus, hipStream_t s);
 

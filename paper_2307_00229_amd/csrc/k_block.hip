@@ -318,9 +318,8 @@ __global__ __launch_bounds__(kGT) __attribute__((amdgpu_waves_per_eu(4))) void k
 
 // persistent grid over the queue, as many workgroups as fit on the device
 hipError_t launch_rows_gj(const Work& w, int cus, hipStream_t s) {
-  int per = 0;
-  hipError_t e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per, k_rows_gj, kGT, 0);
-  if (e != hipSuccess) return e;
+  const int per = resident_blocks<k_rows_gj, kGT>();
+  if (per < 0) return hipErrorInvalidValue;
   hipLaunchKernelGGL(k_rows_gj, dim3(std::max(1, per) * cus), dim3(kGT), 0, s, w);
   return hipGetLastError();
 }

@@ -294,7 +294,7 @@ void launch_k(int n, int n_rows, const int32_t* rp, const int32_t* ci, double* v
 
 }  // namespace
 
-hipError_t launch_project_k(int n, int n_rows, const int32_t* rp, const int32_t* ci, double* va, const int8_t* cf,
+hipError_t launch_project_k(int n, int n_rows, int64_t nnz, const int32_t* rp, const int32_t* ci, double* va, const int8_t* cf,
                             const double* B, int k, double rcond, const ProjectScratch& w,
                             unsigned long long* uncovered, int cus, hipStream_t s) {
   if (n > 0 || n_rows > 0)
@@ -307,7 +307,7 @@ hipError_t launch_project_k(int n, int n_rows, const int32_t* rp, const int32_t*
     if (e != hipSuccess) return e;
     hipLaunchKernelGGL(k_pk_rowc, dim3(kgrid(n, cus)), dim3(kKT), 0, s, n, n_rows, cf, w.pos, w.rowc);
   }
-  e = launch_transpose(n_rows, n, rp, ci, va, w.trp, w.tci, w.tva, w.t_scratch, cus, s);
+  e = launch_transpose(n_rows, n, nnz, rp, ci, va, w.trp, w.tci, w.tva, w.t_scratch, cus, s);
   if (e != hipSuccess) return e;
   switch (k) {
     case 1: launch_k<1>(n, n_rows, rp, ci, va, cf, B, rcond, w, uncovered, cus, s); break;

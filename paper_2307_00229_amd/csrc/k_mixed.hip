@@ -921,6 +921,9 @@ __global__ __launch_bounds__(1024) void k_scan(Work w) {
     nb += tb;
   }
   const long long rows_total = carry_r, nnz_total = carry_z;
+  // a pass left out on a hint that does not hold (the host runs again): no
+  // matrix is live, so nothing uses the unfinished chunks' offsets
+  const bool stop = ((w.skip & 1) && w.cnt->nmid > 0) || ((w.skip & 2) && w.cnt->nbig > 0);
   __syncthreads();
   for (int m = tid; m < w.nmat; m += 1024) {
     const GDesc d = gview(w.desc[m]);
@@ -939,7 +942,7 @@ __global__ __launch_bounds__(1024) void k_scan(Work w) {
     if (st->status != ST_INVALID) {
       const bool fits = d.Rrp && d.Rci && d.Rva && (int64_t)n_c + 1 <= d.row_cap && nnz <= d.nnz_cap &&
                         nnz <= 0x7fffffffLL;
-      if (!fits) {
+      if (!fits || stop) {
         st->status = ST_CAPACITY;
       } else {
         d.Rrp[n_c] = (int32_t)nnz;

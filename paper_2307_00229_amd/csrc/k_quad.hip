@@ -487,9 +487,8 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(3))) void k_
 hipError_t launch_quad8(const Work& w, int wg_threads, int cus, hipStream_t s) {
 #define CLAIR_Q8(NTT)                                                                       \
   if (wg_threads == NTT) {                                                                  \
-    int per = 0;                                                                            \
-    hipError_t e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per, k_quad8<NTT>, NTT, 0); \
-    if (e != hipSuccess) return e;                                                          \
+    const int per = resident_blocks<k_quad8<NTT>, NTT>();                                   \
+    if (per < 0) return hipErrorInvalidValue;                                               \
     const int blocks = (std::max(1, per) * cus + 7) / 8 * 8;                               \
     hipLaunchKernelGGL((k_quad8<NTT>), dim3(blocks), dim3(NTT), 0, s, w);                   \
     return hipGetLastError();                                                               \

@@ -300,17 +300,18 @@ void launch_fill_lg(int m, const int32_t* xrp, const int32_t* xci, const double*
 }  // namespace
 
 hipError_t launch_spgemm_count(int m, const int32_t* xrp, const int32_t* xci, int k, const int32_t* yrp,
-                               const int32_t* yci, int ny, int32_t* cnt, int32_t* flags, int* lg_out, int cus,
-                               hipStream_t s) {
+                               const int32_t* yci, int ny, int32_t* cnt, int32_t* flags, int* lg_out, int32_t* pinned,
+                               int cus, hipStream_t s) {
   *lg_out = 6;
   if (m <= 0) return hipSuccess;
   // the table size: twice the largest product count, as a power of two
   hipLaunchKernelGGL(k_sg_maxprod, dim3(std::max(1, std::min((m + 255) / 256, cus * 2))), dim3(256), 0, s, m, xrp,
                      xci, k, yrp, flags + 2);
-  int32_t maxprod = 0;
-  hipError_t e = hipMemcpyAsync(&maxprod, flags + 2, sizeof(int32_t), hipMemcpyDeviceToHost, s);
+  CollectArgs ca{{flags + 2, nullptr, nullptr, nullptr}, {1, 0, 0, 0}, pinned};
+  hipError_t e = launch_collect(ca, s);
   if (e == hipSuccess) e = hipStreamSynchronize(s);
   if (e != hipSuccess) return e;
+  const int32_t maxprod = pinned[0];
   int lg = 6;
   while (lg < kLgH && (1ll << lg) < 2ll * maxprod) ++lg;
   *lg_out = lg;

@@ -453,9 +453,8 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(T <= 5 ? 3 :
 hipError_t launch_tile(const Work& w, int which, int sm, int cus, hipStream_t s) {
 #define CLAIR_TILE(TT)                                                                     \
   if (sm <= 4 * TT) {                                                                      \
-    int per = 0;                                                                           \
-    hipError_t e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per, k_tile<TT>, 64, 0);  \
-    if (e != hipSuccess) return e;                                                         \
+    const int per = resident_blocks<k_tile<TT>, 64>();                                     \
+    if (per < 0) return hipErrorInvalidValue;                                              \
     const int blocks = (std::max(1, per) * cus + 7) / 8 * 8;                              \
     hipLaunchKernelGGL((k_tile<TT>), dim3(blocks), dim3(64), 0, s, w, which);              \
     return hipGetLastError();                                                              \

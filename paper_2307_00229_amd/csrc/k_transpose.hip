@@ -38,8 +38,12 @@ constexpr int kTS = 8;  // output rows of up to kTS entries are sorted in regist
 
 // cnt[j] = entries of column j (indices outside [0, ncol) are skipped and
 // flagged in *bad)
-__global__ __launch_bounds__(kTT) void k_t_count(int m, int ncol, const int32_t* __restrict__ rp,
+__global__ __launch_bounds__(kTT) void k_t_count(int m, int ncol, int64_t nnz, const int32_t* __restrict__ rp,
                                                  const int32_t* __restrict__ ci, int32_t* cnt, int32_t* bad) {
+  if (rp[0] != 0 || rp[m] != nnz) {  // the arrays that follow are sized from nnz: no row is walked
+    if (blockIdx.x == 0 && threadIdx.x == 0) *bad = 1;
+    return;
+  }
   for (int i = blockIdx.x * kTT + threadIdx.x; i < m; i += gridDim.x * kTT) {
     const int e1 = rp[i + 1];
     for (int e = rp[i]; e < e1; e += kTB) {
@@ -99,10 +103,11 @@ __global__ void k_t_scan_none(int32_t* out) { out[0] = 0; }
 
 // scatter: entry (i, j) to out row j at trp[j] + the column's count, counted
 // down (a skipped index was never counted)
-__global__ __launch_bounds__(kTT) void k_t_fill(int m, int ncol, const int32_t* __restrict__ rp,
+__global__ __launch_bounds__(kTT) void k_t_fill(int m, int ncol, int64_t nnz, const int32_t* __restrict__ rp,
                                                 const int32_t* __restrict__ ci, const double* __restrict__ va,
                                                 const int32_t* __restrict__ trp, int32_t* left, int32_t* tci,
                                                 double* tva) {
+  if (rp[0] != 0 || rp[m] != nnz) return;
   for (int i = blockIdx.x * kTT + threadIdx.x; i < m; i += gridDim.x * kTT) {
     const int e1 = rp[i + 1];
     for (int e = rp[i]; e < e1; e += kTB) {
@@ -182,16 +187,17 @@ hipError_t launch_exclusive_scan(const int32_t* cnt, int n, int32_t* out, int32_
   return hipGetLastError();
 }
 
-hipError_t launch_transpose(int m, int ncol, const int32_t* rp, const int32_t* ci, const double* va, int32_t* trp,
-                            int32_t* tci, double* tva, int32_t* scratch, int cus, hipStream_t s) {
+hipError_t launch_transpose(int m, int ncol, int64_t nnz, const int32_t* rp, const int32_t* ci, const double* va,
+                            int32_t* trp, int32_t* tci, double* tva, int32_t* scratch, int cus, hipStream_t s) {
   int32_t* left = scratch;
   int32_t* bad = scratch + ncol;
   int32_t* sums = scratch + ncol + 1;
   hipLaunchKernelGGL(k_t_zero, dim3(grid_for(ncol + 1, cus)), dim3(kTT), 0, s, left, ncol + 1);
-  if (m > 0) hipLaunchKernelGGL(k_t_count, dim3(grid_for(m, cus)), dim3(kTT), 0, s, m, ncol, rp, ci, left, bad);
+  if (m > 0) hipLaunchKernelGGL(k_t_count, dim3(grid_for(m, cus)), dim3(kTT), 0, s, m, ncol, nnz, rp, ci, left, bad);
   hipError_t e = launch_exclusive_scan(left, ncol, trp, sums, cus, s);
   if (e != hipSuccess) return e;
-  if (m > 0) hipLaunchKernelGGL(k_t_fill, dim3(grid_for(m, cus)), dim3(kTT), 0, s, m, ncol, rp, ci, va, trp, left, tci, tva);
+  if (m > 0)
+    hipLaunchKernelGGL(k_t_fill, dim3(grid_for(m, cus)), dim3(kTT), 0, s, m, ncol, nnz, rp, ci, va, trp, left, tci, tva);
   if (ncol > 0) hipLaunchKernelGGL(k_t_sort, dim3(grid_for(ncol, cus)), dim3(kTT), 0, s, ncol, trp, tci, tva);
   return hipGetLastError();
 }

@@ -4,6 +4,8 @@
 #pragma once
 
 #include <hip/hip_runtime.h>
+
+#include <atomic>
 #include <stdint.h>
 
 #include "clair_device.h"
@@ -24,6 +26,19 @@ __device__ __forceinline__ int row_chunk_fast(const Work& w, int g) {
     if (w.chunk_rbase[mid] <= g) lo = mid; else hi = mid - 1;
   }
   return lo;
+}
+
+// workgroups of NT threads of a kernel that fit on a CU at once (a property of
+// the kernel and the architecture, asked for once per kernel: the query costs a
+// few microseconds), -1 on failure
+template <auto F, int NT>
+inline int resident_blocks() {
+  static std::atomic<int> known{0};
+  int per = known.load(std::memory_order_relaxed);
+  if (per > 0) return per;
+  if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per, F, NT, 0) != hipSuccess) return -1;
+  known.store(per, std::memory_order_relaxed);
+  return per;
 }
 
 struct RowInfo {
