@@ -247,15 +247,26 @@ __global__ void k_validate(Work w) {
 // ---------------------------------------------------------------------------
 
 // The compact adjacency of the matrices whose descriptor carries one: the
-// workgroup of logical block b takes 256 * kAdjPP points of chunk
-// b / ceil(chunk / (256 * kAdjPP)) (the chunk's XCD is the one k_count gives
-// it), kAdjPP points per thread with their loads in flight together (two per
-// thread were slower than one: 98 VGPRs instead of 44 halve the wavefronts).
-constexpr int kAdjPP = 1;
+// workgroup of logical block b takes 256 points of chunk b / ceil(chunk / 256)
+// (the chunk's XCD is the one k_count gives it).  The points' entries are
+// consecutive, so the workgroup reads them in tiles of kAdjTile, a thread at a
+// time the entries 256 apart (their loads in flight together), and leaves in
+// LDS the column of each entry that is an edge to an F-point, -1 for the
+// others; then each thread collects its own point's.
+//
+// Bound: the entries' bytes.  With one thread reading its own row, the lanes of
+// a load were 20 and 40 bytes apart and the address unit was the limit
+// (64 five-point matrices of 64^2 to 768^2: 221 us, now 196; 2048^2 nine-point
+// rows: 190, now 141; 128^3 seven-point rows: 65, now 62).  A tile of 256 times
+// five entries: a larger one issues its empty loads (2048: 199, 151 and 63 us;
+// 2560: 234, 159 and 74), a smaller one takes two turns for five-point rows
+// (1024: 211, 147 and 62).
+constexpr int kAdjTile = 1280;
 
 template <int W>
 __global__ __launch_bounds__(256) void k_adj(Work w) {
-  const int per = (w.chunk + 256 * kAdjPP - 1) / (256 * kAdjPP);
+  __shared__ int s_k[kAdjTile];
+  const int per = (w.chunk + 255) / 256;
   const int b = xcd_logical_block();
   const int c = b / per;
   const int m = chunk_matrix(w.desc, w.nmat, c);
@@ -263,69 +274,66 @@ __global__ __launch_bounds__(256) void k_adj(Work w) {
   if (!d.fadj) return;
   const int f0 = (c - d.chunk0) * w.chunk;
   const int f1 = min(f0 + w.chunk, d.n);
-  const int ub = f0 + (b - c * per) * 256 * kAdjPP + (int)threadIdx.x;
-  int u[kAdjPP], e0[kAdjPP], e1[kAdjPP], cnt[kAdjPP];
-  int o[kAdjPP][W];
+  const int u0 = f0 + (b - c * per) * 256;
+  if (u0 >= f1) return;  // uniform
+  const int tid = threadIdx.x;
+  const int u = u0 + tid;
+  int e0 = 0, e1 = 0;
+  if (u < f1) { e0 = d.grp[u]; e1 = d.grp[u + 1]; }
+  const int g0 = d.grp[u0], g1 = d.grp[min(u0 + 256, f1)];
+  int cnt = 0;
+  int o[W];
 #pragma unroll
-  for (int p = 0; p < kAdjPP; ++p) {
-    u[p] = ub + 256 * p;
-    e0[p] = 0;
-    e1[p] = 0;
-    cnt[p] = 0;
-    if (u[p] < f1) { e0[p] = d.grp[u[p]]; e1[p] = d.grp[u[p] + 1]; }
+  for (int q = 0; q < W; ++q) o[q] = -1;
+  for (int t0 = g0; t0 < g1; t0 += kAdjTile) {
+    const int t1 = min(t0 + kAdjTile, g1);
+    constexpr int PT = kAdjTile / 256;
+    int k[PT];
+    double x[PT];
 #pragma unroll
-    for (int q = 0; q < W; ++q) o[p][q] = -1;
-  }
-  for (int e = 0;; e += 8) {
-    bool any = false;
-#pragma unroll
-    for (int p = 0; p < kAdjPP; ++p) any |= e0[p] + e < e1[p] && cnt[p] <= W;
-    if (!any) break;
-    int k[kAdjPP][8];
-    double x[kAdjPP][8];
-#pragma unroll
-    for (int p = 0; p < kAdjPP; ++p) {
-      const bool go = cnt[p] <= W;
-#pragma unroll
-      for (int j = 0; j < 8; ++j) {
-        k[p][j] = u[p];
-        x[p][j] = 0.0;
-        if (go && e0[p] + e + j < e1[p]) { k[p][j] = d.gci[e0[p] + e + j]; x[p][j] = d.gva[e0[p] + e + j]; }
-      }
+    for (int j = 0; j < PT; ++j) {
+      const int e = t0 + tid + 256 * j;
+      k[j] = -1;
+      x[j] = 0.0;
+      if (e < t1) { k[j] = d.gci[e]; x[j] = d.gva[e]; }
     }
-    int8_t c8[kAdjPP][8];
+    int8_t c8[PT];
 #pragma unroll
-    for (int p = 0; p < kAdjPP; ++p)
+    for (int j = 0; j < PT; ++j) c8[j] = ((unsigned)k[j] < (unsigned)d.n) ? d.cf[k[j]] : (int8_t)1;
+    if (t0 != g0) __syncthreads();  // the last tile has been read
 #pragma unroll
-      for (int j = 0; j < 8; ++j)
-        c8[p][j] = ((unsigned)k[p][j] < (unsigned)d.n) ? d.cf[k[p][j]] : (int8_t)1;
+    for (int j = 0; j < PT; ++j) {
+      const bool edge = x[j] != 0.0 && c8[j] == 0 && strong_edge(x[j], k[j], d.theta, d.cmax);
+      s_k[tid + 256 * j] = edge ? k[j] : -1;
+    }
+    __syncthreads();
+    const int ee = min(e1, t1);
+    for (int e = max(e0, t0); e < ee; e += 4) {
+      int kk[4];
 #pragma unroll
-    for (int p = 0; p < kAdjPP; ++p) {
+      for (int j = 0; j < 4; ++j) kk[j] = s_k[min(e + j, ee - 1) - t0];
 #pragma unroll
-      for (int j = 0; j < 8; ++j) {
-        if (k[p][j] != u[p] && x[p][j] != 0.0 && c8[p][j] == 0 && strong_edge(x[p][j], k[p][j], d.theta, d.cmax)) {
+      for (int j = 0; j < 4; ++j) {
+        if (e + j < ee && kk[j] >= 0 && kk[j] != u) {
 #pragma unroll
           for (int q = 0; q < W; ++q)
-            if (q == cnt[p]) o[p][q] = k[p][j];
-          ++cnt[p];
+            if (q == cnt) o[q] = kk[j];
+          ++cnt;
         }
       }
     }
   }
+  if (u >= f1) return;
+  if (cnt > W) o[0] = kAdjOverflow;
+  gptr<adj_v4> dst = (gptr<adj_v4>)(to_global(w.fadj) + (d.fine0 + u) * W);
 #pragma unroll
-  for (int p = 0; p < kAdjPP; ++p) {
-    if (u[p] >= f1) continue;
-    if (cnt[p] > W) o[p][0] = kAdjOverflow;
-    gptr<adj_v4> dst = (gptr<adj_v4>)(to_global(w.fadj) + (d.fine0 + u[p]) * W);
-#pragma unroll
-    for (int q = 0; q < W / 4; ++q) {
-      adj_v4 t;
-      t.x = o[p][4 * q];
-      t.y = o[p][4 * q + 1];
-      t.z = o[p][4 * q + 2];
-      t.w = o[p][4 * q + 3];
-      dst[q] = t;
-    }
+  for (int q = 0; q < W / 4; ++q) {
+    adj_v4 t;
+    t.x = o[4 * q];
+    t.y = o[4 * q + 1];
+    t.z = o[4 * q + 2];
+    t.w = o[4 * q + 3];
+    dst[q] = t;
   }
 }
 
@@ -2082,7 +2090,7 @@ hipError_t launch_validate(const Work& w, int blocks, hipStream_t s) {
 
 hipError_t launch_adj(const Work& w, hipStream_t s) {
   if (w.nchunks == 0 || w.adj_w == 0) return hipSuccess;
-  const int per = (w.chunk + 256 * kAdjPP - 1) / (256 * kAdjPP);
+  const int per = (w.chunk + 255) / 256;
   const dim3 grid((unsigned)w.nchunks * (unsigned)per);
   if (w.adj_w == 4) hipLaunchKernelGGL(k_adj<4>, grid, dim3(256), 0, s, w);
   else if (w.adj_w == 8) hipLaunchKernelGGL(k_adj<8>, grid, dim3(256), 0, s, w);
