@@ -312,6 +312,7 @@ int check_args(int32_t nmat, const clair_csr_t* A, const int8_t* const* cf, cons
 // about 524,000 points on the chunk is the tuning's own.
 int effective_chunk(const clair_ctx* c, int64_t n_total) {
   int chunk = c->chunk;
+  if (c->fixed) return chunk;  // (its scratch is sized for whole chunks)
   while (chunk > 64 && n_total < (int64_t)chunk * 2 * c->cus) chunk /= 2;
   return chunk;
 }
