@@ -652,7 +652,7 @@ int enqueue_symbolic(clair_ctx* c, Batch& b, hipStream_t s, bool validate, bool 
     timing_mark(c, timing, s, "aggregates");
   }
   if (c->theta > 0.0) {
-    HIPCHK(launch_colmax(b.w, b.n_total, occupancy_blocks(c, 4), s));
+    HIPCHK(launch_colmax(b.w, b.n_total, c->cus, s));
     if (capture_check(c->capturing, s, "k_colmax", __LINE__)) return CLAIR_ERR_HIP;
     timing_mark(c, timing, s, "colmax");
   }

@@ -1967,13 +1967,29 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void k
 // for every matrix of the batch (batch-wide fine numbering).  Non-negative
 // doubles order like their bit patterns, so an unsigned 64-bit atomic max
 // takes the maximum.
+//
+// Bound: the rate of atomics in memory (about 65 a ns), so a workgroup gathers
+// the maxima of its own run of points in LDS and sends one atomic for each;
+// only entries that leave the run go to memory one by one.  1001^2 five-point
+// rows: 69 us with an atomic per entry (also with eight entries a thread in
+// flight), now 52 (two rows a thread: 55).
 __global__ void k_colmax_clear(Work w, int64_t n_total) {
   for (int64_t g = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; g < n_total; g += (int64_t)gridDim.x * blockDim.x)
     w.cmax[g] = 0.0;
 }
 
-__global__ void k_colmax(Work w, int64_t n_total) {
-  for (int64_t g = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; g < n_total; g += (int64_t)gridDim.x * blockDim.x) {
+constexpr int kCMT = 1024, kCMRows = 4;  // threads of a workgroup; rows a thread takes, at most
+
+__global__ __launch_bounds__(kCMT) void k_colmax(Work w, int64_t n_total, int rows) {
+  __shared__ unsigned long long s_max[kCMT * kCMRows];
+  const int tid = threadIdx.x;
+  const int np = kCMT * rows;
+  const int64_t g0 = (int64_t)blockIdx.x * np;
+  for (int t = tid; t < np; t += kCMT) s_max[t] = 0;
+  __syncthreads();
+  for (int r = 0; r < rows; ++r) {
+    const int64_t g = g0 + r * kCMT + tid;
+    if (g >= n_total) break;
     int lo = 0, hi = w.nmat - 1;  // the matrix holding fine point g
     while (lo < hi) {
       const int mid = (lo + hi + 1) >> 1;
@@ -1982,13 +1998,29 @@ __global__ void k_colmax(Work w, int64_t n_total) {
     const GDesc d = gview(w.desc[lo]);
     if (d.theta == 0.0 || !matrix_live(w.st[lo])) continue;
     const int u = (int)(g - d.fine0);
-    for (int e = d.grp[u]; e < d.grp[u + 1]; ++e) {  // column maxima of the search graph
-      const int v = d.gci[e];
-      if (v == u || (unsigned)v >= (unsigned)d.n) continue;
-      atomicMax(reinterpret_cast<unsigned long long*>(w.cmax + d.fine0 + v),
-                (unsigned long long)__double_as_longlong(fabs(d.gva[e])));
+    const int64_t at = d.fine0 - g0;  // column v's place in s_max: at + v
+    const int e1 = d.grp[u + 1];
+    for (int e = d.grp[u]; e < e1; e += 8) {  // column maxima of the search graph
+      int v[8];
+      double x[8];
+#pragma unroll
+      for (int k = 0; k < 8; ++k) {
+        v[k] = e + k < e1 ? d.gci[e + k] : u;
+        x[k] = e + k < e1 ? d.gva[e + k] : 0.0;
+      }
+#pragma unroll
+      for (int k = 0; k < 8; ++k) {
+        if (v[k] == u || (unsigned)v[k] >= (unsigned)d.n) continue;
+        const unsigned long long b = (unsigned long long)__double_as_longlong(fabs(x[k]));
+        const int64_t q = at + v[k];
+        if ((uint64_t)q < (uint64_t)np) atomicMax(&s_max[q], b);
+        else atomicMax(reinterpret_cast<unsigned long long*>(w.cmax + d.fine0 + v[k]), b);
+      }
     }
   }
+  __syncthreads();
+  for (int t = tid; t < np; t += kCMT)
+    if (s_max[t]) atomicMax(reinterpret_cast<unsigned long long*>(w.cmax + g0 + t), s_max[t]);
 }
 
 // Member lists of the aggregates (matrices given with aggregates only):
@@ -2066,9 +2098,14 @@ hipError_t launch_clear_sums(const Work& w, int64_t n_total, int blocks, hipStre
   return hipGetLastError();
 }
 
-hipError_t launch_colmax(const Work& w, int64_t n_total, int blocks, hipStream_t s) {
-  hipLaunchKernelGGL(k_colmax_clear, dim3(blocks), dim3(256), 0, s, w, n_total);
-  hipLaunchKernelGGL(k_colmax, dim3(blocks), dim3(256), 0, s, w, n_total);
+hipError_t launch_colmax(const Work& w, int64_t n_total, int cus, hipStream_t s) {
+  if (n_total <= 0) return hipSuccess;
+  const int64_t cb = std::min<int64_t>((n_total + 255) / 256, (int64_t)cus * 8);
+  hipLaunchKernelGGL(k_colmax_clear, dim3((unsigned)cb), dim3(256), 0, s, w, n_total);
+  // four rows a thread where that leaves most CUs a workgroup, else one
+  const int rows = n_total >= (int64_t)kCMT * kCMRows * cus / 2 ? kCMRows : 1;
+  const int64_t per = (int64_t)kCMT * rows;
+  hipLaunchKernelGGL(k_colmax, dim3((unsigned)((n_total + per - 1) / per)), dim3(kCMT), 0, s, w, n_total, rows);
   return hipGetLastError();
 }
 
