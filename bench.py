@@ -96,9 +96,9 @@ def bin_rows(outs, tuning):
 
 def stage_kernel_name(stage, tuning):
     g = tuning["group"]
-    small = {1: "k_rows8", 4: "k_quad8", 8: "k_quad8"}.get(g, f"k_numeric<{g},...> (bin A)")
+    small = {1: "k_rows8", 4: "k_quad8", 8: "k_quad8"}.get(g, "k_tile<T> (bin A)")
     return {"adj": "k_adj", "count": "k_count", "count_mid": "k_count_mid", "count_big": "k_count_big", "scan": "k_scan", "numeric": small,
-            "numeric32": "k_numeric<16|32,128,SM> (bin B)", "rows_wg": "k_rows_wg", "project": "k_colproj",
+            "numeric32": "k_tile<T> (bin B)", "rows_wg": "k_rows_wg", "project": "k_colproj",
             "upload": "descriptor upload"}.get(stage, stage)
 
 
@@ -123,7 +123,7 @@ def measure_copy_bandwidth(torch, dev, stream, mib=1024, reps=5):
 
 def kernel_source_hash():
     h = hashlib.sha256()
-    for fn in ("k_mixed.hip", "k_quad.hip", "mixed_device.h", "clair_device.h"):
+    for fn in ("k_mixed.hip", "k_quad.hip", "k_tile.hip", "mixed_device.h", "clair_device.h"):
         with open(os.path.join(ROOT, "paper_2307_00229_amd", "csrc", fn), "rb") as f:
             h.update(f.read())
     return h.hexdigest()

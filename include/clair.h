@@ -43,8 +43,8 @@
  *   factorises them in FP32 and refines the solution with FP64 residuals
  *   until the FP64 backward error is at rounding level; the projection is
  *   FP64.  Rows whose FP32 factorisation is unreliable are redone in FP64.
- *   CLAIR_PREC_FP64 is the plain per-row FP64 form (one thread per row, one
- *   kernel per stage, one matrix at a time).  CLAIR_PREC_MIXED_BF16 is the
+ *   CLAIR_PREC_FP64 is the plain per-row FP64 form (sixteen lanes per row,
+ *   one kernel per stage, one matrix at a time).  CLAIR_PREC_MIXED_BF16 is the
  *   mixed form whose workgroup solver (blocks of 33 to 128 points) takes the
  *   L21 and U12 tiles of its blocked LU's trailing updates rounded to
  *   bfloat16 (matrix cores, FP32 accumulation), refines in FP64 for up to 10
@@ -367,11 +367,12 @@ int clair_ctx_stage_times(clair_ctx_t* ctx, const char** names, float* ms, int32
 
 /*
  * Tuning: kernel shape of the mixed path.  group = lanes that solve one row
- * of |N| <= 8 (1, 4 or 8; 8 runs the four-lane solver too) or the largest |N| the lane-group solver takes
- * (16 or 32, one lane per block row); rows with larger blocks go to the
- * workgroup-per-row path.  wg_threads = threads per workgroup (64, 128 or
- * 256), chunk = fine points per workgroup in the symbolic pass (multiple of
- * 256, at most 2048).  0 keeps the current value; defaults 8, 256, 1024.
+ * of |N| <= 8 (1, 4 or 8; 8 runs the four-lane solver too), or the largest
+ * |N| of the first size bin (16 or 32, sixteen lanes per row); the other rows
+ * of up to 32 points take sixteen lanes each, larger ones a workgroup.
+ * wg_threads = threads per workgroup (64, 128 or 256), chunk = fine points
+ * per workgroup in the symbolic pass (multiple of 256, at most 2048; batches
+ * of fewer than two chunks per CU use smaller ones).  0 keeps the current value; defaults 8, 256, 1024.
  * Invalid values return CLAIR_ERR_INVALID and change nothing.  clair_autotune picks them by timing
  * candidates on the given inputs (and stores the result in ctx).
  */
@@ -380,12 +381,10 @@ int clair_ctx_get_tuning(clair_ctx_t* ctx, int32_t* group, int32_t* wg_threads, 
 
 /*
  * Lane layout of the bin-B solver (rows whose |N| lies above the bin-A bound
- * and at most 32): binB_lanes = 8, 16 or 32 lanes per row, each lane holding
- * ceil(b / binB_lanes) rows of the block, where b = 16, 20, 24 or 32 is the
- * smallest bound that holds the largest block the last synchronous call read
- * back (8 lanes become 16 at b = 32, 32 lanes become 16 at b = 16).  0 keeps
- * the current value; default 32.  Other values return CLAIR_ERR_INVALID and
- * change nothing.
+ * and at most 32): binB_lanes = 8, 16 or 32.  The value is kept and returned;
+ * every one of them runs the same solver, sixteen lanes per row.  0 keeps the
+ * current value; default 32.  Other values return CLAIR_ERR_INVALID and change
+ * nothing.
  */
 int clair_ctx_set_bin_shape(clair_ctx_t* ctx, int32_t binB_lanes);
 int clair_ctx_get_bin_shape(clair_ctx_t* ctx, int32_t* binB_lanes);
@@ -492,13 +491,11 @@ int clair_ctx_set_graph(clair_ctx_t* ctx, int32_t nmat, const clair_csr_t* S);
 int clair_ctx_set_literal_pattern(clair_ctx_t* ctx, int32_t on);
 int clair_ctx_get_strength(clair_ctx_t* ctx, double* theta);
 /*
- * clair_autotune -- picks the tuning (clair_ctx_set_tuning) and the bin-B
- * layout (clair_ctx_set_bin_shape) for a batch by timing candidates on it
- * (reps setups each, after one warm-up), and stores them in ctx.  The
- * candidates follow the batch's histogram of block sizes (read back after
- * one synchronous setup): bin-A bounds of 16 and 32 are tried only when rows
- * above 8 (16) points exist, the bin-B layouts only when rows fall between
- * the bin-A bound and 32.  The pick is cached per process by (device,
+ * clair_autotune -- picks the tuning (clair_ctx_set_tuning) for a batch by
+ * timing candidates on it (reps setups each, after one warm-up), and stores
+ * it in ctx.  The candidates follow the batch's histogram of block sizes (read
+ * back after one synchronous setup): bin-A bounds of 16 and 32 are tried only
+ * when rows above 8 (16) points exist.  The pick is cached per process by (device,
  * histogram signature, the number of matrices, the strength setting): a
  * batch whose histogram has, size by size, the same binary order of
  * magnitude of rows reuses it with no timing runs.  Leaves R_out as one

@@ -144,7 +144,7 @@ struct clair_ctx {
   std::vector<clair_csr_t> graph;  // strength matrices of the search, one per matrix (empty: A's graph)
   int literal = 0;  // the literal S^{ell-1} T pattern (both forms; the same pattern as the default at ell <= 2)
   int binB_max = 32;  // largest block of the last batch whose sizes were read back (9..32)
-  int binB_lanes = 32;  // lanes per row of the bin-B solver (8, 16 or 32)
+  int binB_lanes = 32;  // accepted and returned; every value takes the same solver
   int tune_timed = 0;   // timing runs of the last clair_autotune (0: the cache held the histogram)
   int last_maxb = 0;  // the same, unclamped (0: none read back yet)
   int wg_threads = 256;
@@ -630,7 +630,6 @@ int enqueue_numeric(clair_ctx* c, Batch& b, hipStream_t s, bool timing, const Co
   }
   timing_mark(c, timing, s, "rows_wg");
   if (b.any_B) {
-    // rows of up to 8 points: one thread per row; longer rows: eight lanes each
     HIPCHK(launch_project(b.w, s));
     if (capture_check(c->capturing, s, "k_project", __LINE__)) return CLAIR_ERR_HIP;
     timing_mark(c, timing, s, "project");

@@ -165,7 +165,7 @@ struct MatStatus {
 
 struct Counters {
   int32_t total_rows;  // sum of n_c over all matrices
-  int32_t nA;          // rows for the small lane-group solver (|N| <= GA)
+  int32_t nA;          // rows of bin A
   int32_t nB;          // rows for the 32-lane solver (GA < |N| <= 32)
   int32_t nC;          // rows queued for the workgroup solver (larger, or FP32 not trusted)
   int32_t nbig;        // rows with more than 32 points queued for k_count_big
@@ -212,7 +212,7 @@ struct Work {
   int32_t nmat;
   int32_t nchunks;
   int32_t chunk;
-  int32_t GA;             // lane-group size of the small solver (8, 16 or 32)
+  int32_t GA;             // bin A: 1, 4 or 8 (|N| <= 8), 16 or 32 (its bound)
   int32_t capC;
   int32_t adj_w;          // slots per point of the compact adjacency (0: none built)
   int32_t* fadj;          // [n_total * adj_w]

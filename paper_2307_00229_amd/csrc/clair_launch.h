@@ -28,7 +28,7 @@ hipError_t launch_scan(const Work& w, hipStream_t s);
 // sixteen lanes per row, blocks of up to sm <= 32 points (which = 0: bin A of
 // bound 16 or 32; which = 1: bin B)
 hipError_t launch_tile(const Work& w, int which, int sm, int cus, hipStream_t s);
-// one thread per row with |N| <= 8 (GA == 1); four lanes per row (GA == 4)
+// rows of |N| <= 8: four lanes per row (GA = 4 or 8); one thread per row (GA = 1)
 hipError_t launch_quad8(const Work& w, int wg_threads, int cus, hipStream_t s);
 hipError_t launch_rows8(const Work& w, int wg_threads, int cus, hipStream_t s);
 // queued rows of 33 to 128 points: FP32 inverse in registers, FP64 refinement
@@ -167,7 +167,7 @@ hipError_t launch_kkt_dot(const KktWork& w, const double* x, const double* y, do
 hipError_t launch_kkt_step(const KktWork& w, hipStream_t s);
 hipError_t launch_kkt_apply(const KktWork& w, hipStream_t s);               // z -= B_i Abar^{-1} x|_N
 
-// plain FP64 per-row form: one matrix, one thread per row, one kernel per stage
+// plain FP64 per-row form: one matrix, sixteen lanes per row, one kernel per stage
 struct PlainWork {
   const int32_t* rp;
   const int32_t* ci;

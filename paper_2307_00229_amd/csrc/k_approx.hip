@@ -15,8 +15,8 @@
 //            search of row q (sorted; it holds the C-point's 1 too);
 //     u_i = Khat_i^{-1} rho_i: rho_ij / a_jj (diagonal, same kernel), the
 //            two triangular solves with the row's ILU(0) factors, or GMRES
-//            with the row's block (one thread per row, in place on the row's
-//            entries);
+//            with the row's block (in place on the row's entries; ILU(0) by sixteen
+//            lanes per row with the factors in LDS, GMRES by one thread);
 //            with B, s_j += u_ij B_i (FP64 atomics);
 //     z_ij += u_ij - B_i s_j / d_j (the projection; Q Q^T is diagonal).
 // The residual reads only the old R, so each iteration is one residual

@@ -35,7 +35,8 @@
 //                refinement; otherwise, or when that does not converge, FP64 LU
 //                with partial pivoting (block in LDS, or in global scratch when
 //                large).
-//   k_project    persistent, one thread per row:
+//   k_colproj    one workgroup per chunk of fine points, one thread per F-point,
+//                over the column lists:
 //                z_ij -= B_i (sum_k z_kj B_k - B_j) / sum_k B_k^2 per F-entry;
 //                counts F-points no row reaches.
 #include <hip/hip_runtime.h>
@@ -1776,10 +1777,6 @@ __global__ __launch_bounds__(kWT) void k_rows_wg(Work w) {
 // ---------------------------------------------------------------------------
 // projection
 // ---------------------------------------------------------------------------
-// LPR = 1: one thread per row (short rows: a wavefront covers 64
-// consecutive rows, a contiguous run of R).  LPR = 8: eight lanes per row,
-// entry by entry (long rows).  Workgroups [0, nproj) project (nproj a
-// multiple of 8); the rest count the uncovered F-points at the same time.
 // Constraint projection, one workgroup per chunk of fine points, one thread
 // per F-point j (the survey's exchange step: Algorithm 1's projection applied
 // per F-column, QQ^T being diagonal): the entries of column j are those

@@ -30,8 +30,8 @@ namespace {
 // lists' exchanges are collected one row later.  64 five-point matrices of
 // 64^2 to 768^2 (3.19 M rows): 730 us with one lane per row of A and waited
 // exchanges, 717 with the shared gather, 667 with the two latency steps; 16
-// matrices of 129^2 to 515^2: 105 us, where eight lanes per row (k_numeric)
-// took 134.
+// matrices of 129^2 to 515^2: 105 us, where eight lanes per row took
+// 134.
 // ---------------------------------------------------------------------------
 // lane src of the quad, to all four (src is a constant once the calling loops
 // are unrolled, so the switch folds to one DPP move)

@@ -16,9 +16,9 @@
 // fewer wavefronts than the registers do (two per SIMD above 20 points, where
 // three spill: 922 against 1,495 us at 24; three up to 20, four at 12).
 //
-// Bound: VALU issue.  466,489 rows of 24 points (2048^2 nine-point): 1,260 us with
-// one lane per block row, 922 here; 262,144
-// rows of up to 18 points (128^3 seven-point): 467 and 352.
+// Bound: VALU issue (about 70% busy).  466,489 rows of 24 points (2048^2
+// nine-point): 1,260 us with one lane per block row, 922 here; 262,144 rows of
+// up to 18 points (128^3 seven-point): 467 and 352.
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 

@@ -1,5 +1,5 @@
 // mixed_device.h -- device code shared by the kernels of the mixed form
-// (k_mixed.hip, k_quad.hip): row bookkeeping, work distribution, lane-group
+// (k_mixed, k_quad, k_tile and k_block.hip): row bookkeeping, work distribution, lane-group
 // communication.
 #pragma once
 
@@ -266,8 +266,7 @@ __device__ __forceinline__ int wave_append(bool want, int32_t* counter, int cap)
   return (want && slot < cap) ? slot : -1;
 }
 
-// rows the small solvers take: |N| <= 8 for the thread-per-row solver
-// (GA == 1), |N| <= GA for the lane-group solver
+// rows bin A takes: |N| <= 8 (GA = 1, 4 or 8), else |N| <= GA
 __device__ __forceinline__ int small_limit(int GA) { return GA <= 4 ? 8 : GA; }
 // stride of a row's slot in slotA
 __device__ __forceinline__ int slot_stride(int GA) { return GA <= 4 ? 8 : GA; }
