@@ -605,14 +605,14 @@ int enqueue_numeric(clair_ctx* c, Batch& b, hipStream_t s, bool timing, const Co
     } else {
       HIPCHK(launch_tile(b.w, 0, std::min(c->group, c->binB_max), c->cus, s));
     }
-    if (capture_check(c->capturing, s, "k_numeric", __LINE__)) return CLAIR_ERR_HIP;
+    if (capture_check(c->capturing, s, "bin-A solver", __LINE__)) return CLAIR_ERR_HIP;
   }
   timing_mark(c, timing, s, "numeric");
   if (c->group < 32 && (!known || known->nB > 0)) {
     // bin B, for the largest block the last synchronous call read back (a
     // larger row goes to the workgroup solvers, so any bound is correct)
     HIPCHK(launch_tile(b.w, 1, c->binB_max, c->cus, s));
-    if (capture_check(c->capturing, s, "k_numeric32", __LINE__)) return CLAIR_ERR_HIP;
+    if (capture_check(c->capturing, s, "bin-B solver", __LINE__)) return CLAIR_ERR_HIP;
     timing_mark(c, timing, s, "numeric32");
   }
   b.w.gj = 0;

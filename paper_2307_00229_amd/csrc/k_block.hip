@@ -200,6 +200,9 @@ __global__ __launch_bounds__(kGT) __attribute__((amdgpu_waves_per_eu(4))) void k
     const RowInfo ri = row_info(w, c, e - c * w.chunk);
     const int s = ri.s;
     if (s <= 32 || s > kGMax) continue;
+    // without an FP64 scratch (which a row that does not converge here would need)
+    // rows above kLdsBlockMax points are reported by k_rows_wg, not solved
+    if (s > kLdsBlockMax && w.scratch_slots == 0) continue;
     MatStatus* st = &w.st[ri.m];
     if (!matrix_live(*st)) continue;
     const GDesc d = gview(w.desc[ri.m]);

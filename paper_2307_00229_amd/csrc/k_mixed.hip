@@ -1992,9 +1992,9 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void k
 // doubles order like their bit patterns, so an unsigned 64-bit atomic max
 // takes the maximum.
 //
-// Bound: the rate of atomics in memory (about 65 a ns), so a workgroup gathers
+// Bound: the rate of atomics in memory (about 130 a ns), so a workgroup gathers
 // the maxima of its own run of points in LDS and sends one atomic for each;
-// only entries that leave the run go to memory one by one.  1001^2 five-point
+// only entries that leave the run go to memory one by one.  1001^2 nine-point
 // rows: 69 us with an atomic per entry (also with eight entries a thread in
 // flight), now 52 (two rows a thread: 55).
 __global__ void k_colmax_clear(Work w, int64_t n_total) {

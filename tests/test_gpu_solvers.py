@@ -309,3 +309,30 @@ def test_malformed_transpose_is_refused():
             clair.clair_smooth_B(M, cf[0], B[0], 1, 0.6, transpose=True)
         assert e.value.status == 1
     clair.clair_transpose(A[0], p.n)  # and the library goes on
+
+
+@pytest.mark.parametrize("top,status", [(64, 0), (65, 5), (128, 5)])
+def test_rows_beyond_the_lds_need_a_scratch(top, status):
+    """Without an FP64 scratch (the fixed-memory entry point; an asynchronous
+    call before any synchronous one) rows above 64 points are reported."""
+    import ctypes
+
+    from paper_2307_00229_amd import clair
+
+    lib = clair.load_library()
+    p = _groups([5, top, 33, 8], 61, 6)
+    o = oracle.build_R_problem(p)
+    (A,), (cf,), (B,), _ = to_device([p])
+    first = int(np.nonzero(p.cf)[0][1])
+    out, info, Ac = clair.ROut(o["n_c"], o["nnz"]), clair.Info(), A.c()
+    Rc = out.c()
+    st = lib.clair_build_R_noalloc(ctypes.byref(Ac), cf.data_ptr(), B.data_ptr(), 1, ctypes.byref(Rc), None,
+                                   ctypes.byref(info))
+    assert st == status and info.status == status
+    assert info.first_bad_row == (first if status else -1)
+    ctx = clair.Context()
+    outs, _, _ = clair.clair_build_R_batched([A], [cf], [B], [1], ctx=ctx, outs=[clair.ROut(o["n_c"], o["nnz"])],
+                                             async_=True)
+    st, infos = ctx.info(1, outs)
+    assert infos[0]["status"] == status and infos[0]["first_bad_row"] == (first if status else -1)
+    _check([p], ctx=ctx)  # a synchronous call sizes the scratch
