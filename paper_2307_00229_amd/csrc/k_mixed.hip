@@ -5,8 +5,9 @@
 //                graphs): for every point, the F-points one step reaches.
 //   k_count      symbolic pass per chunk of fine points: the C-points of the
 //                chunk; rows at ell = 1 (up to 8 entries) and at ell = 2 over
-//                a width-4 adjacency sized by one thread each from a sorted
-//                candidate list and written to their slot; a chunk with every
+//                the adjacency sized from a sorted candidate list, by one thread
+//                each (up to four edges a point) or by a quad (up to eight), and
+//                written to their slot; a chunk with every
 //                row sized gets its chunk-local prefix of |N(i)|+1 here;
 //                clears the projection's column lists of the chunk.
 //   k_count_mid  the other rows of unfinished chunks at distance 1 and 2: one
@@ -382,38 +383,150 @@ __device__ __forceinline__ int emit_distinct(const int (&v)[P], const Work& w, i
   return sz;
 }
 
-// N(i) at ell = 2 from the compact adjacency of width 4: the four slots of
-// i and the four of each of them, sorted, duplicates dropped.  -1 when a
-// point overflows its slots (the row is left to k_count_mid).
-__device__ __forceinline__ int count_adj4_ell2(const Work& w, const GDesc& d, int i, int64_t row, int SA, int lim,
-                                               int* stage) {
-  int a[4];
-  adj_load<4>(d.fadj, i, a);
+// N(i) at ell = 2 from the compact adjacency: the first four slots of i and the
+// first four of each of them, sorted, duplicates dropped.  -1 when a point
+// overflows its slots (the row is left to k_count_mid); at width 8, -2 when a
+// point has more than four (count_adj8_ell2 takes the row).
+template <int W>
+__device__ __forceinline__ int count_adj_ell2(const Work& w, const GDesc& d, int i, int64_t row, int SA, int lim,
+                                              int* stage) {
+  int a[W];
+  adj_load<W>(d.fadj, i, a);
   if (a[0] == kAdjOverflow) return -1;
-  int b[4][4];
+  if (W > 4 && a[W > 4 ? 4 : 0] >= 0) return -2;
+  int b[4][W];
 #pragma unroll
   for (int q = 0; q < 4; ++q) {
     if (a[q] >= 0) {
-      adj_load<4>(d.fadj, a[q], b[q]);
+      adj_load<W>(d.fadj, a[q], b[q]);
     } else {
 #pragma unroll
-      for (int r = 0; r < 4; ++r) b[q][r] = -1;
+      for (int r = 0; r < W; ++r) b[q][r] = -1;
     }
   }
   int v[32];
-  bool ovf = false;
+  bool ovf = false, more = false;
 #pragma unroll
   for (int q = 0; q < 4; ++q) {
     ovf |= b[q][0] == kAdjOverflow;
+    more |= W > 4 && b[q][W > 4 ? 4 : 0] >= 0;
     v[q] = a[q] >= 0 ? a[q] : 0x7fffffff;
 #pragma unroll
     for (int r = 0; r < 4; ++r) v[4 + 4 * q + r] = b[q][r] >= 0 ? b[q][r] : 0x7fffffff;
   }
   if (ovf) return -1;
+  if (more) return -2;
 #pragma unroll
   for (int q = 20; q < 32; ++q) v[q] = 0x7fffffff;
   bitonic_sort<32>(v);
   return emit_distinct<32>(v, w, row, SA, lim, stage);
+}
+
+// N(i) at ell = 2 from the compact adjacency of width 8, by a quad: lane l
+// takes slots 2l and 2l + 1 of i and the eight of each of them (18 candidates),
+// sorts them, and the four lists are merged across the quad (bitonic merges;
+// the exchanges are DPP quad permutations), so the distinct ones end up in
+// order, lane by lane.  They go to the row's slot through `stage` (33 words of
+// LDS per quad).  -1 when a point overflows its slots or there are more than 32
+// points (the row is left to k_count_mid).  All lanes of the wavefront call it;
+// a quad without a row has on = false.
+//
+// Two trips to memory a row and about 90 registers, where k_count_mid's search
+// takes a round of loads per four frontier points at two wavefronts per SIMD:
+// the two kernels took 300 us on 2048^2 nine-point rows (24 points, 72
+// candidates) and 103 on 128^3 seven-point rows, now 146 and 74.
+__device__ __forceinline__ int count_adj8_ell2(const Work& w, const GDesc& d, bool on, int i, int64_t row, int SA,
+                                               int lim, int ql, int* stage) {
+  i2u a;
+  a.x = -1;
+  a.y = -1;
+  if (on) a = *(gptr<const i2u>)(d.fadj + (int64_t)i * 8 + 2 * ql);
+  int b0[8], b1[8];
+#pragma unroll
+  for (int r = 0; r < 8; ++r) { b0[r] = -1; b1[r] = -1; }
+  if (a.x >= 0) adj_load<8>(d.fadj, a.x, b0);
+  if (a.y >= 0) adj_load<8>(d.fadj, a.y, b1);
+  int bad = (a.x == kAdjOverflow || b0[0] == kAdjOverflow || b1[0] == kAdjOverflow) ? 1 : 0;
+  int v[32];
+  v[0] = a.x >= 0 ? a.x : 0x7fffffff;
+  v[1] = a.y >= 0 ? a.y : 0x7fffffff;
+#pragma unroll
+  for (int r = 0; r < 8; ++r) {
+    v[2 + r] = b0[r] >= 0 ? b0[r] : 0x7fffffff;
+    v[10 + r] = b1[r] >= 0 ? b1[r] : 0x7fffffff;
+  }
+#pragma unroll
+  for (int r = 18; r < 32; ++r) v[r] = 0x7fffffff;
+  bitonic_sort<32>(v);
+  auto merge = [&]() {
+#pragma unroll
+    for (int st = 16; st > 0; st >>= 1)
+#pragma unroll
+      for (int k = 0; k < 32; ++k)
+        if ((k & st) == 0) {
+          const int lo = min(v[k], v[k | st]), hi = max(v[k], v[k | st]);
+          v[k] = lo;
+          v[k | st] = hi;
+        }
+  };
+  // lanes 0, 1 and lanes 2, 3: the smaller 32 to the even lane
+  auto cross_reversed = [&](auto ctrl, bool low) {
+    int o[32];
+#pragma unroll
+    for (int k = 0; k < 32; ++k) o[k] = __builtin_amdgcn_mov_dpp(v[31 - k], decltype(ctrl)::value, 0xF, 0xF, false);
+#pragma unroll
+    for (int k = 0; k < 32; ++k) v[k] = low ? min(v[k], o[k]) : max(v[k], o[k]);
+  };
+  cross_reversed(std::integral_constant<int, 0xB1>{}, (ql & 1) == 0);  // quad_perm [1,0,3,2]
+  merge();
+  // the pairs' lists: the smaller 64 to lanes 0 and 1, then in order within each half
+  cross_reversed(std::integral_constant<int, 0x1B>{}, ql < 2);  // quad_perm [3,2,1,0]
+#pragma unroll
+  for (int k = 0; k < 32; ++k) {
+    const int o = __builtin_amdgcn_mov_dpp(v[k], 0xB1, 0xF, 0xF, false);
+    v[k] = (ql & 1) == 0 ? min(v[k], o) : max(v[k], o);
+  }
+  merge();
+  // distinct values: places from a prefix over the quad
+  const int before = __builtin_amdgcn_mov_dpp(v[31], 0x90, 0xF, 0xF, false);  // the lane below's last
+  int cnt = 0;
+#pragma unroll
+  for (int q = 0; q < 32; ++q) {
+    const bool first = q == 0 && ql == 0;
+    const int pv = q == 0 ? before : v[q > 0 ? q - 1 : 0];
+    cnt += (v[q] != 0x7fffffff && (first || v[q] != pv)) ? 1 : 0;
+  }
+  int pre = cnt;
+  const int x1 = __builtin_amdgcn_mov_dpp(pre, 0x90, 0xF, 0xF, false);  // quad_perm [0,0,1,2]
+  pre += ql >= 1 ? x1 : 0;
+  const int x2 = __builtin_amdgcn_mov_dpp(pre, 0x40, 0xF, 0xF, false);  // quad_perm [0,0,0,1]
+  pre += ql >= 2 ? x2 : 0;
+  const int sz = __builtin_amdgcn_mov_dpp(pre, 0xFF, 0xF, 0xF, false);
+  bad |= __builtin_amdgcn_mov_dpp(bad, 0xB1, 0xF, 0xF, false);
+  bad |= __builtin_amdgcn_mov_dpp(bad, 0x4E, 0xF, 0xF, false);
+  const bool ok = on && !bad && sz <= 32;
+  if (ok) {
+    int pos = pre - cnt;
+#pragma unroll
+    for (int q = 0; q < 32; ++q) {
+      const bool first = q == 0 && ql == 0;
+      const int pv = q == 0 ? before : v[q > 0 ? q - 1 : 0];
+      const bool u = v[q] != 0x7fffffff && (first || v[q] != pv);
+      if (u) stage[pos] = v[q];
+      pos += u ? 1 : 0;
+    }
+  }
+  wave_sync();
+  if (ok) {
+    gptr<int32_t> dst = sz <= lim ? to_global(w.slotA) + row * SA : to_global(w.slotB) + row * 32;
+    for (int p = 4 * ql; p < sz; p += 16) {  // (a slot holds a multiple of four words)
+      adj_v4 t;
+      t.x = stage[p]; t.y = stage[p + 1]; t.z = stage[p + 2]; t.w = stage[p + 3];
+      *(gptr<adj_v4>)(dst + p) = t;
+    }
+  }
+  wave_sync();  // the stage is free
+  return ok ? sz : -1;
 }
 
 // N(i) at ell = 1 from row i of the search graph (at most 8 stored entries;
@@ -492,9 +605,10 @@ __device__ __forceinline__ void finish_chunk(const Work& w, int c, int m, MatSta
 
 // Symbolic pass, first part: one workgroup per chunk of fine points.  The
 // chunk's C-points are compacted; rows at ell = 1 with at most 8 stored
-// entries, and rows at ell = 2 of matrices with a width-4 compact adjacency,
+// entries, and rows at ell = 2 of matrices with a compact adjacency,
 // are sized by one thread each from a sorted candidate list (no search
-// state); a chunk whose rows are all sized is finished here.  Other rows
+// state; over a width-8 adjacency by a quad where a point has more than four
+// edges); a chunk whose rows are all sized is finished here.  Other rows
 // (larger stencils, ell >= 3, aggregates, overflowing points) are marked -1
 // in lnz and left, with the chunk's bookkeeping, to k_count_mid.
 template <int W>
@@ -504,7 +618,8 @@ __global__ __launch_bounds__(kNT) void k_count(Work w) {
   __shared__ int s_scan[kNT];
   __shared__ int s_stage[kNT * kStage];
   __shared__ int s_flag[4];  // max |N|, -, rows in bin A, rows in bin B
-  __shared__ int s_ndef, s_qbase;
+  __shared__ int s_ndef, s_qbase, s_nlist;
+  __shared__ int16_t s_list[W == 8 ? kMaxChunk : 1];  // rows for the quads
 
   // each XCD's chunks newest first: k_adj wrote them in ascending order, so
   // the last ones' adjacency is the part most likely still cached (and the
@@ -547,17 +662,42 @@ __global__ __launch_bounds__(kNT) void k_count(Work w) {
     w.clocal[base + rank] = j;
     ++rank;
   }
-  if (tid == 0) { s_flag[0] = 0; s_flag[1] = 0; s_flag[2] = 0; s_flag[3] = 0; s_ndef = 0; }
+  if (tid == 0) { s_flag[0] = 0; s_flag[1] = 0; s_flag[2] = 0; s_flag[3] = 0; s_ndef = 0; s_nlist = 0; }
   __syncthreads();
 
   const int SA = slot_stride(w.GA);
   const int lim = small_limit(w.GA);
   int ndef = 0;
-  for (int t = tid; t < nc; t += kNT) {
+  if (W == 8 && d.fadj && d.ell == 2 && !d.agg_rp) {
+    static_assert(kNT / 4 * 33 <= kNT * kStage, "33 words of the stage per quad");
+    const int qd = tid >> 2, ql = tid & 3;
+    // rows whose points have at most four edges each by one thread, the others
+    // by quads (a strength test leaves few edges: 1001^2 nine-point rows at
+    // 0.25: both kernels 57 us with k_count_mid's
+    // search, 61 with quads alone, 31 so; 2048^2 rows, all for the quads, 139
+    // and 146)
+    for (int t = tid; t < nc; t += kNT) {
+      const int sz = count_adj_ell2<8>(w, d, s_rows[t], base + t, SA, lim, s_stage + tid * kStage);
+      s_size[t] = (int16_t)sz;
+      ndef += sz == -1 ? 1 : 0;
+      if (sz == -2) s_list[atomicAdd(&s_nlist, 1)] = (int16_t)t;
+    }
+    __syncthreads();
+    const int nl = s_nlist;
+    for (int k0 = 0; k0 < nl; k0 += kNT / 4) {
+      const bool on = k0 + qd < nl;
+      const int t = on ? s_list[k0 + qd] : 0;
+      const int sz = count_adj8_ell2(w, d, on, s_rows[t], base + t, SA, lim, ql, s_stage + 33 * qd);
+      if (on && ql == 0) {
+        s_size[t] = (int16_t)sz;
+        ndef += sz < 0 ? 1 : 0;
+      }
+    }
+  } else for (int t = tid; t < nc; t += kNT) {
     int sz = -1;
     if (!d.agg_rp) {
       if constexpr (W == 4) {
-        if (d.fadj && d.ell == 2) sz = count_adj4_ell2(w, d, s_rows[t], base + t, SA, lim, s_stage + tid * kStage);
+        if (d.fadj && d.ell == 2) sz = count_adj_ell2<4>(w, d, s_rows[t], base + t, SA, lim, s_stage + tid * kStage);
       }
       if (d.ell == 1) sz = count_row_ell1(w, d, s_rows[t], base + t, SA, lim, s_stage + tid * kStage);
     }
@@ -2163,7 +2303,8 @@ hipError_t launch_count(const Work& w, hipStream_t s) {
   if (w.nchunks == 0) return hipSuccess;
   const dim3 grid(w.nchunks), block(kNT);
   if (w.adj_w == 4) hipLaunchKernelGGL(k_count<4>, grid, block, 0, s, w);
-  else if (w.adj_w == 0 || w.adj_w == 8) hipLaunchKernelGGL(k_count<0>, grid, block, 0, s, w);
+  else if (w.adj_w == 8) hipLaunchKernelGGL(k_count<8>, grid, block, 0, s, w);
+  else if (w.adj_w == 0) hipLaunchKernelGGL(k_count<0>, grid, block, 0, s, w);
   else return hipErrorInvalidValue;
   return hipGetLastError();
 }

@@ -336,3 +336,17 @@ def test_rows_beyond_the_lds_need_a_scratch(top, status):
     st, infos = ctx.info(1, outs)
     assert infos[0]["status"] == status and infos[0]["first_bad_row"] == (first if status else -1)
     _check([p], ctx=ctx)  # a synchronous call sizes the scratch
+
+
+@pytest.mark.parametrize("deg", [2, 4, 5, 7, 8, 9])
+@pytest.mark.parametrize("group", [4, 16, 32])
+def test_width_8_adjacency_rows(group, deg):
+    """Rows at distance 2 over a width-8 adjacency: points of up to four edges,
+    of five to eight and beyond, neighbourhoods up to and above 32 points."""
+    from paper_2307_00229_amd import clair
+
+    ctx = clair.Context()
+    ctx.set_tuning(group=group)
+    ctx.set_search_adjacency(8)
+    _check([_groups([0, 1, 3, 4, 5, 6, 7, 8, 2] * 29, 71 + deg, deg, ell=2), _groups([8, 4] * 3, 5, 2, ell=2),
+            P.random_sparse(200, 0.02, deg, ell=2)], ctx=ctx)
