@@ -730,8 +730,9 @@ __global__ __launch_bounds__(kNT) void k_count(Work w) {
 // Bound: latency at two wavefronts per SIMD (the register set).  A chunk of
 // 1024 points has 114 to 256 rows, so workgroups of 128 threads keep their
 // wavefronts busy (with 256, half of each workgroup's waited):
-// 2048^2 nine-point rows 251 -> 230 us, 128^3 seven-point 81 -> 70 us.  (A set
-// in LDS shared by sixteen lanes per row, as in k_count_wide, took 222 and 93.)
+// 2048^2 nine-point rows 251 -> 230 us, 128^3 seven-point 81 -> 70 us, measured
+// while this kernel sized them (k_count does now).  (A set in LDS shared by
+// sixteen lanes per row, as in k_count_wide, took 222 and 93.)
 constexpr int kMT = 128;
 template <int W>
 __global__ __launch_bounds__(kMT) void k_count_mid(Work w) {
