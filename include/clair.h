@@ -372,7 +372,7 @@ int clair_ctx_stage_times(clair_ctx_t* ctx, const char** names, float* ms, int32
  * of up to 32 points take sixteen lanes each, larger ones a workgroup.
  * wg_threads = threads per workgroup (64, 128 or 256), chunk = fine points
  * per workgroup in the symbolic pass (multiple of 256, at most 2048; batches
- * of fewer than two chunks per CU use smaller ones).  0 keeps the current value; defaults 8, 256, 1024.
+ * of fewer chunks than CUs use smaller ones).  0 keeps the current value; defaults 8, 256, 1024.
  * Invalid values return CLAIR_ERR_INVALID and change nothing.  clair_autotune picks them by timing
  * candidates on the given inputs (and stores the result in ctx).
  */

@@ -152,7 +152,7 @@ def test_far_searches(ell, mode):
 
 @pytest.mark.parametrize("ell", [1, 2])
 def test_small_batches(ell):
-    """Batches below two chunks per CU use smaller chunks: matrices below, at
+    """Batches of fewer chunks than CUs use smaller chunks: matrices below, at
     and above a chunk, and of one point."""
     ps = []
     for n in (1, 2, 63, 64, 65, 127, 129, 1000, 4099):
