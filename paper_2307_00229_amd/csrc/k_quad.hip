@@ -479,7 +479,7 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(3))) void k_
   }
   }
   pend.flush(w);
-  if (ql == 0) rmx.flush(w);
+  rmx.flush_wave(w);
 }
 
 }  // namespace

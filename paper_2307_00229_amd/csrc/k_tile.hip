@@ -443,7 +443,7 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(T <= 5 ? 3 :
     }
   }
   }
-  if (l == 0) rmx.flush(w);
+  rmx.flush_wave(w);
 }
 
 }  // namespace

@@ -248,6 +248,23 @@ struct RefineMax {
     }
     v = max(v, it);
   }
+  // the last flush, by the whole wavefront (lanes without rows too): one atomic
+  // per wavefront and matrix.  One per row group, where each has a row only, met
+  // at one address: 330^2 five-point rows, distance 1, numeric pass 25 -> 16 us.
+  __device__ __forceinline__ void flush_wave(const Work& w) {
+    uint64_t left = __ballot(m >= 0);
+    while (left) {
+      const int lead = __ffsll((unsigned long long)left) - 1;
+      const int mm = __builtin_amdgcn_readlane(m, lead);
+      int mx = m == mm ? v : 0;
+#pragma unroll
+      for (int o = 32; o > 0; o >>= 1) mx = max(mx, __shfl_xor(mx, o, 64));
+      if ((int)(threadIdx.x & 63) == lead &&
+          mx > __hip_atomic_load(&w.st[mm].refine_max, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT))
+        atomicMax(&w.st[mm].refine_max, mx);
+      left &= ~__ballot(m == mm);
+    }
+  }
 };
 
 __device__ __forceinline__ int lane_id() { return threadIdx.x & 63; }
