@@ -19,6 +19,7 @@
 #include "clair.h"
 #include "clair_device.h"
 #include "clair_launch.h"
+#include "launch_rules.h"
 
 using namespace clair;
 
@@ -590,10 +591,22 @@ const Counters* host_counters(clair_ctx* c, const Batch& b) {
   return reinterpret_cast<const Counters*>(readback_base(c) + (b.L.cnt - b.L.desc));
 }
 
+// bin A (which = 0) or B (1) by k_tile (see tile_pick)
+int enqueue_tile(clair_ctx* c, const Batch& b, int which, bool sized, hipStream_t s) {
+  int points = which ? c->binB_max : std::min(c->group, c->binB_max);
+  // (no bin-B row the last time: one instance, empty most likely, does)
+  if (which && !sized && c->last_maxb && c->last_maxb <= 8) points = bin_b_reach(points);
+  const TilePick p = tile_pick(points, which ? bin_b_reach(points) : c->group, sized);
+  HIPCHK(launch_tile(b.w, which, p.first, -1, p.second ? p.first : INT_MAX, c->cus, s));
+  if (p.second) HIPCHK(launch_tile(b.w, which, p.second, p.first, INT_MAX, c->cus, s));
+  return CLAIR_OK;
+}
+
 // enqueue the numeric half (after the symbolic pass).  `known` holds the queue
 // lengths when the host has read them back (synchronous calls): empty queues
-// then launch nothing.
-int enqueue_numeric(clair_ctx* c, Batch& b, hipStream_t s, bool timing, const Counters* known, bool skip_wg = false) {
+// then launch nothing.  sized: the context's block sizes are this batch's own.
+int enqueue_numeric(clair_ctx* c, Batch& b, hipStream_t s, bool timing, const Counters* known, bool sized,
+                    bool skip_wg = false) {
   b.w.scratch = static_cast<double*>(c->scratch.p);
   b.w.scratch_slots = c->scratch_slots;
   b.w.scratch_stride = c->scratch_stride;
@@ -606,7 +619,7 @@ int enqueue_numeric(clair_ctx* c, Batch& b, hipStream_t s, bool timing, const Co
       // 667 against 990 us on 64 of 64^2 to 768^2)
       HIPCHK(launch_quad8(b.w, c->wg_threads, c->cus, s));
     } else {
-      HIPCHK(launch_tile(b.w, 0, std::min(c->group, c->binB_max), c->cus, s));
+      if (int rc = enqueue_tile(c, b, 0, sized, s)) return rc;
     }
     if (capture_check(c->capturing, s, "bin-A solver", __LINE__)) return CLAIR_ERR_HIP;
   }
@@ -614,7 +627,7 @@ int enqueue_numeric(clair_ctx* c, Batch& b, hipStream_t s, bool timing, const Co
   if (c->group < 32 && (!known || known->nB > 0)) {
     // bin B, for the largest block the last synchronous call read back (a
     // larger row goes to the workgroup solvers, so any bound is correct)
-    HIPCHK(launch_tile(b.w, 1, c->binB_max, c->cus, s));
+    if (int rc = enqueue_tile(c, b, 1, sized, s)) return rc;
     if (capture_check(c->capturing, s, "bin-B solver", __LINE__)) return CLAIR_ERR_HIP;
     timing_mark(c, timing, s, "numeric32");
   }
@@ -765,7 +778,7 @@ int run_mixed_once(clair_ctx* c, int32_t nmat, const clair_csr_t* A, const int8_
   }
   rc = enqueue_symbolic(c, b, s, false, false);
   if (rc) return rc;
-  rc = enqueue_numeric(c, b, s, false, &h.cnt, h.cnt.nC == 0);
+  rc = enqueue_numeric(c, b, s, false, &h.cnt, true, h.cnt.nC == 0);
   if (rc) return rc;
   c->last_work = b.w;
   rc = read_status(c, b, s);
@@ -849,7 +862,7 @@ int run_mixed(clair_ctx* c, int32_t nmat, const clair_csr_t* A, const int8_t* co
   if (rc) return rc;
   Counters known{};
   if (!async) known = *host_counters(c, b);
-  rc = enqueue_numeric(c, b, s, timing, async ? nullptr : &known);
+  rc = enqueue_numeric(c, b, s, timing, async ? nullptr : &known, !async);
   if (rc) return rc;
   c->last_work = b.w;
   if (async) return CLAIR_OK;
@@ -2240,7 +2253,7 @@ int clair_plan_execute(clair_plan_t* pl, int32_t nmat, const clair_csr_t* A, con
   rc = ensure_links(c, b);
   if (rc) return rc;
   const Counters* known = async ? nullptr : reinterpret_cast<const Counters*>(pl->head.data() + (b.L.cnt - b.L.desc));
-  rc = enqueue_numeric(c, b, s, timing, known);
+  rc = enqueue_numeric(c, b, s, timing, known, true);
   if (rc) return rc;
   if (async) return CLAIR_OK;
   rc = read_status(c, b, s);

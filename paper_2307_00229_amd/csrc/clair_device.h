@@ -170,7 +170,8 @@ struct Counters {
   int32_t nC;          // rows queued for the workgroup solver (larger, or FP32 not trusted)
   int32_t nbig;        // rows with more than 32 points queued for k_count_big
   int32_t nmid;        // chunks k_count left to k_count_mid (queued in midq)
-  int32_t pad1, pad2;
+  int32_t maxb;        // largest block of the batch (written by k_scan)
+  int32_t pad;
 };
 
 // Row t of chunk c: fine offset base = fine0 + (c - chunk0) * chunk of its

@@ -26,8 +26,8 @@ hipError_t launch_count_wide(const Work& w, int blocks, hipStream_t s);
 hipError_t launch_count_big(const Work& w, int blocks, hipStream_t s);
 hipError_t launch_scan(const Work& w, hipStream_t s);
 // sixteen lanes per row, blocks of up to sm <= 32 points (which = 0: bin A of
-// bound 16 or 32; which = 1: bin B)
-hipError_t launch_tile(const Work& w, int which, int sm, int cus, hipStream_t s);
+// bound 16 or 32; which = 1: bin B), for batches whose largest block lies in (above, upto]
+hipError_t launch_tile(const Work& w, int which, int sm, int above, int upto, int cus, hipStream_t s);
 // rows of |N| <= 8: four lanes per row (GA = 4 or 8); one thread per row (GA = 1)
 hipError_t launch_quad8(const Work& w, int wg_threads, int cus, hipStream_t s);
 hipError_t launch_rows8(const Work& w, int wg_threads, int cus, hipStream_t s);

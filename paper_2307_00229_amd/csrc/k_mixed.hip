@@ -20,8 +20,8 @@
 //                it (queued for the workgroup solver); the last row of a chunk
 //                to be sized redoes the chunk's prefix.
 //   k_scan       one workgroup: chunk bases -> global row numbers, R offsets,
-//                n_c and nnz(R) per matrix, bin sizes, capacity check,
-//                R.row_ptr[n_c].
+//                n_c and nnz(R) per matrix, bin sizes, the largest block,
+//                capacity check, R.row_ptr[n_c].
 //   k_quad8      (k_quad.hip) persistent over the rows, four lanes per row with
 //                |N| <= 8: see there.
 //   k_tile       (k_tile.hip) sixteen lanes per row with up to 32 points: FP32
@@ -1012,6 +1012,7 @@ __global__ __launch_bounds__(kNT) void k_count_big(Work w) {
 __global__ __launch_bounds__(1024) void k_scan(Work w) {
   __shared__ long long s_wr[17], s_wz[17];
   __shared__ int s_wa[17], s_wb[17];
+  __shared__ int s_maxb;
   const int tid = threadIdx.x;
   const int lane = tid & 63, wid = tid >> 6;
   const int nch = w.nchunks;
@@ -1101,6 +1102,7 @@ __global__ __launch_bounds__(1024) void k_scan(Work w) {
   // a pass left out on a hint that does not hold (the host runs again): no
   // matrix is live, so nothing uses the unfinished chunks' offsets
   const bool stop = ((w.skip & 1) && w.cnt->nmid > 0) || ((w.skip & 2) && w.cnt->nbig > 0);
+  if (tid == 0) s_maxb = 0;
   __syncthreads();
   for (int m = tid; m < w.nmat; m += 1024) {
     const GDesc d = gview(w.desc[m]);
@@ -1116,6 +1118,7 @@ __global__ __launch_bounds__(1024) void k_scan(Work w) {
     st->nz_base = zb;
     st->n_c = n_c;
     st->nnz = nnz;
+    atomicMax(&s_maxb, st->max_block);
     if (st->status != ST_INVALID) {
       const bool fits = d.Rrp && d.Rci && d.Rva && (int64_t)n_c + 1 <= d.row_cap && nnz <= d.nnz_cap &&
                         nnz <= 0x7fffffffLL;
@@ -1126,7 +1129,9 @@ __global__ __launch_bounds__(1024) void k_scan(Work w) {
       }
     }
   }
+  __syncthreads();
   if (tid == 0) {
+    w.cnt->maxb = s_maxb;
     w.chunk_rbase[nch] = (int32_t)rows_total;
     w.cnt->total_rows = (int32_t)rows_total;
     w.cnt->nA = na;

@@ -129,9 +129,10 @@ __device__ __forceinline__ void tile_steps(float (&kf)[T][T], int r, int c, int 
 }
 
 // which = 0: bin A (|N| <= GA, GA = 16 or 32); which = 1: bin B (the bin-A bound
-// < |N| <= 32).  A row of more than 4 T points goes to the workgroup solvers.
+// < |N| <= 32).  It runs for batches whose largest block lies in (above, upto].  A row
+// of more than 4 T points goes to the workgroup solvers.
 template <int T>
-__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(T <= 5 ? 3 : 2))) void k_tile(Work w, int which) {
+__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(T <= 5 ? 3 : 2))) void k_tile(Work w, int which, int above, int upto) {
   typedef TileBuf<T> Buf;
   constexpr int SM = Buf::SM, HA = Buf::HA, LD = Buf::LD, HALF = 4 * HA * LD;
   constexpr int NG = 4;               // rows of a wavefront
@@ -141,7 +142,7 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(T <= 5 ? 3 :
   const int tid = threadIdx.x;
   const int grp = tid >> 4, l = tid & 15, r = l >> 2, c = l & 3;
   Buf& gb = sb[grp];
-  if ((which ? w.cnt->nB : w.cnt->nA) == 0) return;
+  if ((which ? w.cnt->nB : w.cnt->nA) == 0 || w.cnt->maxb <= above || w.cnt->maxb > upto) return;
   const int smin = which ? small_limit(w.GA) + 1 : 0;
   const int32_t* slots = which ? w.slotB : w.slotA;
   const int sstride = which ? 32 : w.GA;
@@ -449,14 +450,14 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(T <= 5 ? 3 :
 }  // namespace
 
 // persistent grid: as many workgroups as fit on the device at once.  sm: the
-// largest block to expect (at most 32).
-hipError_t launch_tile(const Work& w, int which, int sm, int cus, hipStream_t s) {
+// largest block to take (at most 32); above, upto as in k_tile.
+hipError_t launch_tile(const Work& w, int which, int sm, int above, int upto, int cus, hipStream_t s) {
 #define CLAIR_TILE(TT)                                                                     \
   if (sm <= 4 * TT) {                                                                      \
     const int per = resident_blocks<k_tile<TT>, 64>();                                     \
     if (per < 0) return hipErrorInvalidValue;                                              \
     const int blocks = (std::max(1, per) * cus + 7) / 8 * 8;                              \
-    hipLaunchKernelGGL((k_tile<TT>), dim3(blocks), dim3(64), 0, s, w, which);              \
+    hipLaunchKernelGGL((k_tile<TT>), dim3(blocks), dim3(64), 0, s, w, which, above, upto);              \
     return hipGetLastError();                                                              \
   }
   CLAIR_TILE(3)

@@ -1,0 +1,48 @@
+"""GPU calls whose kernels are chosen from what earlier calls read back.
+
+Blocks larger than the context has seen, rows and outputs at the choice's
+edges.  Against the oracle with the gates of tests/_util.py (the generated
+systems are the strictly dominant ones of tests/test_gpu_solvers.py).
+"""
+import numpy as np
+import pytest
+
+import oracle
+from paper_2307_00229_amd import problems as P
+
+from ._util import assert_matches_oracle, to_device
+from .test_gpu_solvers import _groups, _need_gpu  # noqa: F401
+
+pytestmark = pytest.mark.gpu
+
+torch = pytest.importorskip("torch")
+
+
+def _host(out):
+    rp, ci, va = (x.cpu().numpy() for x in out.trimmed())
+    return dict(row_ptr=rp, col_idx=ci, val=va, n_c=out.n_c, nnz=out.nnz)
+
+
+@pytest.mark.parametrize("group", [4, 8, 16, 32])
+@pytest.mark.parametrize("seen,then", [(5, 9), (9, 13), (9, 16), (12, 16), (20, 20), (26, 29), (28, 32)])
+def test_larger_blocks_in_an_asynchronous_call(group, seen, then):
+    """An asynchronous call whose blocks outgrow the last synchronous call's,
+    within the bin's bounds of 16, 20, 24 and 32 points (bin A: the group), is
+    solved by the same solvers: no row falls to the one-workgroup FP64 solver."""
+    from paper_2307_00229_amd import clair
+
+    ctx = clair.Context()
+    ctx.set_tuning(group=group)
+    small, big = _groups([seen, 3, 8] * 5, 1, 5), _groups([then, then - 1, 3, 9, 8] * 11, 2, 6)
+    for p in (small, big, small):  # (the larger blocks are never read back before their call)
+        As, cfs, Bs, ells = to_device([p])
+        o = oracle.build_R_problem(p)
+        outs = [clair.ROut(o["n_c"], o["nnz"])]
+        if p is small:
+            clair.clair_build_R_batched(As, cfs, Bs, ells, ctx=ctx, outs=outs)
+            continue
+        for _ in range(2):
+            clair.clair_build_R_batched(As, cfs, Bs, ells, ctx=ctx, outs=outs, async_=True)
+            st, infos = ctx.info(1, outs)
+            assert st == 0 and infos[0]["n_fp64_rows"] == 0
+            assert_matches_oracle(p, _host(outs[0]), o, infos[0])
