@@ -129,6 +129,12 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(3))) void k_
   if (!rbk.block(0, &r0, &r1)) return;
   RefineMax rmx;
   const int q0 = ql, q1 = ql + 4;  // this lane's rows of K
+  // With a bin-A bound of 8 the residual that passes the stopping test is still
+  // taken off.  That bound had a solver of eight lanes whose first correction
+  // came unchecked; this one's test alone left up to 1.6e-14 of a row where that
+  // left 1.6e-16 (300^2 five-point, eps = 1, distance 2; now 1.3e-16).  About 3 us
+  // of 175 on 16 matrices of 129^2 to 515^2.
+  const bool last = w.GA == 8;
   ChunkCursor cc;
 
   PendingLinks pend;
@@ -339,8 +345,10 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(3))) void k_
           for (int p = 0; p < 4; ++p) r = fma(-kq[p], qbd(z, p), r);
           const double rn = qmaxd(fabs(r));
           const double zn = qmaxd(fabs(z));
-          if (rn <= 0x1p-47 * (knorm * zn + fnorm)) { conv = true; break; }
+          conv = rn <= 0x1p-47 * (knorm * zn + fnorm);
+          if (conv && !last) break;
           z += (double)solve4((float)(r * scale));
+          if (conv) break;
         }
         conv = conv && (z == z);
         conv = qori(conv ? 0 : 1) == 0;
@@ -452,11 +460,13 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(3))) void k_
         }
         const double rn = qmaxd(fmax(fabs(r0), fabs(r1)));
         const double zn = qmaxd(fmax(fabs(z0), fabs(z1)));
-        if (rn <= 0x1p-47 * (knorm * zn + fnorm)) { conv = true; break; }
+        conv = rn <= 0x1p-47 * (knorm * zn + fnorm);
+        if (conv && !last) break;
         float d0, d1;
         solve((float)(r0 * scale), (float)(r1 * scale), &d0, &d1);
         z0 += (double)d0;
         z1 += (double)d1;
+        if (conv) break;
       }
       conv = conv && (z0 == z0) && (z1 == z1);
       conv = qori(conv ? 0 : 1) == 0;

@@ -46,3 +46,44 @@ def test_larger_blocks_in_an_asynchronous_call(group, seen, then):
             st, infos = ctx.info(1, outs)
             assert st == 0 and infos[0]["n_fp64_rows"] == 0
             assert_matches_oracle(p, _host(outs[0]), o, infos[0])
+
+
+def _row_bounds(p, g):
+    """(error, bound) of every non-empty row of an unconstrained g: the distance
+    to the row's solution in extended precision, and the forward error that one
+    FP64 residual's rounding allows, (s + 2) 2^-53 |K^-1| (|K| |z| + |f|)."""
+    import scipy.sparse as sp
+
+    M = sp.csr_matrix((p.val, p.col_idx, p.row_ptr), shape=(p.n, p.n))
+    C = np.nonzero(p.cf)[0]
+    err, bound = [], []
+    for r in range(g["n_c"]):
+        cols, z = (g[k][g["row_ptr"][r]:g["row_ptr"][r + 1]] for k in ("col_idx", "val"))
+        N, z = cols[cols != C[r]], z[cols != C[r]]
+        if not N.size:
+            continue
+        K, f = M[N][:, N].toarray().T, -M[C[r]][:, N].toarray().ravel()
+        inv = np.linalg.inv(K)
+        x = (inv @ f).astype(np.longdouble)
+        for _ in range(4):
+            x = x + inv @ (f - K.astype(np.longdouble) @ x).astype(np.float64)
+        x64 = np.abs(x.astype(np.float64))
+        err.append(float(np.abs(z - x).max()))
+        bound.append((N.size + 2) * 2.0**-53 * (np.abs(inv) @ (np.abs(K) @ x64 + np.abs(f))).max())
+    return np.array(err), np.array(bound)
+
+
+@pytest.mark.parametrize("case", ["diffusive", "4", "8"])
+def test_rows_of_the_default_group_to_a_residual_rounding(case):
+    """Rows of up to 8 points with a bin-A bound of 8 (the default): off by no more
+    than the rounding of one FP64 residual, whatever the residual that passed the
+    stopping test was."""
+    from paper_2307_00229_amd import clair
+
+    p = P.small_2d(61, stencil=5, eps=1.0, ell=2) if case == "diffusive" else _groups([int(case)] * 200, 9, 4)
+    p.B = None
+    As, cfs, _, ells = to_device([p])
+    outs, infos, st = clair.clair_build_R_batched(As, cfs, None, ells, ctx=clair.Context())
+    assert st == 0 and infos[0]["n_fp64_rows"] == 0 and infos[0]["max_block"] <= 8
+    err, bound = _row_bounds(p, _host(outs[0]))
+    assert np.all(err <= bound), float((err / bound).max())
