@@ -65,11 +65,6 @@ __device__ __forceinline__ double quads_maxd(double v) {
   v = fmax(v, gpartd<8>(v));
   return v;
 }
-__device__ __forceinline__ float quads_maxf(float v) {
-  v = fmaxf(v, __int_as_float(gpart<4>(__float_as_int(v))));
-  v = fmaxf(v, __int_as_float(gpart<8>(__float_as_int(v))));
-  return v;
-}
 
 template <int T>
 struct TileBuf {
@@ -90,8 +85,16 @@ __device__ __forceinline__ int by_group(int q) { return (q & 3) * 8 + (q >> 2); 
 // pivot row subtracts (1 - 1/pivot) of itself, which scales it; the pivot
 // column's lanes take u = pivot + 1, so that a column entry x becomes
 // x - x / pivot (pivot + 1) = -x / pivot and the pivot itself 1 / pivot (the
-// block is scaled to at most 1, so nothing cancels beyond FP32 rounding, and
-// the FP64 refinement decides what is good enough).
+// block is scaled to at most 1, so this costs a rounding or two of FP32).
+//
+// What that leaves in a row: the FP64 refinement stops at a residual of
+// 2^-47 (|K| |z| + |f|), as in the solver of one lane per block row before, and
+// which residual first passes depends on how the inverse is rounded.  The same
+// largest error of a row on both sides, 2 to 5e-14, and either is the better
+// one: root mean squares before and here 4.8e-15 and 6.3e-15 (dominant random
+// blocks of 24 points), 3.8e-16 and 1.2e-15 (40^3 seven-point, eps = 0.1),
+// 1.2e-14 and 3.2e-15 (the same, eps = 1e-4), 1.7e-14 and 2.6e-15 (200^2
+// nine-point, eps = 1e-4).
 template <int T, int AK, int RK>
 __device__ __forceinline__ void tile_step(float (&kf)[T][T], int r, int c, int& bad) {
   float u[T];
@@ -325,22 +328,22 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(T <= 5 ? 3 :
     frexp(bad || s == 0 ? 1.0 : amax, &ex);
     const double scale = ldexp(1.0, -ex);
     float kf[T][T];
-    float norm = 0.f;  // largest row sum of the scaled block
+    double knorm = 0.0;  // largest row sum of the block, for the stopping test: in FP64
 #pragma unroll
     for (int a = 0; a < T; ++a) {
-      float rs = 0.f;
+      double rs = 0.0;
 #pragma unroll
       for (int b = 0; b < T; ++b) {
         kf[a][b] = (float)(K[a][b] * scale);
-        rs += fabsf(kf[a][b]);
+        rs += fabs(K[a][b]);
       }
-      norm = fmaxf(norm, quad_sum(rs));
+      knorm = fmax(knorm, quad_sum(rs));
     }
+    knorm = quads_maxd(knorm);
     // identity on the padding (its rows of the FP64 block stay zero)
 #pragma unroll
     for (int a = 0; a < T; ++a)
       if (r == c && 4 * a + r >= s) kf[a][a] = 1.f;
-    const double knorm = ldexp((double)quads_maxf(norm), ex);
     tile_steps<T, 0>(kf, r, c, s, bad);
     bad = group_ori<16>(bad);
 
