@@ -280,14 +280,45 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(T <= 5 ? 3 :
 #pragma unroll
       for (int j = 0; j < NR + NL; ++j) { at[j] = -1; av[j] = 0.0; }
     }
-    // entries beyond the ninth (read again in each half)
-    auto rest = [&](int lo, int hi_) {
+    // entries beyond the ninth, a row of A per lane and four in flight: the first
+    // pass takes those of the first half and marks those of the second in a word
+    // per row (where z will stand), so that the second pass reads no others again;
+    // beyond 64 of them it reads all.  40,000 rows of 24 points whose rows of A
+    // have about 45 entries: 676 us a call with every entry read and located in
+    // both passes, one at a time, 450 here (one lane per block row: 560).
+    uint64_t* later = reinterpret_cast<uint64_t*>(gb.z);
+    auto rest1 = [&]() {
 #pragma unroll
       for (int h = 0; h < NL; ++h) {
-        for (int e = eb[h].x + 9; e < eb[h].y; ++e) {
+        uint64_t m = 0, bit = 1;
+#pragma unroll 1
+        for (int e = eb[h].x + 9; e < eb[h].y; e += 4) {
+          int k[4];
+#pragma unroll
+          for (int t = 0; t < 4; ++t) k[t] = e + t < eb[h].y ? d.ci[e + t] : -1;
+#pragma unroll
+          for (int t = 0; t < 4; ++t) {
+            const int q = find(k[t]);
+            if (q >= 4 * HA) m |= bit;
+            else if (q >= 0) gb.half[q * LD + l + 16 * h] = d.va[e + t];
+            bit <<= 1;
+          }
+        }
+        later[l + 16 * h] = m;
+      }
+    };
+    auto rest2 = [&]() {
+#pragma unroll
+      for (int h = 0; h < NL; ++h) {
+        const int e0 = eb[h].x + 9;
+        const bool all = eb[h].y - e0 > 64;
+        for (uint64_t m = later[l + 16 * h]; m; m &= m - 1) {
+          const int e = e0 + __ffsll((unsigned long long)m) - 1;
+          gb.half[find(d.ci[e]) * LD + l + 16 * h - HALF] = d.va[e];
+        }
+        for (int e = all ? e0 + 64 : eb[h].y; e < eb[h].y; ++e) {
           const int q = find(d.ci[e]);
-          const int a_ = q * LD + l + 16 * h;
-          if (q >= 0 && a_ >= lo && a_ < hi_) gb.half[a_ - lo] = d.va[e];
+          if (q >= 4 * HA) gb.half[q * LD + l + 16 * h - HALF] = d.va[e];
         }
       }
     };
@@ -295,7 +326,7 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(T <= 5 ? 3 :
 #pragma unroll
     for (int j = 0; j < NR + NL; ++j)
       gb.half[(unsigned)at[j] < (unsigned)HALF ? at[j] : HALF + l] = av[j];
-    if (over > 0) rest(0, HALF);
+    if (over > 0) rest1();
     wave_sync();
 #pragma unroll
     for (int a = 0; a < HA; ++a)
@@ -307,7 +338,7 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(T <= 5 ? 3 :
 #pragma unroll
     for (int j = 0; j < NR + NL; ++j)
       gb.half[at[j] >= HALF ? at[j] - HALF : HALF + l] = av[j];
-    if (over > 0) rest(HALF, 2 * HALF);
+    if (over > 0) rest2();
     wave_sync();
 #pragma unroll
     for (int a = HA; a < T; ++a)

@@ -87,3 +87,29 @@ def test_rows_of_the_default_group_to_a_residual_rounding(case):
     assert st == 0 and infos[0]["n_fp64_rows"] == 0 and infos[0]["max_block"] <= 8
     err, bound = _row_bounds(p, _host(outs[0]))
     assert np.all(err <= bound), float((err / bound).max())
+
+
+@pytest.mark.parametrize("extra", [0, 3, 40, 70, 150])
+@pytest.mark.parametrize("top", [12, 16, 20, 24, 28, 32])
+def test_tile_rows_of_long_rows(top, extra):
+    """Blocks of the 4 x 4-grid solver whose rows of A hold up to `extra` entries
+    outside the block, on both sides of it: below and above the nine of the first
+    reads and the 64 that a marking word covers."""
+    import scipy.sparse as sp
+
+    from paper_2307_00229_amd import clair
+
+    p = _groups([top, top - 2, 9, top] * 45, 31 + top, 31)
+    rng = np.random.default_rng(extra)
+    M = sp.csr_matrix((p.val, p.col_idx, p.row_ptr), shape=(p.n, p.n))
+    F, C = np.nonzero(p.cf == 0)[0], np.nonzero(p.cf)[0]
+    cols = np.concatenate([rng.choice(C, extra, replace=False) for _ in F]) if extra else np.zeros(0, int)
+    X = sp.coo_matrix((-rng.uniform(0.01, 0.1, cols.size), (np.repeat(F, extra), cols)), shape=M.shape).tocsr()
+    M = (M + X + sp.diags(np.asarray(abs(X).sum(axis=1)).ravel())).tocsr()
+    M.sort_indices()
+    p = P.Problem(f"long_{top}_{extra}", p.n, M.indptr.astype(np.int32), M.indices.astype(np.int32), M.data, p.cf,
+                  p.B, 1)
+    As, cfs, Bs, ells = to_device([p])
+    outs, infos, st = clair.clair_build_R_batched(As, cfs, Bs, ells, ctx=clair.Context())
+    assert st == 0 and infos[0]["max_block"] == top
+    assert_matches_oracle(p, _host(outs[0]), oracle.build_R_problem(p), infos[0])
