@@ -727,15 +727,14 @@ __global__ __launch_bounds__(kNT) void k_count(Work w) {
 // matrix has one); larger rows are left unsized for k_count_big.  Then the
 // chunk's bookkeeping.
 //
-// Bound: latency at two wavefronts per SIMD (the register set).  A chunk of
-// 1024 points has 114 to 256 rows, so workgroups of 128 threads keep their
-// wavefronts busy (with 256, half of each workgroup's waited):
-// 2048^2 nine-point rows 251 -> 230 us, 128^3 seven-point 81 -> 70 us, measured
-// while this kernel sized them (k_count does now).  (A set in LDS shared by
-// sixteen lanes per row, as in k_count_wide, took 222 and 93.)
-constexpr int kMT = 128;
+// Bound: latency at two wavefronts per SIMD (the register set).  Workgroups of
+// 256 threads size a chunk's rows (114 to 256 of 1024 points) in one turn: with
+// 128 threads 1024^2 nine-point rows at distance 1 took 65 us for every second
+// point a C-point and 53 for every third, 50 and 45 so; 80^3 seven-point rows at
+// distance 2 without the adjacency 283 and 242 us a call.  (128 are better where a
+// chunk has few rows: 48 of 24 points, 80 us against 97.)
 template <int W>
-__global__ __launch_bounds__(kMT) void k_count_mid(Work w) {
+__global__ __launch_bounds__(kNT) void k_count_mid(Work w) {
   __shared__ int s_rows[kMaxChunk];
   __shared__ int16_t s_size[kMaxChunk];
   __shared__ int s_scan[kNT];
@@ -757,7 +756,7 @@ __global__ __launch_bounds__(kMT) void k_count_mid(Work w) {
   const int nc = w.chunk_nc[c];
   if (tid == 0) { s_flag[0] = 0; s_flag[1] = 0; s_flag[2] = 0; s_flag[3] = 0; s_nlist = 0; }
   __syncthreads();
-  for (int t = tid; t < nc; t += kMT) {
+  for (int t = tid; t < nc; t += kNT) {
     s_rows[t] = w.clocal[base + t];
     const int sz = w.lnz[base + t];
     s_size[t] = (int16_t)sz;
@@ -767,7 +766,7 @@ __global__ __launch_bounds__(kMT) void k_count_mid(Work w) {
   const int SA = slot_stride(w.GA);
   const int lim = small_limit(w.GA);
   const int nl = s_nlist;
-  for (int k = tid; k < nl; k += kMT) {
+  for (int k = tid; k < nl; k += kNT) {
     const int t = s_list[k];
     const int i = s_rows[t];
     RegSetA<32> S;
@@ -2317,7 +2316,7 @@ hipError_t launch_count(const Work& w, hipStream_t s) {
 
 hipError_t launch_count_mid(const Work& w, int blocks, hipStream_t s) {
   if (w.nchunks == 0) return hipSuccess;
-  const dim3 grid(std::min(w.nchunks, std::max(1, blocks))), block(kMT);
+  const dim3 grid(std::min(w.nchunks, std::max(1, blocks))), block(kNT);
   if (w.adj_w == 0) hipLaunchKernelGGL(k_count_mid<0>, grid, block, 0, s, w);
   else if (w.adj_w == 4) hipLaunchKernelGGL(k_count_mid<4>, grid, block, 0, s, w);
   else if (w.adj_w == 8) hipLaunchKernelGGL(k_count_mid<8>, grid, block, 0, s, w);
