@@ -288,33 +288,53 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(T <= 5 ? 3 :
     // both passes, one at a time, 450 here (one lane per block row: 560).
     uint64_t* later = reinterpret_cast<uint64_t*>(gb.z);
     auto rest1 = [&]() {
-#pragma unroll
-      for (int h = 0; h < NL; ++h) {
-        uint64_t m = 0, bit = 1;
+      uint64_t m[NL] = {};
 #pragma unroll 1
-        for (int e = eb[h].x + 9; e < eb[h].y; e += 4) {
-          int k[4];
+      for (int o = 0; o < over; o += 4) {
+        int k[NL][4];
 #pragma unroll
-          for (int t = 0; t < 4; ++t) k[t] = e + t < eb[h].y ? d.ci[e + t] : -1;
+        for (int h = 0; h < NL; ++h)
 #pragma unroll
           for (int t = 0; t < 4; ++t) {
-            const int q = find(k[t]);
-            if (q >= 4 * HA) m |= bit;
-            else if (q >= 0) gb.half[q * LD + l + 16 * h] = d.va[e + t];
-            bit <<= 1;
+            const int e = eb[h].x + 9 + o + t;
+            k[h][t] = e < eb[h].y ? d.ci[e] : -1;
           }
-        }
-        later[l + 16 * h] = m;
+#pragma unroll
+        for (int h = 0; h < NL; ++h)
+#pragma unroll
+          for (int t = 0; t < 4; ++t) {
+            const int q = find(k[h][t]);
+            if (q >= 4 * HA) { if (o + t < 64) m[h] |= 1ull << (o + t); }
+            else if (q >= 0) gb.half[q * LD + l + 16 * h] = d.va[eb[h].x + 9 + o + t];
+          }
       }
+#pragma unroll
+      for (int h = 0; h < NL; ++h) later[l + 16 * h] = m[h];
     };
     auto rest2 = [&]() {
 #pragma unroll
       for (int h = 0; h < NL; ++h) {
         const int e0 = eb[h].x + 9;
         const bool all = eb[h].y - e0 > 64;
-        for (uint64_t m = later[l + 16 * h]; m; m &= m - 1) {
-          const int e = e0 + __ffsll((unsigned long long)m) - 1;
-          gb.half[find(d.ci[e]) * LD + l + 16 * h - HALF] = d.va[e];
+        for (uint64_t m = later[l + 16 * h]; m;) {
+          int k[2];
+          double x[2];
+#pragma unroll
+          for (int t = 0; t < 2; ++t) {
+            k[t] = -1;
+            x[t] = 0.0;
+            if (m) {
+              const int e = e0 + __ffsll((unsigned long long)m) - 1;
+              k[t] = d.ci[e];
+              x[t] = d.va[e];
+            }
+            m &= m - 1;
+          }
+#pragma unroll
+          for (int t = 0; t < 2; ++t) {
+            const int q = find(k[t]);
+            if (q >= 0) gb.half[q * LD + l + 16 * h - HALF] = x[t];
+          }
         }
         for (int e = all ? e0 + 64 : eb[h].y; e < eb[h].y; ++e) {
           const int q = find(d.ci[e]);
