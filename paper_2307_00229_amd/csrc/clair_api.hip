@@ -116,7 +116,7 @@ Layout make_layout(int nmat, int nchunks, int64_t n_total, int GA, bool any_agg,
   L.agg_cnt = take(sizeof(int32_t) * (na + 1));
   L.agg_rp = take(sizeof(int32_t) * (na + 2));
   L.agg_list = take(sizeof(int32_t) * (na + 1));
-  L.agg_sums = take(sizeof(int32_t) * (na / 1024 + 4));
+  L.agg_sums = take(sizeof(int32_t) * scan_scratch_ints((int)na));
   L.fadj = take(sizeof(int32_t) * (adj_w ? n_total * adj_w : 1));
   L.midq = take(sizeof(int32_t) * (nchunks + 1));
   L.total = o;

@@ -4,7 +4,7 @@
 // setup, and the transpose of its result.  Rows of the output are sorted by
 // column like every CSR array of the library.  Stages: column counts
 // (integer atomics) -> exclusive scan (per-block scans, then every block adds
-// the totals before it) -> scatter (the counts, counted down) -> sort of each
+// the totals before it, scanned themselves where there are many) -> scatter (the counts, counted down) -> sort of each
 // output row (the scatter order within a column is arbitrary).  Values are
 // copied, so the transpose is exact.
 //
@@ -33,6 +33,11 @@ __global__ void k_t_zero(int32_t* a, int n) {
   for (int j = blockIdx.x * kTT + threadIdx.x; j < n; j += gridDim.x * kTT) a[j] = 0;
 }
 
+// Up to so many blocks each sums the totals before its own (k_t_scan_add); above,
+// the totals are scanned in turn, as the former's reads grow with their square.  A
+// transpose of a diagonal of 2^21 entries 69 us so and 79 with the totals scanned,
+// 2^23: 164 and 163, 2^24: 320 and 284, 2^27: 4,430 and 2,243.
+constexpr int kTFlat = 8192;
 constexpr int kTB = 8;  // entries of a row a thread has in flight
 constexpr int kTS = 8;  // output rows of up to kTS entries are sorted in registers
 
@@ -97,6 +102,17 @@ __global__ __launch_bounds__(kTT) void k_t_scan_add(int32_t* out, int n, const i
   for (int k = 0; k < kTPer; ++k)
     if (j0 + k * kTT < n) out[j0 + k * kTT] += base;
   if (b == nb - 1 && threadIdx.x == 0) out[n] = base + sums[b];
+}
+
+// the same with the totals already scanned (sums[nb] the sum of all)
+__global__ __launch_bounds__(kTT) void k_t_scan_shift(int32_t* out, int n, const int32_t* sums, int nb) {
+  const int b = blockIdx.x;
+  const int base = sums[b];
+  const int j0 = b * kTBlk + threadIdx.x;
+#pragma unroll
+  for (int k = 0; k < kTPer; ++k)
+    if (j0 + k * kTT < n) out[j0 + k * kTT] += base;
+  if (b == nb - 1 && threadIdx.x == 0) out[n] = sums[nb];
 }
 
 __global__ void k_t_scan_none(int32_t* out) { out[0] = 0; }
@@ -171,9 +187,13 @@ int grid_for(int n, int cus) { return std::max(1, std::min((n + kTT - 1) / kTT, 
 
 }  // namespace
 
-size_t transpose_scratch_ints(int ncol) { return (size_t)ncol + (size_t)(ncol / kTBlk + 2) + 1; }
+size_t transpose_scratch_ints(int ncol) { return (size_t)ncol + 1 + scan_scratch_ints(ncol); }
 
-size_t scan_scratch_ints(int n) { return (size_t)(n / kTBlk + 2); }
+// block totals and their sum; the totals of blocks of those
+size_t scan_scratch_ints(int n) {
+  const size_t nb = (size_t)n / kTBlk + 1;
+  return nb + 1 + nb / kTBlk + 1;
+}
 
 hipError_t launch_exclusive_scan(const int32_t* cnt, int n, int32_t* out, int32_t* sums, int cus, hipStream_t s) {
   (void)cus;
@@ -183,6 +203,12 @@ hipError_t launch_exclusive_scan(const int32_t* cnt, int n, int32_t* out, int32_
     return hipGetLastError();
   }
   hipLaunchKernelGGL(k_t_scan_blocks, dim3(nb), dim3(kTT), 0, s, cnt, n, out, sums);
+  if (nb > kTFlat) {  // (once: 2^31 entries are 2^21 blocks, 2^11 blocks of those)
+    hipError_t e = launch_exclusive_scan(sums, nb, sums, sums + nb + 1, cus, s);
+    if (e != hipSuccess) return e;
+    hipLaunchKernelGGL(k_t_scan_shift, dim3(nb), dim3(kTT), 0, s, out, n, sums, nb);
+    return hipGetLastError();
+  }
   hipLaunchKernelGGL(k_t_scan_add, dim3(nb), dim3(kTT), 0, s, out, n, sums, nb);
   return hipGetLastError();
 }

@@ -113,3 +113,21 @@ def test_tile_rows_of_long_rows(top, extra):
     outs, infos, st = clair.clair_build_R_batched(As, cfs, Bs, ells, ctx=clair.Context())
     assert st == 0 and infos[0]["max_block"] == top
     assert_matches_oracle(p, _host(outs[0]), oracle.build_R_problem(p), infos[0])
+
+
+@pytest.mark.parametrize("blocks,left", [(8191, 1), (8192, 0), (8192, 1), (8200, 1023)])
+def test_scans_of_many_blocks(blocks, left):
+    """Column pointers over as many blocks of 1,024 columns as one kernel sums
+    for itself, and over more (the blocks' totals are then scanned in turn)."""
+    from paper_2307_00229_amd import clair
+
+    ncol, m, w = 1024 * blocks + left, 200, 5000
+    rng = np.random.default_rng(blocks + left)
+    cols = np.sort(rng.integers(0, ncol // w, (m, w)) + np.arange(w) * (ncol // w), axis=1).astype(np.int32)
+    cols[-1, -1] = ncol - 1
+    A = clair.CSR(torch.arange(0, m * w + 1, w, dtype=torch.int32).cuda(), torch.from_numpy(cols.ravel()).cuda(),
+                  torch.from_numpy(rng.uniform(1, 2, m * w)).cuda())
+    rp, ci, va = (x.cpu().numpy() for x in clair.clair_transpose(A, ncol))
+    order = np.argsort(cols.ravel(), kind="stable")
+    assert np.array_equal(rp, np.concatenate([[0], np.cumsum(np.bincount(cols.ravel(), minlength=ncol))]))
+    assert np.array_equal(ci, (order // w).astype(np.int32)) and np.array_equal(va, A.val.cpu().numpy()[order])
