@@ -1124,7 +1124,6 @@ int clair_build_R(const clair_csr_t* A, const int8_t* cf, const double* B, int32
 
 namespace {
 
-// B = A^T (A: m x ncol) into device arrays of sufficient size; synchronous
 // row_ptr[0] == 0 and row_ptr[m] == nnz on the device (the buffers that
 // follow are sized from nnz, the kernels follow row_ptr); synchronous
 int check_row_ptr_ends(clair_ctx* c, const int32_t* rp, int32_t m, int64_t nnz, hipStream_t s) {
@@ -1137,23 +1136,24 @@ int check_row_ptr_ends(clair_ctx* c, const int32_t* rp, int32_t m, int64_t nnz, 
 
 // Enqueues A^T and sends the transpose's flag to word `at` of c->small: A is
 // invalid if transpose_bad(c, at) once the stream has been synchronised (the
-// result can be walked in any case, see launch_transpose).
+// result can be walked in any case or, with keep, is left as it was: see
+// launch_transpose).
 constexpr int kFlagAt = 64;  // beyond the words other reads use
 int transpose_enqueue(clair_ctx* c, const clair_csr_t& A, int32_t ncol, int32_t* trp, int32_t* tci, double* tva,
-                      hipStream_t s, int at = kFlagAt) {
+                      hipStream_t s, bool keep = false, int at = kFlagAt) {
   if (A.n <= 0 && A.nnz != 0) return CLAIR_ERR_INVALID;
   const size_t ints = transpose_scratch_ints(ncol);
   HIPCHK(c->t_scratch.ensure(sizeof(int32_t) * ints));
   int32_t* scr = static_cast<int32_t*>(c->t_scratch.p);
-  HIPCHK(launch_transpose(A.n, ncol, A.nnz, A.row_ptr, A.col_idx, A.val, trp, tci, tva, scr, c->cus, s));
+  HIPCHK(launch_transpose(A.n, ncol, A.nnz, A.row_ptr, A.col_idx, A.val, trp, tci, tva, scr, c->cus, s, keep));
   COLLECT(scr + ncol, 1, nullptr, 0, nullptr, 0, nullptr, 0, at);
   return CLAIR_OK;
 }
 bool transpose_bad(clair_ctx* c, int at = kFlagAt) { return small_words(c)[at] != 0; }
 
 int transpose_into(clair_ctx* c, const clair_csr_t& A, int32_t ncol, int32_t* trp, int32_t* tci, double* tva,
-                   hipStream_t s) {
-  if (int rc = transpose_enqueue(c, A, ncol, trp, tci, tva, s)) return rc;
+                   hipStream_t s, bool keep = false) {
+  if (int rc = transpose_enqueue(c, A, ncol, trp, tci, tva, s, keep)) return rc;
   HIPCHK(hipStreamSynchronize(s));
   return transpose_bad(c) ? CLAIR_ERR_INVALID : CLAIR_OK;
 }
@@ -1176,7 +1176,8 @@ int clair_transpose(clair_ctx_t* c, const clair_csr_t* A, int32_t ncol, clair_cs
       (A->nnz > 0 && (!AT->col_idx || !AT->val)))
     return CLAIR_ERR_CAPACITY;
   try {
-    return transpose_into(c, *A, ncol, AT->row_ptr, AT->col_idx, AT->val, static_cast<hipStream_t>(stream));
+    // (an invalid A leaves the arrays of AT as they are)
+    return transpose_into(c, *A, ncol, AT->row_ptr, AT->col_idx, AT->val, static_cast<hipStream_t>(stream), true);
   } catch (...) {
     return CLAIR_ERR_NOMEM;
   }

@@ -59,14 +59,17 @@ hipError_t launch_copy_unless(const int32_t* flag, const double* src, double* ds
 // transpose_scratch_ints(ncol) ints (column counts, a flag set to 1 for an
 // index outside [0, ncol) or row pointers that do not run from 0 to nnz, block
 // totals).  With the flag set the result is still a CSR array that can be
-// walked (skipped entries are left out; none at all for bad row pointers).
+// walked (skipped entries are left out; none at all for bad row pointers), or,
+// with keep, not written at all.
 size_t transpose_scratch_ints(int ncol);
 hipError_t launch_transpose(int m, int ncol, int64_t nnz, const int32_t* rp, const int32_t* ci, const double* va, int32_t* trp,
-                            int32_t* tci, double* tva, int32_t* scratch, int cus, hipStream_t s);
+                            int32_t* tci, double* tva, int32_t* scratch, int cus, hipStream_t s, bool keep = false);
 
-// out[0..n) = exclusive prefix of cnt, out[n] = total; sums: scan_scratch_ints(n)
+// out[0..n) = exclusive prefix of cnt, out[n] = total; sums: scan_scratch_ints(n);
+// with *stop set (when given) nothing is written
 size_t scan_scratch_ints(int n);
-hipError_t launch_exclusive_scan(const int32_t* cnt, int n, int32_t* out, int32_t* sums, int cus, hipStream_t s);
+hipError_t launch_exclusive_scan(const int32_t* cnt, int n, int32_t* out, int32_t* sums, int cus, hipStream_t s,
+                                 const int32_t* stop = nullptr);
 
 // sparse product C = X Y (X: m rows, Y: k x ny), one wavefront per row of C.
 // Symbolic: cnt[i] = distinct columns of row i; flags (4 ints, zeroed by the

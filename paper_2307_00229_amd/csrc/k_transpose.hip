@@ -66,8 +66,10 @@ __global__ __launch_bounds__(kTT) void k_t_count(int m, int ncol, int64_t nnz, c
 }
 
 // exclusive scan of cnt[0..n) into out[0..n), per block of kTBlk entries;
-// block totals to sums[b]
-__global__ __launch_bounds__(kTT) void k_t_scan_blocks(const int32_t* cnt, int n, int32_t* out, int32_t* sums) {
+// block totals to sums[b].  (stop: nothing is written when it is given and set)
+__global__ __launch_bounds__(kTT) void k_t_scan_blocks(const int32_t* cnt, int n, int32_t* out, int32_t* sums,
+                                                       const int32_t* stop) {
+  if (stop && *stop) return;
   __shared__ int sh[kTT / 64];
   const int base = blockIdx.x * kTBlk + threadIdx.x * kTPer;
   int v[kTPer];
@@ -90,7 +92,9 @@ __global__ __launch_bounds__(kTT) void k_t_scan_blocks(const int32_t* cnt, int n
 // out[j] += the totals of the blocks before j's; out[n] = the sum of all
 // nb blocks (one workgroup per block; each sums the totals it needs, so no
 // kernel of one workgroup stands between the two)
-__global__ __launch_bounds__(kTT) void k_t_scan_add(int32_t* out, int n, const int32_t* sums, int nb) {
+__global__ __launch_bounds__(kTT) void k_t_scan_add(int32_t* out, int n, const int32_t* sums, int nb,
+                                                    const int32_t* stop) {
+  if (stop && *stop) return;
   __shared__ int sh[kTT / 64];
   const int b = blockIdx.x;
   int my = 0;
@@ -105,7 +109,9 @@ __global__ __launch_bounds__(kTT) void k_t_scan_add(int32_t* out, int n, const i
 }
 
 // the same with the totals already scanned (sums[nb] the sum of all)
-__global__ __launch_bounds__(kTT) void k_t_scan_shift(int32_t* out, int n, const int32_t* sums, int nb) {
+__global__ __launch_bounds__(kTT) void k_t_scan_shift(int32_t* out, int n, const int32_t* sums, int nb,
+                                                      const int32_t* stop) {
+  if (stop && *stop) return;
   const int b = blockIdx.x;
   const int base = sums[b];
   const int j0 = b * kTBlk + threadIdx.x;
@@ -115,15 +121,17 @@ __global__ __launch_bounds__(kTT) void k_t_scan_shift(int32_t* out, int n, const
   if (b == nb - 1 && threadIdx.x == 0) out[n] = sums[nb];
 }
 
-__global__ void k_t_scan_none(int32_t* out) { out[0] = 0; }
+__global__ void k_t_scan_none(int32_t* out, const int32_t* stop) {
+  if (!stop || !*stop) out[0] = 0;
+}
 
 // scatter: entry (i, j) to out row j at trp[j] + the column's count, counted
 // down (a skipped index was never counted)
 __global__ __launch_bounds__(kTT) void k_t_fill(int m, int ncol, int64_t nnz, const int32_t* __restrict__ rp,
                                                 const int32_t* __restrict__ ci, const double* __restrict__ va,
                                                 const int32_t* __restrict__ trp, int32_t* left, int32_t* tci,
-                                                double* tva) {
-  if (rp[0] != 0 || rp[m] != nnz) return;
+                                                double* tva, const int32_t* stop) {
+  if (rp[0] != 0 || rp[m] != nnz || (stop && *stop)) return;
   for (int i = blockIdx.x * kTT + threadIdx.x; i < m; i += gridDim.x * kTT) {
     const int e1 = rp[i + 1];
     for (int e = rp[i]; e < e1; e += kTB) {
@@ -147,7 +155,9 @@ __global__ __launch_bounds__(kTT) void k_t_fill(int m, int ncol, int64_t nnz, co
 // sort every output row by column: rows of up to kTS entries in registers
 // (every entry goes to its rank; equal columns keep their order), longer rows
 // by insertion in place
-__global__ __launch_bounds__(kTT) void k_t_sort(int ncol, const int32_t* __restrict__ trp, int32_t* tci, double* tva) {
+__global__ __launch_bounds__(kTT) void k_t_sort(int ncol, const int32_t* __restrict__ trp, int32_t* tci, double* tva,
+                                                const int32_t* stop) {
+  if (stop && *stop) return;
   for (int j = blockIdx.x * kTT + threadIdx.x; j < ncol; j += gridDim.x * kTT) {
     const int e0 = trp[j], e1 = trp[j + 1];
     if (e1 - e0 <= 1) continue;
@@ -195,36 +205,39 @@ size_t scan_scratch_ints(int n) {
   return nb + 1 + nb / kTBlk + 1;
 }
 
-hipError_t launch_exclusive_scan(const int32_t* cnt, int n, int32_t* out, int32_t* sums, int cus, hipStream_t s) {
+hipError_t launch_exclusive_scan(const int32_t* cnt, int n, int32_t* out, int32_t* sums, int cus, hipStream_t s,
+                                 const int32_t* stop) {
   (void)cus;
   const int nb = (n + kTBlk - 1) / kTBlk;
   if (nb == 0) {
-    hipLaunchKernelGGL(k_t_scan_none, dim3(1), dim3(1), 0, s, out);
+    hipLaunchKernelGGL(k_t_scan_none, dim3(1), dim3(1), 0, s, out, stop);
     return hipGetLastError();
   }
-  hipLaunchKernelGGL(k_t_scan_blocks, dim3(nb), dim3(kTT), 0, s, cnt, n, out, sums);
+  hipLaunchKernelGGL(k_t_scan_blocks, dim3(nb), dim3(kTT), 0, s, cnt, n, out, sums, stop);
   if (nb > kTFlat) {  // (once: 2^31 entries are 2^21 blocks, 2^11 blocks of those)
-    hipError_t e = launch_exclusive_scan(sums, nb, sums, sums + nb + 1, cus, s);
+    hipError_t e = launch_exclusive_scan(sums, nb, sums, sums + nb + 1, cus, s, stop);
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(k_t_scan_shift, dim3(nb), dim3(kTT), 0, s, out, n, sums, nb);
+    hipLaunchKernelGGL(k_t_scan_shift, dim3(nb), dim3(kTT), 0, s, out, n, sums, nb, stop);
     return hipGetLastError();
   }
-  hipLaunchKernelGGL(k_t_scan_add, dim3(nb), dim3(kTT), 0, s, out, n, sums, nb);
+  hipLaunchKernelGGL(k_t_scan_add, dim3(nb), dim3(kTT), 0, s, out, n, sums, nb, stop);
   return hipGetLastError();
 }
 
 hipError_t launch_transpose(int m, int ncol, int64_t nnz, const int32_t* rp, const int32_t* ci, const double* va,
-                            int32_t* trp, int32_t* tci, double* tva, int32_t* scratch, int cus, hipStream_t s) {
+                            int32_t* trp, int32_t* tci, double* tva, int32_t* scratch, int cus, hipStream_t s,
+                            bool keep) {
   int32_t* left = scratch;
   int32_t* bad = scratch + ncol;
+  const int32_t* stop = keep ? bad : nullptr;
   int32_t* sums = scratch + ncol + 1;
   hipLaunchKernelGGL(k_t_zero, dim3(grid_for(ncol + 1, cus)), dim3(kTT), 0, s, left, ncol + 1);
   if (m > 0) hipLaunchKernelGGL(k_t_count, dim3(grid_for(m, cus)), dim3(kTT), 0, s, m, ncol, nnz, rp, ci, left, bad);
-  hipError_t e = launch_exclusive_scan(left, ncol, trp, sums, cus, s);
+  hipError_t e = launch_exclusive_scan(left, ncol, trp, sums, cus, s, stop);
   if (e != hipSuccess) return e;
   if (m > 0)
-    hipLaunchKernelGGL(k_t_fill, dim3(grid_for(m, cus)), dim3(kTT), 0, s, m, ncol, nnz, rp, ci, va, trp, left, tci, tva);
-  if (ncol > 0) hipLaunchKernelGGL(k_t_sort, dim3(grid_for(ncol, cus)), dim3(kTT), 0, s, ncol, trp, tci, tva);
+    hipLaunchKernelGGL(k_t_fill, dim3(grid_for(m, cus)), dim3(kTT), 0, s, m, ncol, nnz, rp, ci, va, trp, left, tci, tva, stop);
+  if (ncol > 0) hipLaunchKernelGGL(k_t_sort, dim3(grid_for(ncol, cus)), dim3(kTT), 0, s, ncol, trp, tci, tva, stop);
   return hipGetLastError();
 }
 

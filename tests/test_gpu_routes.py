@@ -131,3 +131,47 @@ def test_scans_of_many_blocks(blocks, left):
     order = np.argsort(cols.ravel(), kind="stable")
     assert np.array_equal(rp, np.concatenate([[0], np.cumsum(np.bincount(cols.ravel(), minlength=ncol))]))
     assert np.array_equal(ci, (order // w).astype(np.int32)) and np.array_equal(va, A.val.cpu().numpy()[order])
+
+
+@pytest.mark.parametrize("fault", ["start", "end", "column", "below", "no columns"])
+def test_refused_transposes_leave_their_outputs(fault):
+    """Row pointers that do not run from 0 to nnz, and a column out of range:
+    refused, and no output array of the call is written."""
+    import ctypes
+
+    from paper_2307_00229_amd import clair
+
+    lib = clair.load_library()
+    p = P.small_2d(40, stencil=5, ell=1)
+    (A,), (cf,), (B,), _ = to_device([p])
+    M = clair.CSR(A.row_ptr.clone(), A.col_idx.clone(), A.val, n=p.n)
+    if fault == "start":
+        M.row_ptr[0] = 1
+    elif fault == "end":
+        M.row_ptr[p.n] -= 1
+    elif fault != "no columns":
+        M.col_idx[p.nnz // 2] = p.n if fault == "column" else -1
+    ncol = 0 if fault == "no columns" else p.n
+    ctx, mc = clair.Context(), M.c()
+
+    def out():
+        o = clair.ROut(p.n, 4 * p.nnz)
+        for t in (o.row_ptr, o.col_idx, o.val):
+            t.fill_(-7)
+        return o, o.c()
+
+    o, oc = out()
+    assert lib.clair_transpose(ctx.handle, ctypes.byref(mc), ncol, ctypes.byref(oc), None) == 1
+    q, qc = out()
+    s = torch.full_like(B, -7)
+    if fault != "no columns":
+        opts, info = clair.Opts(), clair.Info()
+        assert lib.clair_build_P(ctx.handle, ctypes.byref(mc), cf.data_ptr(), B.data_ptr(), 1, ctypes.byref(qc),
+                                 ctypes.byref(opts), ctypes.byref(info)) == 1
+        assert lib.clair_smooth_B(ctx.handle, ctypes.byref(mc), cf.data_ptr(), B.data_ptr(), s.data_ptr(), 2, 0.6, 1,
+                                  None) == 1
+    torch.cuda.synchronize()
+    for t in (o.row_ptr, o.col_idx, o.val, q.row_ptr, q.col_idx, q.val, s):
+        assert bool((t == -7).all())
+    R = clair.clair_transpose(A, p.n, ctx=ctx)  # the context goes on
+    assert torch.equal(clair.clair_transpose(clair.CSR(*R), p.n, ctx=ctx)[1], A.col_idx)
