@@ -749,13 +749,17 @@ clair_ctx::Hint* find_hint(clair_ctx* c, const clair_ctx::Hint& k) {
   return nullptr;
 }
 
-// A synchronous call in one step on the sizes of `h`; kHintWrong when they are
-// not this call's (R may then hold anything up to its capacities, as before a
-// call that has yet to write it).
+CallSizes call_sizes(int maxb, const Counters& n) {
+  return {maxb, n.nA > 0, n.nB > 0, n.nC > 0, n.nmid > 0, n.nbig > 0};
+}
+
+// A synchronous call in one step on the sizes of `h`; kHintWrong when its
+// launches do not serve this call (R may then hold anything up to its
+// capacities, as before a call that has yet to write it).
 constexpr int kHintWrong = -1;
 int run_mixed_once(clair_ctx* c, int32_t nmat, const clair_csr_t* A, const int8_t* const* cf, const double* const* B,
                    const int32_t* ell, clair_csr_out_t* R, const clair_opts_t* o, clair_info_t* info,
-                   const int32_t* const* agg, const clair_ctx::Hint& h) {
+                   const int32_t* const* agg, clair_ctx::Hint& h) {
   const hipStream_t s = static_cast<hipStream_t>(o ? o->stream : nullptr);
   Batch b;
   int rc = prepare(c, nmat, A, cf, B, ell, R, &b, agg);
@@ -787,9 +791,13 @@ int run_mixed_once(clair_ctx* c, int32_t nmat, const clair_csr_t* A, const int8_
   const Counters& cnt = *host_counters(c, b);
   int maxb = 0;
   for (int m = 0; m < nmat; ++m) maxb = std::max(maxb, hs[m].max_block);
-  const bool same = maxb == h.maxb && (h.cnt.nmid > 0 || cnt.nmid == 0) && (h.cnt.nbig > 0 || cnt.nbig == 0) &&
-                    (h.cnt.nA > 0 || cnt.nA == 0) && (h.cnt.nB > 0 || cnt.nB == 0) && (h.cnt.nC > 0 || cnt.nC == 0);
-  if (!same) return kHintWrong;
+  static_assert(kLdsBlockMax == 64, "launches_hold");
+  if (!launches_hold(call_sizes(h.maxb, h.cnt), call_sizes(maxb, cnt), c->scratch_slots ? c->scratch_stride : 0))
+    return kHintWrong;
+  // (a smaller tile is the faster one: the next call takes it)
+  h.maxb = maxb;
+  c->binB_max = std::max(9, std::min(32, maxb));
+  c->last_maxb = maxb;
   fill_results(hs, nmat, R, info, A);
   return first_error(hs, nmat);
 }
@@ -799,10 +807,11 @@ int run_mixed_once(clair_ctx* c, int32_t nmat, const clair_csr_t* A, const int8_
 // bin-B kernel, the scratch and which queues are empty).  When the last
 // synchronous call of this shape read the same sizes back, the wait between
 // the steps only repeats them: such a call enqueues both steps on what it read
-// then and waits once, checks the sizes it assumed against the ones it finds,
-// and runs again in two steps where they differ (the shape then keeps to two
-// steps).  A call on 32 x 32 takes 55 us, of 75 with the wait, status copies to
-// unpinned memory and an occupancy query per launch.
+// then and waits once, checks the sizes it finds against what it launched, and
+// runs again in two steps where that does not serve them, a larger block or work
+// for a pass left out (the shape then keeps to two steps).  A call on 32 x 32
+// takes 55 us, of 75 with the wait, status copies to unpinned memory and an
+// occupancy query per launch.
 int run_mixed(clair_ctx* c, int32_t nmat, const clair_csr_t* A, const int8_t* const* cf, const double* const* B,
               const int32_t* ell, clair_csr_out_t* R, const clair_opts_t* o, clair_info_t* info,
               const int32_t* const* agg = nullptr) {

@@ -2,6 +2,8 @@
 // knows of.  Plain C++ (no HIP), so that the rules can be checked by themselves.
 #pragma once
 
+#include <stdint.h>
+
 #include <algorithm>
 
 namespace clair {
@@ -27,6 +29,25 @@ inline TilePick tile_pick(int points, int reach, bool sized) {
   const int wide = tile_bound(reach);
   if (sized || first >= wide) return {first, 0};
   return {first, wide};
+}
+
+// What a call's launches were sized for, or what it found: the largest block
+// and whether there were rows of bin A, of bin B, for the workgroup solvers, and
+// unfinished chunks for the two further searches.
+struct CallSizes {
+  int points = 0;
+  bool rows_a = false, rows_b = false, rows_wg = false, mid = false, big = false;
+};
+
+// Whether launches sized for `had` also serve a call that found `got`: no pass
+// was left out that has work, its rows of up to 32 points fit the tile, and the
+// FP64 scratch (scratch_doubles a slot, 0: none) takes its rows above 64 points,
+// which do not fit in LDS.
+inline bool launches_hold(const CallSizes& had, const CallSizes& got, int64_t scratch_doubles) {
+  if ((got.mid && !had.mid) || (got.big && !had.big)) return false;
+  if ((got.rows_a && !had.rows_a) || (got.rows_b && !had.rows_b) || (got.rows_wg && !had.rows_wg)) return false;
+  if (tile_bound(got.points) > tile_bound(had.points)) return false;
+  return got.points <= 64 || (int64_t)got.points * got.points <= scratch_doubles;
 }
 
 // how far an unsized call's bin B reaches: the block bounds 16, 20, 24 and 32
