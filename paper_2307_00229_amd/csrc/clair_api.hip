@@ -305,20 +305,9 @@ int check_args(int32_t nmat, const clair_csr_t* A, const int8_t* const* cf, cons
   return CLAIR_OK;
 }
 
-// Fine points per workgroup: the tuning's, halved while the batch has fewer
-// workgroups than CUs (not below 64).  The chunk-wise passes (symbolic search,
-// projection) then fill the chip on small inputs too; the results do not depend
-// on the chunk.  150^2 at distance 5: its two 22-workgroup passes took 254 us with 1024
-// points (search 124, projection 130) and the projection takes 39 with 64; from
-// about 262,000 points on the chunk is the tuning's own.  (Two workgroups a CU:
-// more of them meet at the matrix's counters and rows take more steps to find
-// their chunk: 330^2 five-point, distance 1, numeric pass 31 and projection 14
-// us against 25 and 12; 40^3 seven-point, projection 19 against 13.)
 int effective_chunk(const clair_ctx* c, int64_t n_total) {
-  int chunk = c->chunk;
-  if (c->fixed) return chunk;  // (its scratch is sized for whole chunks)
-  while (chunk > 64 && n_total < (int64_t)chunk * c->cus) chunk /= 2;
-  return chunk;
+  if (c->fixed) return c->chunk;  // (its scratch is sized for whole chunks)
+  return shrunk_chunk(c->chunk, n_total, c->cus);
 }
 
 int prepare(clair_ctx* c, int32_t nmat, const clair_csr_t* A, const int8_t* const* cf,

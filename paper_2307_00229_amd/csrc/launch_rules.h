@@ -31,6 +31,21 @@ inline TilePick tile_pick(int points, int reach, bool sized) {
   return {first, wide};
 }
 
+// Fine points per workgroup of the chunk-wise passes (symbolic search,
+// projection): the tuning's, halved while the batch has fewer workgroups than
+// CUs, though not below 64.  The passes then fill the chip on small inputs too;
+// the results do not depend on the chunk.  150^2 at distance 5: its two
+// 22-workgroup passes took 254 us with 1024 points (search 124, projection 130)
+// and the projection takes 39 with 64; from about 262,000 points on the chunk is
+// the tuning's own.  (Two workgroups a CU were tried: more of them meet at the
+// matrix's counters and rows take more steps to find their chunk: 330^2
+// five-point, distance 1, numeric pass 31 and projection 14 us against 25 and 12;
+// 40^3 seven-point, projection 19 against 13.)
+inline int shrunk_chunk(int chunk, int64_t n_total, int cus) {
+  while (chunk / 2 >= 64 && n_total < (int64_t)chunk * cus) chunk /= 2;
+  return chunk;
+}
+
 // What a call's launches were sized for, or what it found: the largest block
 // and whether there were rows of bin A, of bin B, for the workgroup solvers, and
 // unfinished chunks for the two further searches.

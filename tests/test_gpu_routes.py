@@ -175,3 +175,28 @@ def test_refused_transposes_leave_their_outputs(fault):
         assert bool((t == -7).all())
     R = clair.clair_transpose(A, p.n, ctx=ctx)  # the context goes on
     assert torch.equal(clair.clair_transpose(clair.CSR(*R), p.n, ctx=ctx)[1], A.col_idx)
+
+
+@pytest.mark.parametrize("chunk", [256, 768, 1280, 1792])
+def test_small_batches_of_odd_chunks(chunk):
+    """Tuned chunks that halve to 64, 96, 80 and 112 points: several start inside
+    one 64-row block of the row lookup, some hold no C-point."""
+    import scipy.sparse as sp
+
+    from paper_2307_00229_amd import clair
+
+    ps = []
+    for n in (1, 79, 80, 81, 95, 97, 1000, 4099):
+        rng = np.random.default_rng(n)
+        M = sp.diags([-rng.uniform(0.2, 1, n), np.full(n, 2.5), -rng.uniform(0.2, 1, n)], [-1, 0, 1], shape=(n, n)).tocsr()
+        cf = ((np.arange(n) % 3 == 1) & ((np.arange(n) // 100) % 2 == 0)) | (n == 1)
+        ps.append(P.Problem(f"line_{n}", n, M.indptr.astype(np.int32), M.indices.astype(np.int32), M.data,
+                            cf.astype(np.int8), rng.uniform(0.5, 1.5, n), 2))
+    ctx = clair.Context()
+    ctx.set_tuning(chunk=chunk)
+    As, cfs, Bs, ells = to_device(ps)
+    for _ in range(2):
+        outs, infos, st = clair.clair_build_R_batched(As, cfs, Bs, ells, ctx=ctx)
+        assert st == 0
+        for p, o, inf in zip(ps, outs, infos):
+            assert_matches_oracle(p, _host(o), oracle.build_R_problem(p), inf)

@@ -28,6 +28,8 @@ int main() {
       std::printf("%d %d\n", p.first, p.second);
     } else if (!std::strcmp(rule, "reach")) {
       std::printf("%d 0\n", bin_b_reach((int)a));
+    } else if (!std::strcmp(rule, "chunk")) {
+      std::printf("%d 0\n", shrunk_chunk((int)a, b, (int)c));
     } else if (!std::strcmp(rule, "hold")) {
       std::printf("%d 0\n", launches_hold(sizes((int)a, (int)b), sizes((int)c, (int)d), e) ? 1 : 0);
     } else {
@@ -81,3 +83,15 @@ def test_sizes_that_launches_serve(ask):
         assert ok == (0 if left_out or beyond_tile or beyond_scratch else 1), (h, hf, g, gf, scratch)
         if g <= h and not left_out and (g <= 64 or h * h <= scratch):
             assert ok == 1
+
+
+def test_chunks_of_small_batches(ask):
+    """Halved while workgroups are fewer than CUs, never below 64 points."""
+    asked = [("chunk", c, n, cus) for c in range(256, 2049, 256) for cus in (64, 256, 304)
+             for n in (1, 63, 5000, 20000, 60000, 130000, 262143, 262144, 10**7)]
+    for (_, chunk, n, cus), (got, _) in zip(asked, ask(asked)):
+        assert got >= 64 and got in [chunk >> k for k in range(6)]
+        if got < chunk:  # each halving was for want of workgroups
+            assert n < (got * 2) * cus
+        if n < got * cus:  # and one more would go below 64
+            assert got // 2 < 64
