@@ -200,3 +200,54 @@ def test_small_batches_of_odd_chunks(chunk):
         assert st == 0
         for p, o, inf in zip(ps, outs, infos):
             assert_matches_oracle(p, _host(o), oracle.build_R_problem(p), inf)
+
+
+@pytest.mark.parametrize("group", [8, 16, 32])
+def test_graph_replays_with_larger_blocks(group):
+    """A captured setup whose values, and with them the blocks, change between
+    replays: 9 points when captured, then 16, on the same buffers."""
+    from paper_2307_00229_amd import clair
+
+    big = _groups([16, 14, 9, 3] * 9, 5, 6)
+    rows = np.repeat(np.arange(big.n), np.diff(big.row_ptr))
+    rank = np.arange(big.nnz) - big.row_ptr[rows]
+    few = np.where((big.cf[rows] != 0) & (rows != big.col_idx) & (rank >= 10), 0.0, big.val)
+    small = P.Problem("few", big.n, big.row_ptr, big.col_idx, few, big.cf, big.B, 1)
+    want = {q.name: oracle.build_R_problem(q) for q in (small, big)}
+    assert np.diff(want["few"]["row_ptr"]).max() <= 12 < np.diff(want[big.name]["row_ptr"]).max()
+    As, cfs, Bs, ells = to_device([small])
+    o = want[big.name]
+    outs = [clair.ROut(o["n_c"], o["nnz"])]
+    ctx = clair.Context()
+    ctx.set_tuning(group=group)
+    stream = torch.cuda.Stream()
+    torch.cuda.synchronize()
+    graph = clair.Graph(ctx, As, cfs, Bs, ells, outs, stream=stream)
+    for q in (small, big, big, small, big):
+        As[0].val.copy_(torch.from_numpy(q.val).cuda())
+        torch.cuda.synchronize()
+        graph.launch(stream=stream)
+        stream.synchronize()
+        st, infos = graph.info()
+        assert st == 0 and infos[0]["n_fp64_rows"] == 0
+        assert_matches_oracle(q, _host(outs[0]), want[q.name], infos[0])
+    graph.close()
+
+
+@pytest.mark.parametrize("top", [9, 12, 13, 16, 17, 20, 21, 24, 25, 28, 29, 32])
+@pytest.mark.parametrize("group", [4, 16, 32])
+def test_tile_rows_of_a_repeated_call(group, top):
+    """The same call three times with its buffers: sizes read back, then known."""
+    from paper_2307_00229_amd import clair
+
+    ctx = clair.Context()
+    ctx.set_tuning(group=group)
+    p = _groups([top, 0, 9, top - 1, 3, top, 10, 8, 1] * 5, 200 + top, 5)
+    As, cfs, Bs, ells = to_device([p, p])
+    o = oracle.build_R_problem(p)
+    for _ in range(3):
+        outs = [clair.ROut(o["n_c"], o["nnz"]) for _ in range(2)]
+        outs, infos, st = clair.clair_build_R_batched(As, cfs, Bs, ells, ctx=ctx, outs=outs)
+        assert st == 0
+        for out, inf in zip(outs, infos):
+            assert_matches_oracle(p, _host(out), o, inf)
