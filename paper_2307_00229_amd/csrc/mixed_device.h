@@ -267,42 +267,28 @@ struct RefineMax {
   }
 };
 
-__device__ __forceinline__ int lane_id() { return threadIdx.x & 63; }
-
-// wave-aggregated queue append: every lane with `want` gets a distinct slot
-// (or -1 once the queue is full); one atomic per wave
-__device__ __forceinline__ int wave_append(bool want, int32_t* counter, int cap) {
-  const uint64_t mask = __ballot(want);
-  if (!mask) return -1;
-  const int leader = __ffsll((unsigned long long)mask) - 1;
-  int base = 0;
-  if (lane_id() == leader) base = atomicAdd(counter, __popcll(mask));
-  base = __shfl(base, leader, 64);
-  const int rank = __popcll(mask & ((1ull << lane_id()) - 1ull));
-  const int slot = base + rank;
-  return (want && slot < cap) ? slot : -1;
-}
-
 // rows bin A takes: |N| <= 8 (GA = 1, 4 or 8), else |N| <= GA
 __device__ __forceinline__ int small_limit(int GA) { return GA <= 4 ? 8 : GA; }
 // stride of a row's slot in slotA
 __device__ __forceinline__ int slot_stride(int GA) { return GA <= 4 ? 8 : GA; }
 
-// Communication inside a group of G lanes (G = 8, 16 or 32; groups are
+// Communication inside a group of G lanes (G = 8 or 16; groups are
 // aligned runs of G lanes of a wavefront).
 //
 // gpart: the value of a partner lane for a butterfly-like reduction.  Steps 1
 // and 2 pair lanes inside a quad (DPP quad_perm [1,0,3,2] and [2,3,0,1]), step
 // 4 mirrors the halves of 8 lanes (DPP row_half_mirror), step 8 mirrors the
-// halves of 16 (DPP row_mirror), step 16 swaps the halves of 32 (ds_swizzle
-// xor 16).  After the steps up to G/2 every lane holds the group's reduction.
+// halves of 16 (DPP row_mirror).  After the steps up to G/2 every lane holds the
+// group's reduction.
 template <int STEP>
 __device__ __forceinline__ int gpart(int v) {
   if constexpr (STEP == 1) return __builtin_amdgcn_update_dpp(v, v, 0xB1, 0xF, 0xF, false);
   else if constexpr (STEP == 2) return __builtin_amdgcn_update_dpp(v, v, 0x4E, 0xF, 0xF, false);
   else if constexpr (STEP == 4) return __builtin_amdgcn_update_dpp(v, v, 0x141, 0xF, 0xF, false);
-  else if constexpr (STEP == 8) return __builtin_amdgcn_update_dpp(v, v, 0x140, 0xF, 0xF, false);
-  else return __builtin_amdgcn_ds_swizzle(v, 0x1f | (0x10 << 10));
+  else {
+    static_assert(STEP == 8, "within sixteen lanes");
+    return __builtin_amdgcn_update_dpp(v, v, 0x140, 0xF, 0xF, false);
+  }
 }
 template <int STEP>
 __device__ __forceinline__ double gpartd(double v) {
@@ -315,7 +301,6 @@ __device__ __forceinline__ int group_ori(int v) {
   if constexpr (G >= 4) v |= gpart<2>(v);
   if constexpr (G >= 8) v |= gpart<4>(v);
   if constexpr (G >= 16) v |= gpart<8>(v);
-  if constexpr (G >= 32) v |= gpart<16>(v);
   return v;
 }
 
