@@ -398,6 +398,14 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(T <= 5 ? 3 :
     tile_steps<T, 0>(kf, r, c, s, bad);
     bad = group_ori<16>(bad);
 
+    // The block's entries again: in LDS its second half still stands as the gather
+    // left it, and the largest tile reads it there (held in registers through the
+    // elimination its 64 VGPRs made 63 spills).
+    auto block = [&](int a, int b) {
+      if (T == 8 && a >= HA) return gb.half[(4 * (a - HA) + r) * LD + 4 * b + c];
+      return K[a][b];
+    };
+
     // ---- solve and refine in FP64 (z stays in LDS) ----
     // z += Kinv v for the right-hand side v of this lane's rows
     auto correct = [&](const float (&x)[T], bool first) {
@@ -447,7 +455,7 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(T <= 5 ? 3 :
           for (int a = 0; a < T; ++a) {
             double p = 0.0;
 #pragma unroll
-            for (int b = 0; b < T; ++b) p = fma(-K[a][b], zc[b], p);
+            for (int b = 0; b < T; ++b) p = fma(-block(a, b), zc[b], p);
             p = gb.f[r * 8 + a] + quad_sum(p);
             rn = fmax(rn, fabs(p));
             if (!(p == p)) rn = __builtin_huge_val();  // (fmax drops a NaN)
