@@ -669,7 +669,7 @@ int enqueue_symbolic(clair_ctx* c, Batch& b, hipStream_t s, bool validate, bool 
   if (capture_check(c->capturing, s, "k_count", __LINE__)) return CLAIR_ERR_HIP;
   timing_mark(c, timing, s, "count");
   if (b.any_near && !(b.w.skip & 1)) {
-    HIPCHK(launch_count_mid(b.w, occupancy_blocks(c, 8), s));
+    HIPCHK(launch_count_mid(b.w, c->cus, s));
     if (capture_check(c->capturing, s, "k_count_mid", __LINE__)) return CLAIR_ERR_HIP;
   }
   if (b.any_far && !(b.w.skip & 1)) {

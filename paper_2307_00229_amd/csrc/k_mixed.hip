@@ -727,14 +727,15 @@ __global__ __launch_bounds__(kNT) void k_count(Work w) {
 // matrix has one); larger rows are left unsized for k_count_big.  Then the
 // chunk's bookkeeping.
 //
-// Bound: latency at two wavefronts per SIMD (the register set).  Workgroups of
-// 256 threads size a chunk's rows (114 to 256 of 1024 points) in one turn: with
-// 128 threads 1024^2 nine-point rows at distance 1 took 65 us for every second
-// point a C-point and 53 for every third, 50 and 45 so; 80^3 seven-point rows at
-// distance 2 without the adjacency 283 and 242 us a call.  (128 are better where a
-// chunk has few rows: 48 of 24 points, 80 us against 97.)
-template <int W>
-__global__ __launch_bounds__(kNT) void k_count_mid(Work w) {
+// Bound: latency at two wavefronts per SIMD (the register set), so the number of
+// threads decides how many chunks a CU has at once against how long one takes.
+// Up to four chunks a CU workgroups of 256 threads are better on grids: 1024^2
+// nine-point rows at distance 1, every third point a C-point, 144 us a call (128
+// threads: 152, 64: 177), every second 204 (218); 80^3 seven-point at distance 2
+// without the adjacency 244 (283).  Beyond, 128 threads: 2900^2 nine-point 983 us
+// (256: 1,044), 80,000 rows of 24 points 487 (554); 2048^2 517 and 514.
+template <int W, int NT>
+__global__ __launch_bounds__(NT) void k_count_mid(Work w) {
   __shared__ int s_rows[kMaxChunk];
   __shared__ int16_t s_size[kMaxChunk];
   __shared__ int s_scan[kNT];
@@ -756,7 +757,7 @@ __global__ __launch_bounds__(kNT) void k_count_mid(Work w) {
   const int nc = w.chunk_nc[c];
   if (tid == 0) { s_flag[0] = 0; s_flag[1] = 0; s_flag[2] = 0; s_flag[3] = 0; s_nlist = 0; }
   __syncthreads();
-  for (int t = tid; t < nc; t += kNT) {
+  for (int t = tid; t < nc; t += NT) {
     s_rows[t] = w.clocal[base + t];
     const int sz = w.lnz[base + t];
     s_size[t] = (int16_t)sz;
@@ -766,7 +767,7 @@ __global__ __launch_bounds__(kNT) void k_count_mid(Work w) {
   const int SA = slot_stride(w.GA);
   const int lim = small_limit(w.GA);
   const int nl = s_nlist;
-  for (int k = tid; k < nl; k += kNT) {
+  for (int k = tid; k < nl; k += NT) {
     const int t = s_list[k];
     const int i = s_rows[t];
     RegSetA<32> S;
@@ -2319,14 +2320,22 @@ hipError_t launch_count(const Work& w, hipStream_t s) {
   return hipGetLastError();
 }
 
-hipError_t launch_count_mid(const Work& w, int blocks, hipStream_t s) {
+hipError_t launch_count_mid(const Work& w, int cus, hipStream_t s) {
   if (w.nchunks == 0) return hipSuccess;
-  const dim3 grid(std::min(w.nchunks, std::max(1, blocks))), block(kNT);
-  if (w.adj_w == 0) hipLaunchKernelGGL(k_count_mid<0>, grid, block, 0, s, w);
-  else if (w.adj_w == 4) hipLaunchKernelGGL(k_count_mid<4>, grid, block, 0, s, w);
-  else if (w.adj_w == 8) hipLaunchKernelGGL(k_count_mid<8>, grid, block, 0, s, w);
-  else return hipErrorInvalidValue;
-  return hipGetLastError();
+  const dim3 grid(std::min(w.nchunks, std::max(8, cus * 8)));
+#define CLAIR_MID(WW, NTT)                                                             \
+  if (w.adj_w == WW && (NTT == 256) == (w.nchunks <= 4 * cus)) {                       \
+    hipLaunchKernelGGL((k_count_mid<WW, NTT>), grid, dim3(NTT), 0, s, w);              \
+    return hipGetLastError();                                                          \
+  }
+  CLAIR_MID(0, 256)
+  CLAIR_MID(4, 256)
+  CLAIR_MID(8, 256)
+  CLAIR_MID(0, 128)
+  CLAIR_MID(4, 128)
+  CLAIR_MID(8, 128)
+#undef CLAIR_MID
+  return hipErrorInvalidValue;
 }
 
 hipError_t launch_count_wide(const Work& w, int blocks, hipStream_t s) {
