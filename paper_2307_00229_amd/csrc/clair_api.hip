@@ -604,8 +604,9 @@ int enqueue_numeric(clair_ctx* c, Batch& b, hipStream_t s, bool timing, const Co
       HIPCHK(launch_rows8(b.w, c->wg_threads, c->cus, s));
     } else if (c->group <= 8) {
       // 4 and 8 both take the quad solver: eight lanes per row were slower on
-      // every batch (105 against 134 us on 16 matrices of 129^2 to 515^2,
-      // 667 against 990 us on 64 of 64^2 to 768^2)
+      // five-point batches (134 against 107 us on 16 matrices of 129^2 to 515^2,
+      // 990 against 667 us on 64 of 64^2 to 768^2) and as fast on nine-point rows
+      // at distance 1 (see k_quad.hip)
       HIPCHK(launch_quad8(b.w, c->wg_threads, c->cus, s));
     } else {
       if (int rc = enqueue_tile(c, b, 0, sized, s)) return rc;

@@ -14,10 +14,13 @@
 // points leaves the row to k_rows_wg.
 //
 // Bound: the latency of s steps with one barrier each, hidden by four workgroups
-// per CU (128 VGPRs and 37 KB of LDS each).  The blocked LU of k_rows_wg holds
+// per CU (128 VGPRs, 53 more spilled to 216 bytes of scratch a lane, and 34.9 KB
+// of LDS: one kernel serves T = 3 to 8).  The blocked LU of k_rows_wg holds
 // its block in LDS (one workgroup per CU), takes two barriers and a pass over
 // LDS per column and solves triangles in every correction: 2,500 rows of up to
-// 108 points (150^2 nine-point at distance 5) take 3,385 us there, 310 here.
+// 108 points (150^2 nine-point at distance 5) take 3,385 us there, 295 here.  A
+// block of more entries than the lists hold pays for the search and the count in
+// vain: 300 rows of 128 points with about 100 entries a row, 57 us of 2,020.
 // The matrix cores have nothing to add at this size: the whole elimination is
 // 4 MFLOP a row, and a 32-column panel would still be 32 dependent steps.
 #include <hip/hip_runtime.h>

@@ -2136,8 +2136,6 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void k
   if (tid == 0 && s_unc) atomicAdd((unsigned long long*)&w.st[m].n_uncovered, (unsigned long long)s_unc);
 }
 
-// a numeric pass without the symbolic pass before it: projection sums of all
-// fine points to zero, and R.row_ptr[n_c] of every matrix
 // Column maxima for the strength test: cmax[v] = max over w != v of |a_wv|,
 // for every matrix of the batch (batch-wide fine numbering).  Non-negative
 // doubles order like their bit patterns, so an unsigned 64-bit atomic max
@@ -2254,6 +2252,9 @@ __global__ void k_fill_i32(int32_t* a, int64_t n, int32_t v) {
   for (int64_t g = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; g < n; g += (int64_t)gridDim.x * blockDim.x) a[g] = v;
 }
 
+// A numeric pass without the symbolic pass before it (a plan's execute): the
+// projection's column lists of all fine points emptied, and R.row_ptr[n_c] of
+// every matrix.
 __global__ void k_clear_sums(Work w, int64_t n) {
   for (int64_t j = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; j < n; j += (int64_t)gridDim.x * blockDim.x)
     w.chead[j] = -1;

@@ -28,10 +28,12 @@ namespace {
 // the quad reads each row of A together, all of a row's entries are in flight
 // at once, the next row's bookkeeping is loaded one row ahead, and the column
 // lists' exchanges are collected one row later.  64 five-point matrices of
-// 64^2 to 768^2 (3.19 M rows): 730 us with one lane per row of A and waited
+// 64^2 to 768^2 (3.65 M rows): 730 us with one lane per row of A and waited
 // exchanges, 717 with the shared gather, 667 with the two latency steps; 16
-// matrices of 129^2 to 515^2: 105 us, where eight lanes per row took
-// 134.
+// matrices of 129^2 to 515^2 (484,487 rows): 107 us, where eight lanes per row
+// took 134.  Rows of A of six entries and more take a second trip: nine-point
+// rows at distance 1 are as fast as with eight lanes per row, no faster
+// (1024^2, every second point a C-point: 84 and 87 us, every third: 54 and 51).
 // ---------------------------------------------------------------------------
 // lane src of the quad, to all four (src is a constant once the calling loops
 // are unrolled, so the switch folds to one DPP move)

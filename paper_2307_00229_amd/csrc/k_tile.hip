@@ -12,13 +12,17 @@
 //
 // Gather: eight lanes read a row of A together (its ninth entry by one lane per
 // row), every load in flight at once; each entry is located in N and the block
-// goes through LDS in two halves, so that LDS (2.8 KB a row at 24 points) allows
-// fewer wavefronts than the registers do (two per SIMD above 20 points, where
-// three spill: 922 against 1,495 us at 24; three up to 20, four at 12).
+// goes through LDS in two halves, so that LDS (3.5 KB a row at 24 points) does not
+// allow fewer wavefronts than the registers do: two per SIMD above 20 points
+// (three spill: 922 against 1,495 us at 24), three up to 20 (at 20 points with
+// four VGPRs spilled), four at 12 (128 VGPRs).
 //
 // Bound: VALU issue (about 70% busy).  466,489 rows of 24 points (2048^2
-// nine-point): 1,260 us with one lane per block row, 922 here; 262,144 rows of
-// up to 18 points (128^3 seven-point): 467 and 352.
+// nine-point): 1,260 us with one lane per block row, 927 here; 262,144 rows of
+// up to 18 points (128^3 seven-point): 467 and 334.  Whole calls on 120,000 rows
+// of 32 points, distance 1: 1,026 and 895 us (976 with one lane per block row in
+// bin A of 32); dense blocks of 32 points, 40 entries a row of A, gain nothing
+// (408 and 403).
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
