@@ -166,7 +166,7 @@ struct MatStatus {
 struct Counters {
   int32_t total_rows;  // sum of n_c over all matrices
   int32_t nA;          // rows of bin A
-  int32_t nB;          // rows for the 32-lane solver (GA < |N| <= 32)
+  int32_t nB;          // rows of bin B (above bin A, at most 32 points)
   int32_t nC;          // rows queued for the workgroup solver (larger, or FP32 not trusted)
   int32_t nbig;        // rows with more than 32 points queued for k_count_big
   int32_t nmid;        // chunks k_count left to k_count_mid (queued in midq)
