@@ -733,7 +733,11 @@ __global__ __launch_bounds__(kNT) void k_count(Work w) {
 // nine-point rows at distance 1, every third point a C-point, 144 us a call (128
 // threads: 152, 64: 177), every second 204 (218); 80^3 seven-point at distance 2
 // without the adjacency 244 (283).  Beyond, 128 threads: 2900^2 nine-point 983 us
-// (256: 1,044), 80,000 rows of 24 points 487 (554); 2048^2 517 and 514.
+// (256: 1,044), 120,000 rows of 24 points 487 (554); 2048^2 517 and 514.  The rule
+// looks at the chunks only, so up to four a CU chunks of few rows each pay for
+// it: 40,000 rows of 24 points in 940 chunks 227 us a call with 256 threads, 203
+// with 128.  A grid's C-points fill every third chunk or so, so the mean over the
+// chunks, all that the host could know, does not tell the two apart.
 template <int W, int NT>
 __global__ __launch_bounds__(NT) void k_count_mid(Work w) {
   __shared__ int s_rows[kMaxChunk];

@@ -289,7 +289,8 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(T <= 5 ? 3 :
     // per row (where z will stand), so that the second pass reads no others again;
     // beyond 64 of them it reads all.  40,000 rows of 24 points whose rows of A
     // have about 45 entries: 676 us a call with every entry read and located in
-    // both passes, one at a time, 450 here (one lane per block row: 560).
+    // both passes, one at a time, 450 here (one lane per block row: 560), all with
+    // 128 threads a workgroup in the symbolic pass; 475 with its 256 of today.
     uint64_t* later = reinterpret_cast<uint64_t*>(gb.z);
     auto rest1 = [&]() {
       uint64_t m[NL] = {};
